@@ -1,0 +1,41 @@
+/*
+ * Instances of gemm_dma_kernel (hap_gemm_kernels.h): bf16 operands, bf16 or fp32 output.
+ */
+#include "hap_gemm_kernels.h"
+
+namespace hap_gemm_detail {
+
+namespace {
+
+template <typename TC, bool AKC, bool BKC, int BM, int BN, int WGM, int WGN>
+int launch(const GemmArgs& a, int groups, hipStream_t st) {
+  constexpr int BK = 64, STAGES = 2;
+  static bool configured[64] = {};
+  return launch_lds_kernel<TC, BM, BN>(&gemm_dma_kernel<TC, AKC, BKC, BM, BN, BK, WGM, WGN, STAGES>, configured,
+                                       (size_t)STAGES * (BM + BN) * BK * 2, 64 * WGM * WGN, a, groups, st);
+}
+
+template <typename TC>
+int tiles(const hap_gemm_problem* p, const GemmArgs& a, int bm, int groups, hipStream_t st) {
+  if (bm == 128) {
+    if (p->a_kcontig && p->b_kcontig) return launch<TC, true, true, 128, 128, 2, 2>(a, groups, st);
+    if (p->a_kcontig) return launch<TC, true, false, 128, 128, 2, 2>(a, groups, st);
+    if (!p->b_kcontig) return launch<TC, false, false, 128, 128, 2, 2>(a, groups, st);
+    return launch<TC, false, true, 128, 128, 2, 2>(a, groups, st);
+  }
+  // 256-tiles outside the ping-pong kernel: both operands K-contiguous, or a short contraction (A M-contiguous with B
+  // K-contiguous always takes the ping-pong kernel, so that layout of the two-stage kernel is not built at this size)
+  if (p->a_kcontig && p->b_kcontig) return launch<TC, true, true, 256, 256, 2, 4>(a, groups, st);
+  if (p->a_kcontig) return launch<TC, true, false, 256, 256, 2, 4>(a, groups, st);
+  if (!p->b_kcontig) return launch<TC, false, false, 256, 256, 2, 4>(a, groups, st);
+  return hap_fail(HAP_EDEVICE, "internal: no 256-tile two-stage kernel for this layout");
+}
+
+}  // namespace
+
+int run_dma(const hap_gemm_problem* p, const GemmArgs& a, int bm, int bn, int groups, hipStream_t st) {
+  (void)bn;
+  return p->c_dtype == HAP_BF16 ? tiles<__bf16>(p, a, bm, groups, st) : tiles<float>(p, a, bm, groups, st);
+}
+
+}  // namespace hap_gemm_detail
