@@ -19,7 +19,8 @@
  *
  * Kernels.  gemm_pp_kernel: bf16, 256 x 256 tiles, two wave groups that alternate a memory phase and a matrix phase over a
  * 4-stage ring of direct-to-LDS K tiles (all layouts but "both operands K-contiguous").  gemm_dma_kernel: bf16, two-stage ring,
- * 256 x 256 (both operands K-contiguous) and 128 x 128 (small outputs, remainder strips).  gemm_kernel: register-staged, fp32
+ * 256 x 256 (both operands K-contiguous) and 128 x 128 (small outputs, remainder strips).  gemm_kpair_kernel: bf16, 128 x 128, at
+ * most one tile per compute unit, two wave groups that split the tile's contraction.  gemm_kernel: register-staged, fp32
  * and what the direct kernels cannot address.  gemm_skinny_f32_kernel: fp32 products of at most 64 rows, contraction split over
  * the waves of a workgroup.  gemm_generic_kernel: scalar fallback.  Epilogues: bias, GeLU, pre-activation copy, fp32
  * accumulation, or the product times gelu'(saved pre-activation) - the activation backward of the layer that produced the
@@ -323,6 +324,43 @@ double small_tiles_time(long long n) {
 
 inline long long cdiv(long long a, long long b) { return (a + b - 1) / b; }
 
+/* Whether 128-tiles of this product run in gemm_kpair_kernel: at most one tile per compute unit, and two K tiles for each of its two
+ * wave groups.  Against the 4-wave kernel, which fills the chip by splitting K over workgroups (microseconds, forward, MI355X):
+ * 3940 x 1024 outputs over K = 1024 / 4096 29 / 47 -> 15 / 37, 1024 x 1024 over 1024 24 -> 12, 4096 x 1000 over 8192 77 -> 67.
+ * The exceptions: tile counts that leave compute units idle here but not there (93 tiles: two splits 73 %, five half-size
+ * workgroups 91 %) where the contraction is long enough for that to outweigh the reduction (3873 x 286 over 3648: 29 against 25.5;
+ * 144 tiles over K = 768: 12 against 26), and short bwd-data products of very few tiles, where the launch is all there is (144 x 816
+ * over 1088: 13.0 against 12.3).
+ * (An M-contiguous A with a K-contiguous B is a form no product of the path has; the kernel is not built for it.) */
+bool kpair_applies(const hap_gemm_problem* p, long long tiles, long long nk) {
+  const long long cus = cu_count();
+  if (p->in_dtype != HAP_BF16 || (!p->a_kcontig && p->b_kcontig) || tiles > cus || nk < 4) return false;
+  if (p->a_kcontig && p->b_kcontig && tiles * 8 <= cus && nk <= 20) return false;
+  const long long here = cus / tiles * tiles * 2, there = 2 * cus / tiles * tiles;      // of 2 * cus wave groups
+  return nk <= 40 || !p->ws || here * 20 >= there * 17;
+}
+
+/* Into how many workgroups that kernel splits K (1: no partial tiles, no reduction launch) and the estimated time in microseconds.
+ * Measured: a step (a K tile for each wave group) takes 0.6 with few compute units busy and 0.9 with all, 1.15 there over long
+ * contractions, whose operands stream from HBM (256 tiles, K = 50432: 462 in all against 345 for 64 256-tiles with K split in
+ * four); 6 for prologue, exchange and epilogue, 4 / 1.5 more for GeLU / its backward in an epilogue that runs on few compute units
+ * only; a reduction launch 1.2 and 0.03 per partial tile written and read back.  128 tiles over K = 1024: whole 13, split in
+ * two 23; 64 tiles over K = 4096: whole 28, split in four 23. */
+int kpair_splits(const hap_gemm_problem* p, long long tiles, long long nk, size_t ws_splits, double* us) {
+  const long long cus = cu_count();
+  int best = 1;
+  *us = 0.0;
+  for (int s = 1; s <= 16; ++s) {
+    if (s > 1 && (tiles * s > cus || nk < 4 * s || (size_t)s > ws_splits)) break;
+    const long long steps = cdiv(nk, 2 * s);
+    const double busy = (double)(tiles * s) / (double)cus;
+    double t = (double)steps * (steps > 64 && busy > 0.5 ? 1.15 : 0.6 + 0.3 * busy) + 6.0;
+    t += s > 1 ? 1.2 + 0.03 * (double)(tiles * s) : (p->act != HAP_ACT_NONE ? 4.0 : (p->dact != HAP_ACT_NONE ? 1.5 : 0.0));
+    if (s == 1 || t < *us) { best = s; *us = t; }
+  }
+  return best;
+}
+
 /* The sub-problem of p over logical rows [m_lo, m_hi) and columns [n_lo, n_hi). */
 hap_gemm_problem sub_problem(const hap_gemm_problem* p, int64_t m_lo, int64_t m_hi, int64_t n_lo, int64_t n_hi, int tile) {
   hap_gemm_problem q = *p;
@@ -443,7 +481,10 @@ static int run_auto_tiled(const hap_gemm_problem* p, const Plan& pl, void* strea
   auto strip_time = [&](long long big_tiles, long long small_tiles, int* tile) {
     if (big_tiles < kCUs && nk > 0) {
       const double round_us = (double)nk * 2.0 + 7.0;
-      const double tb = few_tiles_us(big_tiles, kCUs, 2.0, 7.0, 0.025), ts = few_tiles_us(small_tiles, 2 * kCUs, 1.05, 5.0, 0.00625);
+      const double tb = few_tiles_us(big_tiles, kCUs, 2.0, 7.0, 0.025);
+      double ts = few_tiles_us(small_tiles, 2 * kCUs, 1.05, 5.0, 0.00625);
+      if (kpair_applies(p, small_tiles, nk))
+        kpair_splits(p, small_tiles, nk, can_split_k ? p->ws_bytes / ((size_t)small_tiles * 128 * 128 * sizeof(float)) : 0, &ts);
       *tile = tb <= ts ? 256 : 128;
       return (tb <= ts ? tb : ts) / round_us;
     }
@@ -614,6 +655,7 @@ int hap_gemm_run(const hap_gemm_problem* p, void* stream) {
     a.cdelta = a.vec_store ? ((skew_c - pl.skewN) % cepc + cepc) % cepc : 0;
   }
   a.ntiles = 0;
+  a.kpair = 0;
   a.ksplit = 1;
   a.partial = nullptr;
   {
@@ -637,6 +679,13 @@ int hap_gemm_run(const hap_gemm_problem* p, void* stream) {
       if (per_split * (size_t)g > p->ws_bytes) g = (long long)(p->ws_bytes / per_split);
       a.ksplit = (int)g;
       a.partial = static_cast<float*>(p->ws);
+    }
+    if (pl.dma && pl.bm == 128 && kpair_applies(p, out_tiles, a.ntiles)) {
+      const size_t ws_splits = p->ws ? p->ws_bytes / per_split : 0;
+      double us;
+      a.kpair = 1;
+      a.ksplit = kpair_splits(p, out_tiles, a.ntiles, ws_splits, &us);
+      a.partial = a.ksplit > 1 ? static_cast<float*>(p->ws) : nullptr;
     }
   }
   if (p->in_dtype == HAP_BF16 && p->c_dtype == HAP_BF16) return dispatch_tile<__bf16, __bf16>(p, pl, a, groups, st);

@@ -1,5 +1,5 @@
 /*
- * Instances of gemm_dma_kernel (hap_gemm_kernels.h): bf16 operands, bf16 or fp32 output.
+ * Instances of gemm_dma_kernel and gemm_kpair_kernel (hap_gemm_kernels.h): bf16 operands, bf16 or fp32 output.
  */
 #include "hap_gemm_kernels.h"
 
@@ -15,8 +15,19 @@ int launch(const GemmArgs& a, int groups, hipStream_t st) {
                                        (size_t)STAGES * (BM + BN) * BK * 2, 64 * WGM * WGN, a, groups, st);
 }
 
+template <typename TC, bool AKC, bool BKC>
+int launch_kpair(const GemmArgs& a, int groups, hipStream_t st) {
+  static bool configured[64] = {};
+  return launch_lds_kernel<TC, 128, 128>(&gemm_kpair_kernel<TC, AKC, BKC>, configured, (size_t)2 * 2 * (128 + 128) * 64 * 2, 512, a, groups, st);
+}
+
 template <typename TC>
 int tiles(const hap_gemm_problem* p, const GemmArgs& a, int bm, int groups, hipStream_t st) {
+  if (a.kpair) {
+    if (p->a_kcontig && p->b_kcontig) return launch_kpair<TC, true, true>(a, groups, st);
+    if (p->a_kcontig) return launch_kpair<TC, true, false>(a, groups, st);
+    return launch_kpair<TC, false, false>(a, groups, st);     // (an M-contiguous A with a K-contiguous B is never paired)
+  }
   if (bm == 128) {
     if (p->a_kcontig && p->b_kcontig) return launch<TC, true, true, 128, 128, 2, 2>(a, groups, st);
     if (p->a_kcontig) return launch<TC, true, false, 128, 128, 2, 2>(a, groups, st);

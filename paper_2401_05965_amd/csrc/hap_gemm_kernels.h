@@ -56,6 +56,7 @@ struct GemmArgs {
   int vec_store;       // C (and preact) rows are 16-byte addressable: whole-chunk stores allowed
   int cdelta;          // columns by which tile columns are shifted in the store patch so that its 16-byte chunks coincide with
                        // 16-byte chunks of C's address space (0 when C has the B operand's phase; see epilogue_transposed)
+  int kpair;           // 1: gemm_kpair_kernel
   int ksplit;          // >1: each output tile is computed by ksplit workgroups over disjoint K-tile ranges, fp32 partials go to `partial`
   float* partial;      // [group][tile][ksplit][BM][BN] fp32 workspace when ksplit > 1
   int ntiles;          // K tiles (of 64) over all segments
@@ -436,6 +437,16 @@ __device__ __forceinline__ BlockPos block_pos(const GemmArgs& args) {
   return b;
 }
 
+/* The arguments of the epilogue that leaves a split's raw fp32 tile [bm][bn] in the workspace: bias, activation and the real store
+ * happen in the reduction kernel. */
+__device__ __forceinline__ GemmArgs partial_outputs(const GemmArgs& args, const BlockPos& bp, int bm, int bn) {
+  GemmArgs pa = args;
+  pa.c = args.partial + (((long long)bp.grp * (gridDim.x / args.ksplit) + bp.out_tile) * args.ksplit + bp.split) * (bm * bn);
+  pa.ldc = bn; pa.M = bm; pa.N = bn; pa.skewM = 0; pa.skewN = 0;
+  pa.preact = nullptr; pa.bias = nullptr; pa.act = HAP_ACT_NONE; pa.accumulate = 0; pa.vec_store = 1; pa.cdelta = 0; pa.dact_preact = nullptr;
+  return pa;
+}
+
 /* Writes a wave's TM x TN accumulator tiles.  Accumulator element e of lane l is row
  * (e/4)*8 + (l/32)*4 + e%4, column l%32 of its 32x32 tile.  (row0, col0): physical origin of the
  * wave tile; rows / columns outside the logical extent are dropped. */
@@ -484,7 +495,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_kernel(const GemmArgs arg
   const int wm0 = (wave / WGN) * WTM, wn0 = (wave % WGN) * WTN;
   // With split-K, ksplit consecutive workgroups share an output tile and take consecutive K-tile ranges.
   const BlockPos bp = block_pos(args);
-  const int ksplit = args.ksplit, out_tile = bp.out_tile, split = bp.split, tm = bp.tm, tn = bp.tn;
+  const int ksplit = args.ksplit, split = bp.split, tm = bp.tm, tn = bp.tn;
   const int m0 = tm * BM, n0 = tn * BN;                 // physical tile origin
   const GroupView gv = group_view(args, bp.grp);
   const int m_lim = args.skewM + gv.M, n_lim = args.skewN + args.N;
@@ -570,11 +581,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_kernel(const GemmArgs arg
   }
 
   if (ksplit > 1) {
-    // raw fp32 partial tile [BM][BN]; bias, activation and the real store happen in the reduction kernel
-    GemmArgs pa = args;
-    pa.c = args.partial + (((long long)bp.grp * (gridDim.x / ksplit) + out_tile) * ksplit + split) * (BM * BN);
-    pa.ldc = BN; pa.M = BM; pa.N = BN; pa.skewM = 0; pa.skewN = 0;
-    pa.preact = nullptr; pa.bias = nullptr; pa.act = HAP_ACT_NONE; pa.accumulate = 0; pa.vec_store = 1; pa.cdelta = 0; pa.dact_preact = nullptr;
+    const GemmArgs pa = partial_outputs(args, bp, BM, BN);
     epilogue<T, float, TM, TN>(pa, acc, wm0, wn0, lane);
     return;
   }
@@ -844,18 +851,22 @@ struct DmaLoader {
 
   /* Edge tile: validity along k decided per chunk; the tile offset (which may be "negative" for the
    * rows a skewed first tile does not use) is added per lane so valid chunks get an exact offset. */
+  __device__ __forceinline__ unsigned edge_offset(int i, int tid, unsigned toff, int k0, int kskew, int kend) const {
+    int row, c;
+    where(tid + i * NT, &row, &c);
+    bool ok;
+    if constexpr (KC) { const int kp = k0 + c * EPC; ok = kp < kend && kp + EPC > kskew; }
+    else { const int kl = k0 + row; ok = kl >= kskew && kl < kend; }
+    return ok && base[i] != kOobOffset ? base[i] + toff : kOobOffset;
+  }
+  __device__ __forceinline__ void edge_offsets(unsigned (&off)[CPT], int tid, unsigned toff, int k0, int kskew, int kend) const {
+#pragma unroll
+    for (int i = 0; i < CPT; ++i) off[i] = edge_offset(i, tid, toff, k0, kskew, kend);
+  }
   __device__ __forceinline__ void issue_edge(__amdgpu_buffer_rsrc_t rsrc, char* lds, int tid, unsigned toff, int k0, int kskew, int kend) const {
     const int wave_first = (tid & ~63);
 #pragma unroll
-    for (int i = 0; i < CPT; ++i) {
-      int row, c;
-      where(tid + i * NT, &row, &c);
-      bool ok;
-      if constexpr (KC) { const int kp = k0 + c * EPC; ok = kp < kend && kp + EPC > kskew; }
-      else { const int kl = k0 + row; ok = kl >= kskew && kl < kend; }
-      ok = ok && base[i] != kOobOffset;
-      dma16(rsrc, lds + (wave_first + i * NT) * 16, ok ? base[i] + toff : kOobOffset, 0);
-    }
+    for (int i = 0; i < CPT; ++i) dma16(rsrc, lds + (wave_first + i * NT) * 16, edge_offset(i, tid, toff, k0, kskew, kend), 0);
   }
 
   /* After the edge tile landed: zero elements outside [kskew, kend) in this thread's own chunks. */
@@ -896,7 +907,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, (WGM * WGN <= 4 ? 2 : 1))   /* the 
   const int wm0 = (wave / WGN) * WTM, wn0 = (wave % WGN) * WTN;
   // With split-K, ksplit consecutive workgroups share an output tile and take consecutive K-tile ranges.
   const BlockPos bp = block_pos(args);
-  const int ksplit = args.ksplit, out_tile = bp.out_tile, split = bp.split, tm = bp.tm, tn = bp.tn;
+  const int ksplit = args.ksplit, split = bp.split, tm = bp.tm, tn = bp.tn;
   const int m0 = tm * BM, n0 = tn * BN;
   const GroupView gv = group_view(args, bp.grp);
   const int m_lim = args.skewM + gv.M, n_lim = args.skewN + args.N;
@@ -1048,11 +1059,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, (WGM * WGN <= 4 ? 2 : 1))   /* the 
 
   __syncthreads();   // every wave is done reading the ring: reuse it as per-wave store patches
   if (ksplit > 1) {
-    // raw fp32 partial tile [BM][BN]; bias, activation and the real store happen in the reduction kernel
-    GemmArgs pa = args;
-    pa.c = args.partial + (((long long)bp.grp * (gridDim.x / ksplit) + out_tile) * ksplit + split) * (BM * BN);
-    pa.ldc = BN; pa.M = BM; pa.N = BN; pa.skewM = 0; pa.skewN = 0;
-    pa.preact = nullptr; pa.bias = nullptr; pa.act = HAP_ACT_NONE; pa.accumulate = 0; pa.vec_store = 1; pa.cdelta = 0; pa.dact_preact = nullptr;
+    const GemmArgs pa = partial_outputs(args, bp, BM, BN);
     epilogue_transposed<T, float, TM, TN>(pa, acc, wm0, wn0, lane, smem + wave * (32 * (TN * 32 * 4 + 16)));
     return;
   }
@@ -1146,7 +1153,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_pp_kernel(const GemmArgs 
   const int wm0 = (wave / WGN) * WTM, wn0 = (wave % WGN) * WTN;
   const bool late_group = wave >= NW / 2;            // waves w and w + NW/2 share a SIMD
   const BlockPos bp = block_pos(args);
-  const int ksplit = args.ksplit, out_tile = bp.out_tile, split = bp.split, tm = bp.tm, tn = bp.tn;
+  const int ksplit = args.ksplit, split = bp.split, tm = bp.tm, tn = bp.tn;
   const int m0 = tm * BM, n0 = tn * BN;
   const GroupView gv = group_view(args, bp.grp);
   const int m_lim = args.skewM + gv.M, n_lim = args.skewN + args.N;
@@ -1288,15 +1295,225 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_pp_kernel(const GemmArgs 
   HAP_EXP_STAMP(2);
 
   if (ksplit > 1) {
-    GemmArgs pa = args;
-    pa.c = args.partial + (((long long)bp.grp * (gridDim.x / ksplit) + out_tile) * ksplit + split) * (BM * BN);
-    pa.ldc = BN; pa.M = BM; pa.N = BN; pa.skewM = 0; pa.skewN = 0;
-    pa.preact = nullptr; pa.bias = nullptr; pa.act = HAP_ACT_NONE; pa.accumulate = 0; pa.vec_store = 1; pa.cdelta = 0; pa.dact_preact = nullptr;
+    const GemmArgs pa = partial_outputs(args, bp, BM, BN);
     epilogue_transposed<T, float, TM, TN>(pa, acc, wm0, wn0, lane, smem + wave * (32 * (TN * 32 * 4 + 16)));
     return;
   }
   epilogue_transposed<T, TC, TM, TN>(group_outputs(args, gv, bp.grp), acc, m0 + wm0, n0 + wn0, lane, smem + wave * (32 * (TN * 32 * (int)sizeof(TC) + 16)));
   HAP_EXP_STAMP(3);
+}
+
+/* ---------------------------------------------------------------------------------------------
+ * bf16 kernel for outputs of few 128 x 128 tiles: two wave groups share ONE tile, each contracts its half of the workgroup's K
+ * tiles in a ring of its own, and the halves meet in LDS before the epilogue, of which each group does one half.
+ *
+ * Such outputs (at most one tile per compute unit) need the contraction split to put two waves on every SIMD.  Split over two
+ * workgroups it costs the fp32 partial tiles and a dependent reduction launch; here the split stays inside the compute unit.
+ *
+ * The groups alternate between a memory phase and a matrix phase as in gemm_pp_kernel (waves w and w + 4 share a SIMD; group 1 runs
+ * one barrier behind): in lockstep, with one barrier per K tile for all eight waves, both waves of a SIMD wait for LDS and then both
+ * want the matrix unit (1.06 us per pair of K tiles at 248 workgroups against 0.68 for two independent workgroups).
+ * A group's tile u is read in its Mem(u); from the barrier behind it on the slot is free, and the request for tile u + 2 goes out
+ * between the MFMAs of Cmp(u).  It has Cmp(u), Mem(u+1), Cmp(u+1) to arrive: at the end of Cmp(u+1) everything but the newest
+ * request has landed.  Requests past the group's last tile are issued out of range (no memory access, zeros), so that the count
+ * of loads in flight is always the same.
+ * ------------------------------------------------------------------------------------------- */
+template <typename TC, bool AKC, bool BKC>
+__global__ __launch_bounds__(512) void gemm_kpair_kernel(const GemmArgs args) {
+  typedef __bf16 T;
+  constexpr int BM = 128, BN = 128, BK = 64, NT = 256, TM = 2, TN = 2, KK = BK / 16;
+  constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2, STAGE_BYTES = A_BYTES + B_BYTES;
+  typedef DmaLoader<AKC, BM, BK, NT> LA;
+  typedef DmaLoader<BKC, BN, BK, NT> LB;
+  constexpr int LPT = LA::CPT + LB::CPT;
+
+  extern __shared__ __attribute__((aligned(1024))) char smem_all[];
+
+  const int kg = uni((int)threadIdx.x / NT);         // wave group
+  const int tid = threadIdx.x - kg * NT, lane = tid & 63, wave = uni(tid >> 6);
+  char* const smem = smem_all + kg * (2 * STAGE_BYTES);
+  const int wm0 = (wave >> 1) * 64, wn0 = (wave & 1) * 64;
+  const BlockPos bp = block_pos(args);
+  const int ksplit = args.ksplit, tm = bp.tm, tn = bp.tn;
+  const int m0 = tm * BM, n0 = tn * BN;
+  const GroupView gv = group_view(args, bp.grp);
+  const int m_lim = args.skewM + gv.M, n_lim = args.skewN + args.N;
+  if (args.ragged == 1 && (gv.M == 0 || m0 >= m_lim)) return;
+  const int all_tiles = gv.k >= 0 ? (args.skewK + gv.k + BK - 1 >= BK ? (args.skewK + gv.k + BK - 1) / BK : 1) : args.ntiles;
+
+  LA la; LB lb;
+  la.init(tid, m0, AKC ? args.skewM : 0, m_lim, args.lda);
+  lb.init(tid, n0, BKC ? args.skewN : 0, n_lim, args.ldb);
+  PinnedFrag<AKC, BM, BK, TM, 1> fra;
+  PinnedFrag<BKC, BN, BK, TN, 1> frb;
+  fra.init(lane, wm0, lds_addr(smem));
+  frb.init(lane, wn0, lds_addr(smem));
+
+  f32x16_t acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
+
+  // the K tiles of this group: the first or the second half of the workgroup's (group 1 takes the odd one, so it never has fewer)
+  const int first_of_both = (int)((long long)all_tiles * bp.split / ksplit);
+  const int both = (int)((long long)all_tiles * (bp.split + 1) / ksplit) - first_of_both;
+  const int steps = both - both / 2;
+  const int first = first_of_both + (kg ? both / 2 : 0), ntiles = kg ? steps : both / 2;
+  int seg0 = 0, skip = first;
+  while (seg0 + 1 < args.nseg) {
+    const int in_seg = (args.skewK + args.seg[seg0].k + BK - 1) / BK;
+    if (skip < in_seg) break;
+    skip -= in_seg;
+    seg0 = uni(seg0 + 1);
+  }
+  int pseg = seg0, pk0 = skip * BK, pkend = uni(args.skewK + (gv.k >= 0 ? gv.k : args.seg[seg0].k)), prepared = 0;
+  __amdgpu_buffer_rsrc_t ra = make_rsrc(static_cast<const char*>(args.seg[seg0].a) + gv.oa, args.seg[seg0].a_bytes);
+  __amdgpu_buffer_rsrc_t rb = make_rsrc(static_cast<const char*>(args.seg[seg0].b) + gv.ob, args.seg[seg0].b_bytes);
+  int lseg = seg0, lk0 = pk0, lkend = pkend;
+
+  // offsets of the next tile to request
+  unsigned va[LA::CPT], vb[LB::CPT], soa = 0, sob = 0;
+  auto prepare = [&]() {
+    if (prepared >= ntiles) {
+#pragma unroll
+      for (int i = 0; i < LA::CPT; ++i) va[i] = kOobOffset;
+#pragma unroll
+      for (int i = 0; i < LB::CPT; ++i) vb[i] = kOobOffset;
+      soa = 0; sob = 0;
+      return;
+    }
+    if (prepared > 0) {
+      pk0 += BK;
+      if (pk0 >= pkend && pseg + 1 < args.nseg) {
+        pseg = uni(pseg + 1);
+        pk0 = 0;
+        pkend = uni(args.skewK + args.seg[pseg].k);
+        ra = make_rsrc(static_cast<const char*>(args.seg[pseg].a) + gv.oa, args.seg[pseg].a_bytes);
+        rb = make_rsrc(static_cast<const char*>(args.seg[pseg].b) + gv.ob, args.seg[pseg].b_bytes);
+      }
+    }
+    ++prepared;
+    soa = LA::tile_offset(pk0, args.skewK, args.lda); sob = LB::tile_offset(pk0, args.skewK, args.ldb);
+    if (pk0 < args.skewK || pk0 + BK > pkend) {      // first / last tile of a segment: validity per chunk
+      la.edge_offsets(va, tid, soa, pk0, args.skewK, pkend);
+      lb.edge_offsets(vb, tid, sob, pk0, args.skewK, pkend);
+      soa = 0; sob = 0;
+    } else {
+#pragma unroll
+      for (int i = 0; i < LA::CPT; ++i) va[i] = la.base[i];
+#pragma unroll
+      for (int i = 0; i < LB::CPT; ++i) vb[i] = lb.base[i];
+    }
+  };
+  auto request = [&](int slot, int i) {              // load i of LPT
+    char* const pa = smem + slot * STAGE_BYTES + (wave << 6) * 16;
+    if (i < LA::CPT) dma16(ra, pa + i * NT * 16, va[i], soa);
+    else dma16(rb, pa + A_BYTES + (i - LA::CPT) * NT * 16, vb[i - LA::CPT], sob);
+  };
+  // all but the newest request have landed: zero the awaited tile's k elements outside the logical range (own chunks only)
+  auto land = [&](int slot) {
+    wait_vmcnt<LPT>();
+    if (lk0 < args.skewK || lk0 + BK > lkend) {
+      char* const sa = smem + slot * STAGE_BYTES;
+      la.fixup(sa, tid, lk0, args.skewK, lkend);
+      lb.fixup(sa + A_BYTES, tid, lk0, args.skewK, lkend);
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    }
+    lk0 += BK;
+    if (lk0 >= lkend && lseg + 1 < args.nseg) { lseg = uni(lseg + 1); lk0 = 0; lkend = uni(args.skewK + args.seg[lseg].k); }
+  };
+
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    prepare();
+#pragma unroll
+    for (int i = 0; i < LPT; ++i) request(u, i);
+  }
+  if (ntiles > 0) land(0);
+  __builtin_amdgcn_s_barrier();                      // the first tiles are in LDS
+  if (kg) __builtin_amdgcn_s_barrier();              // group 1 runs one phase behind group 0
+
+  auto tile = [&](auto slot_tag, int u) __attribute__((always_inline)) {
+    constexpr int SLOT = decltype(slot_tag)::value;
+    // ---- Mem(u): all fragments of the tile; where the request of tile u + 2 goes
+    bf16x8_t fa[KK][TM], fb[KK][TN];
+    static_for<KK>([&](auto kk) {
+      static_for<TN>([&](auto j) { fb[kk][j] = frb.template read<SLOT * STAGE_BYTES + A_BYTES, j, kk>(); });
+      static_for<TM>([&](auto i) { fa[kk][i] = fra.template read<SLOT * STAGE_BYTES, i, kk>(); });
+    });
+    prepare();
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // this wave's reads of tile u are done
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    // ---- Cmp(u)
+    __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk)
+#pragma unroll
+      for (int x = 0; x < TM * TN; ++x) {
+        acc[x / TN][x % TN] = mfma(fb[kk][x % TN], fa[kk][x / TN], acc[x / TN][x % TN]);
+        const int at = kk * TM * TN + x;
+        if (at % 2 == 1 && at / 2 < LPT) {
+          __builtin_amdgcn_sched_barrier(0);
+          request(SLOT, at / 2);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    __builtin_amdgcn_s_setprio(0);
+    __builtin_amdgcn_sched_barrier(0);
+    if (u + 1 < ntiles) land(1 - SLOT);
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  static_assert(LPT <= KK * TM * TN / 2, "one request behind every second MFMA");
+  for (int u = 0; u < ntiles; u += 2) {
+    tile(std::integral_constant<int, 0>(), u);
+    if (u + 1 < ntiles) tile(std::integral_constant<int, 1>(), u + 1);
+  }
+  wait_vmcnt<0>();                                   // (the out-of-range requests still write zeros into the ring)
+  if (!kg) {
+    __builtin_amdgcn_s_barrier();                    // group 1's last matrix phase
+    for (int t = ntiles; t < steps; ++t) { __builtin_amdgcn_s_barrier(); __builtin_amdgcn_s_barrier(); }   // its tile more than group 0 has
+  }
+  __syncthreads();
+
+  // Each group keeps row block `kg` of its waves' tiles and hands the other one over: per register quad the 256 threads write
+  // consecutive 16-byte chunks, 32 KB per group.
+  typedef float f32x4 __attribute__((ext_vector_type(4)));
+  f32x4* const handed = reinterpret_cast<f32x4*>(smem_all) + (1 - kg) * (TN * 4 * NT);
+  const f32x4* const received = reinterpret_cast<f32x4*>(smem_all) + kg * (TN * 4 * NT);
+#pragma unroll
+  for (int j = 0; j < TN; ++j)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      f32x4 v;
+#pragma unroll
+      for (int x = 0; x < 4; ++x) v[x] = kg ? acc[0][j][q * 4 + x] : acc[1][j][q * 4 + x];
+      handed[(j * 4 + q) * NT + tid] = v;
+    }
+  __syncthreads();
+  f32x16_t sum[1][TN];
+#pragma unroll
+  for (int j = 0; j < TN; ++j)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const f32x4 v = received[(j * 4 + q) * NT + tid];
+#pragma unroll
+      for (int x = 0; x < 4; ++x) sum[0][j][q * 4 + x] = (kg ? acc[1][j][q * 4 + x] : acc[0][j][q * 4 + x]) + v[x];
+    }
+  __syncthreads();                                   // the exchange area becomes store patches
+  const int wm = wm0 + kg * 32;
+  char* const patch = smem_all + (kg * 4 + wave) * (32 * (TN * 32 * 4 + 16));
+  if (ksplit > 1) {
+    const GemmArgs pa = partial_outputs(args, bp, BM, BN);
+    epilogue_transposed<T, float, 1, TN>(pa, sum, wm, wn0, lane, patch);
+    return;
+  }
+  epilogue_transposed<T, TC, 1, TN>(group_outputs(args, gv, bp.grp), sum, m0 + wm, n0 + wn0, lane, patch);
 }
 
 /* Split-K reduction: sums the ksplit fp32 partial tiles of every output tile and applies what the

@@ -178,6 +178,16 @@ def test_linear_deep_ragged_contractions(hap, full):
     run_linear_case(hap, "bf16", 150, 264, 1210, 1, [0, 603, 1210], act=True, bias=True, full=full)        # bwd-data contracts 603 | 607 columns
 
 
+@pytest.mark.parametrize("k", [193, 256, 257, 385, 449, 768])
+def test_linear_few_tiles_share_their_contraction_between_wave_groups(hap, k):
+    """Outputs of few 128-tiles: the two wave groups of a workgroup contract the same and different numbers of K tiles (4 to 13 of
+    64, odd and even, also an empty half), ranges that start and end inside a tile, in all three products; the forward without a
+    workspace (contraction whole), the backward with one (also split over workgroups)."""
+    run_linear_case(hap, "bf16", 130, 1000, 200, 2, [0, k, 1000], act=False, bias=False, full=True)
+    run_linear_case(hap, "bf16", 1000, 136, 264, 0, [0, k, 1000], act=True, bias=True, full=True, dw_dtype="f32")
+    run_linear_case(hap, "bf16", 130, 136, 1000, 1, [0, k, 1000], act=True, bias=True, full=True)
+
+
 def test_linear_unaligned_leading_dimensions_take_the_scalar_kernel(hap):
     # compact slices whose leading dimension is not a multiple of 16 bytes
     run_linear_case(hap, "bf16", 70, 50, 90, 1, [0, 37, 90], act=True, bias=True, full=False, pad=3)
