@@ -49,20 +49,24 @@ struct SkinnyArgs {
 
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
-template <bool BKC>
+/* RB: 16-row blocks of a workgroup (blockIdx.y counts them).  1 where that still leaves every workgroup a compute unit of its own: 38
+ * rows of a 1024-wide layer are 64 workgroups of three row blocks or 192 of one, each with a third of the MFMAs and of the A
+ * traffic (the weight is then read three times, out of L2); with all rows in one workgroup (4) the weight is read once, for outputs
+ * wide enough to fill the chip by themselves. */
+template <bool BKC, int RB>
 __global__ __launch_bounds__(1024) void gemm_skinny_f32_kernel(const SkinnyArgs g) {
-  __shared__ float red[16][64][16];                  // one partial [rows][columns] tile per wave: 64 KB
+  __shared__ float red[16][16 * RB][16];             // one partial [rows][columns] tile per wave: 16 KB per row block
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, r = lane & 15, kq = lane >> 4;
-  const int n0 = blockIdx.x * 16, col = n0 + r;
-  const int rb = (g.M + 15) >> 4;                    // 16-row blocks in use
+  const int n0 = blockIdx.x * 16, col = n0 + r, row0 = blockIdx.y * (16 * RB);
+  const int rb = (g.M - row0 + 15) >> 4;             // 16-row blocks in use
   const int kslice = ((g.K + 255) >> 8) << 4;        // k values per wave, a multiple of 16
   const int kb0 = wave * kslice;
   const int kb1 = kb0 + kslice < g.K ? kb0 + kslice : g.K;      // (K is a multiple of 4: a lane's quad is inside or outside as a whole)
-  f32x4_t acc[4];
+  f32x4_t acc[RB];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) acc[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  for (int i = 0; i < RB; ++i) acc[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   for (int kb = kb0; kb < kb1; kb += 64) {
-    f32x4_t av[4][4], bv[4];
+    f32x4_t av[4][RB], bv[4];
     // all loads of four chunks first, then their MFMAs
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
@@ -77,8 +81,8 @@ __global__ __launch_bounds__(1024) void gemm_skinny_f32_kernel(const SkinnyArgs 
         }
       }
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int row = i * 16 + r;
+      for (int i = 0; i < RB; ++i) {
+        const int row = row0 + i * 16 + r;
         av[c][i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
         if (i < rb && kin && row < g.M) av[c][i] = *reinterpret_cast<const f32x4_t*>(g.a + (long long)row * g.lda + kk);
       }
@@ -88,20 +92,20 @@ __global__ __launch_bounds__(1024) void gemm_skinny_f32_kernel(const SkinnyArgs 
 #pragma unroll
       for (int x = 0; x < 4; ++x)
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < RB; ++i)
           if (i < rb) acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[c][i][x], bv[c][x], acc[i], 0, 0, 0);
   }
   // accumulator element v of lane l is output (row 4 * (l / 16) + v, column l % 16) of its 16-row block
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < RB; ++i)
 #pragma unroll
     for (int v = 0; v < 4; ++v) red[wave][i * 16 + 4 * kq + v][r] = acc[i][v];
   __syncthreads();
-  const int row = tid >> 4, c = tid & 15, n = n0 + c;
-  if (row >= g.M || n >= g.N) return;
+  const int lrow = tid >> 4, row = row0 + lrow, c = tid & 15, n = n0 + c;
+  if (lrow >= 16 * RB || row >= g.M || n >= g.N) return;
   float v = 0.f;
 #pragma unroll
-  for (int w = 0; w < 16; ++w) v += red[w][row][c];
+  for (int w = 0; w < 16; ++w) v += red[w][lrow][c];
   if (g.bias) v += g.bias[n];
   if (g.preact) g.preact[(long long)row * g.ldp + n] = v;
   if (g.act == HAP_ACT_GELU_ERF) v = gelu_erf(v);
@@ -577,9 +581,12 @@ int hap_gemm_run(const hap_gemm_problem* p, void* stream) {
     g.a = static_cast<const float*>(p->a[0]); g.b = static_cast<const float*>(p->b[0]);
     g.c = static_cast<float*>(p->c); g.preact = static_cast<float*>(p->preact); g.bias = static_cast<const float*>(p->bias);
     g.act = p->act; g.accumulate = p->accumulate;
-    const dim3 grid((unsigned)((p->N + 15) / 16));
-    if (p->b_kcontig) hipLaunchKernelGGL(gemm_skinny_f32_kernel<true>, grid, dim3(1024), 0, st, g);
-    else hipLaunchKernelGGL(gemm_skinny_f32_kernel<false>, grid, dim3(1024), 0, st, g);
+    const unsigned nb = (unsigned)((p->N + 15) / 16), rb = (unsigned)((p->M + 15) / 16);
+    if (nb * rb <= (unsigned)cu_count()) {
+      if (p->b_kcontig) hipLaunchKernelGGL((gemm_skinny_f32_kernel<true, 1>), dim3(nb, rb), dim3(1024), 0, st, g);
+      else hipLaunchKernelGGL((gemm_skinny_f32_kernel<false, 1>), dim3(nb, rb), dim3(1024), 0, st, g);
+    } else if (p->b_kcontig) hipLaunchKernelGGL((gemm_skinny_f32_kernel<true, 4>), dim3(nb), dim3(1024), 0, st, g);
+    else hipLaunchKernelGGL((gemm_skinny_f32_kernel<false, 4>), dim3(nb), dim3(1024), 0, st, g);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hap_fail(HAP_EDEVICE, "skinny fp32 gemm launch: %s", hipGetErrorString(e));
     return HAP_OK;

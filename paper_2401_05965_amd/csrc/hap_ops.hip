@@ -540,15 +540,19 @@ int hap_colsum_grouped(int groups, int64_t rows, int64_t cols, int io_dtype, con
   const dim3 grid((unsigned)((cols + skew + per_block - 1) / per_block), (unsigned)parts, (unsigned)groups);
   const int64_t rpb = kColsumRowsPerBlock;
   const int* gl = group_len;
+  // Few rows: one partial row is the result; stage 1 writes it where it belongs and the second launch (2 us and the gap before it)
+  // is saved.
+  const bool direct = parts == 1 && (groups == 1 || ldo == cols);
+  float* const part = direct ? out : static_cast<float*>(ws);
   if (io_dtype == HAP_BF16) {
-    if (vec) hipLaunchKernelGGL((colsum_partial_kernel<__bf16, 8>), grid, dim3(256), 0, s, rows, cols, (const __bf16*)base, lda, skew, rpb, (float*)ws, group_stride, gl);
-    else hipLaunchKernelGGL((colsum_partial_kernel<__bf16, 1>), grid, dim3(256), 0, s, rows, cols, (const __bf16*)a, lda, 0, rpb, (float*)ws, group_stride, gl);
+    if (vec) hipLaunchKernelGGL((colsum_partial_kernel<__bf16, 8>), grid, dim3(256), 0, s, rows, cols, (const __bf16*)base, lda, skew, rpb, part, group_stride, gl);
+    else hipLaunchKernelGGL((colsum_partial_kernel<__bf16, 1>), grid, dim3(256), 0, s, rows, cols, (const __bf16*)a, lda, 0, rpb, part, group_stride, gl);
   } else {
-    if (vec) hipLaunchKernelGGL((colsum_partial_kernel<float, 4>), grid, dim3(256), 0, s, rows, cols, (const float*)base, lda, skew, rpb, (float*)ws, group_stride, gl);
-    else hipLaunchKernelGGL((colsum_partial_kernel<float, 1>), grid, dim3(256), 0, s, rows, cols, (const float*)a, lda, 0, rpb, (float*)ws, group_stride, gl);
+    if (vec) hipLaunchKernelGGL((colsum_partial_kernel<float, 4>), grid, dim3(256), 0, s, rows, cols, (const float*)base, lda, skew, rpb, part, group_stride, gl);
+    else hipLaunchKernelGGL((colsum_partial_kernel<float, 1>), grid, dim3(256), 0, s, rows, cols, (const float*)a, lda, 0, rpb, part, group_stride, gl);
   }
   int rc = check_launch("colsum_partial");
-  if (rc) return rc;
+  if (rc || direct) return rc;
   hipLaunchKernelGGL(colsum_final_kernel, fgrid, dim3(256), 0, s, cols, (int)parts, (const float*)ws, out, ldo);
   return check_launch("colsum_final");
 }

@@ -197,6 +197,20 @@ def test_colsum_unaligned_base(hap, dtype):
         check("colsum skew", host(s), ah[:rows, off:off + cols].sum(0), dtype)
 
 
+@pytest.mark.parametrize("rows", [1, 127, 128, 129])
+@pytest.mark.parametrize("off", [0, 3])
+def test_colsum_of_few_rows_is_one_launch(hap, rows, off):
+    """Up to 128 rows the first stage writes the sums themselves: both sides of that line, aligned and skewed, nothing past the end."""
+    ld, cols = 1024, 700
+    ah, ad = gen(6, T.DY, (rows, ld), 1.0, "bf16")
+    s = empty((cols + 8,), "f32", 768.0)
+    ws = empty((max(hap.hap_colsum_workspace(rows, cols), 16),), "u8")
+    hap.hap_colsum(rows, cols, 1, ad.data_ptr() + off * 2, ld, s, ws)
+    got = host(s)
+    check("colsum", got[:cols], ah[:, off:off + cols].sum(0), "bf16")
+    assert (got[cols:] == 768).all()
+
+
 def test_row_ops_degenerate_sizes(hap):
     """Empty and one-element extents: every helper returns HAP_OK and leaves what it does not own untouched."""
     for dtype in ("bf16", "f32"):
