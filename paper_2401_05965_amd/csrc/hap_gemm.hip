@@ -34,7 +34,7 @@ namespace hap_gemm_detail {
  * fp32 products with at most 64 output rows (a layer whose batch shard is a few dozen samples: the single fully-connected layer
  * of the smallest workload, 38 / 26 rows of 64).  Such a product has far too few output tiles for the chip, and splitting its
  * contraction over workgroups costs a second, dependent launch for the reduction - on this machine about as long as the product
- * itself.  Here the split happens INSIDE a workgroup: one workgroup owns all (<= 64) rows of 16 output columns, its 16 waves each
+ * itself.  Here the split happens INSIDE a workgroup: one workgroup owns one 16-row block or all (<= 64) rows of 16 output columns, its 16 waves each
  * contract 1/16 of K with v_mfma_f32_16x16x4_f32, and their partial tiles are summed through LDS in a fixed order (deterministic).
  *   A (K-contiguous): lane (row r = lane % 16, k-quad q = lane / 16) fetches the 4 consecutive k values 16c + 4q .. + 3 of a
  *   16-wide chunk c as one 16-byte load and feeds element s to step s; B's lane (k-quad q, column) supplies the same k, so the
@@ -661,6 +661,7 @@ int hap_gemm_run(const hap_gemm_problem* p, void* stream) {
     const int skew_c = (int)(((uintptr_t)p->c % 16) / ces);       // columns of C's 16-byte chunk that precede logical column 0
     a.cdelta = a.vec_store ? ((skew_c - pl.skewN) % cepc + cepc) % cepc : 0;
   }
+  a.streamed = p->c_dtype == HAP_BF16;      // (fp32 outputs: no difference beyond the noise at 4096 x 16384 over 2560 rows)
   a.ntiles = 0;
   a.kpair = 0;
   a.ksplit = 1;
