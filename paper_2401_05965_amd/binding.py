@@ -132,6 +132,7 @@ lib.hap_strerror.argtypes = [C.c_int]
 lib.hap_last_error.restype = C.c_char_p
 lib.hap_version.restype = C.c_char_p
 lib.hap_debug_set_gemm_view_limit.restype = C.c_int64
+lib.hap_debug_kpair_products.restype = C.c_int64
 lib.hap_allgather_capacity.restype = C.c_int64
 for _n in ("hap_linear_fwd_workspace", "hap_linear_bwd_workspace", "hap_sfb_workspace", "hap_attn_bwd_workspace",
            "hap_layernorm_bwd_workspace", "hap_colsum_workspace", "hap_moe_linear_fwd_workspace", "hap_moe_linear_bwd_workspace"):
@@ -504,6 +505,11 @@ def hap_debug_set_gemm_view_limit(nbytes: int) -> int:
     """Testing aid: operand-view size from which the GEMM engine cuts a product into pieces (0 restores the default).
     Returns the number of products run in pieces so far."""
     return int(lib.hap_debug_set_gemm_view_limit(C.c_int64(int(nbytes))))
+
+
+def hap_debug_kpair_products() -> int:
+    """Testing aid: how many products the GEMM engine has handed to gemm_kpair_kernel so far."""
+    return int(lib.hap_debug_kpair_products())
 
 
 def hap_device_info():

@@ -55,9 +55,6 @@ struct hap_gemm_problem {
 /* Validates nothing beyond what the kernels need (callers validate user input); returns hap_status. */
 int hap_gemm_run(const hap_gemm_problem* p, void* stream);
 
-/* Name of the kernel variant the launcher would choose, for reports. */
-const char* hap_gemm_variant(const hap_gemm_problem* p);
-
 /* Scratch that lets every problem split K as far as the engine would like to (an upper bound). */
 #define HAP_GEMM_WS_BYTES ((size_t)64 << 20)
 

@@ -191,14 +191,13 @@ struct Plan {
   int skewM, skewN, skewK;
   int bm, bn;       // tile
   int bk;           // K step of the kernel that will run (the K-tile counts handed to it are in this unit)
-  const char* name;
   int dma;          // 1: bf16, direct-to-LDS kernel; 0: fp32, register-staged kernel
   bool pingpong;    // 256 x 256 tiles run by gemm_pp_kernel
 };
 
 /* Decides whether the aligned-chunk kernel can address the operands and with which skews. */
 Plan make_plan(const hap_gemm_problem* p) {
-  Plan pl = {false, 0, 0, 0, 0, 0, 64, "generic", 0, false};
+  Plan pl = {false, 0, 0, 0, 0, 0, 64, 0, false};
   if (p->force_generic) return pl;
   const int es = esize(p->in_dtype);
   if ((p->lda * es) % 16 || (p->ldb * es) % 16) return pl;
@@ -250,7 +249,7 @@ Plan make_plan(const hap_gemm_problem* p) {
     if (ea * es >= (double)kViewLimitBytes || eb * es >= (double)kViewLimitBytes) return pl;
   }
   pl.tiled = true;
-  if (p->in_dtype == HAP_F32) { pl.bm = pl.bn = 64; pl.name = "f32_64x64x16"; }
+  if (p->in_dtype == HAP_F32) pl.bm = pl.bn = 64;
   else {
     bool big = p->tile ? p->tile == 256 : (p->M + pl.skewM > 128 && p->N + pl.skewN > 128);
     if (big && !p->tile && (p->groups > 1 || p->group_len)) {
@@ -276,7 +275,6 @@ Plan make_plan(const hap_gemm_problem* p) {
     const bool short_k = nk64 < 20 && !(!p->a_kcontig && p->b_kcontig);
     pl.pingpong = big && !(p->a_kcontig && p->b_kcontig) && !short_k;
     pl.bk = pl.pingpong ? kPingPongBK : 64;
-    pl.name = pl.pingpong ? "bf16_256x256x32_pingpong4" : (big ? "bf16_256x256x64_dma2" : "bf16_128x128x64_dma2");
   }
   return pl;
 }
@@ -303,15 +301,13 @@ int dispatch_tile(const hap_gemm_problem* p, const Plan& pl, const GemmArgs& a, 
   if constexpr (sizeof(T) == 4) {
     return dispatch_layout<T, TC, 64, 64, 64, 2, 2>(p, a, groups, st);
   } else {
-    return pl.pingpong ? run_pp(p, a, pl.bm, pl.bn, groups, st) : run_dma(p, a, pl.bm, pl.bn, groups, st);
+    return pl.pingpong ? run_pp(p, a, groups, st) : run_dma(p, a, pl.bm, groups, st);
   }
 }
 
 }  // namespace hap_gemm_detail
 
 using namespace hap_gemm_detail;
-
-const char* hap_gemm_variant(const hap_gemm_problem* p) { return make_plan(p).name; }
 
 namespace {
 
@@ -385,6 +381,10 @@ hap_gemm_problem sub_problem(const hap_gemm_problem* p, int64_t m_lo, int64_t m_
 
 static int64_t g_view_limit = kViewLimitBytes;
 static int64_t g_cut_products = 0;      // products run in pieces so far (testing aid, not synchronised)
+
+static int64_t g_kpair_products = 0;    // products handed to gemm_kpair_kernel so far (testing aid)
+
+extern "C" int64_t hap_debug_kpair_products(void) { return __atomic_load_n(&g_kpair_products, __ATOMIC_RELAXED); }
 
 /* Test hook (declared in hap_internal.h, not part of the public interface): lowers the reach at which operand views are
  * cut so the cutting can be exercised on small inputs; returns how many products have run in pieces so far. */
@@ -691,6 +691,7 @@ int hap_gemm_run(const hap_gemm_problem* p, void* stream) {
       const size_t ws_splits = p->ws ? p->ws_bytes / per_split : 0;
       double us;
       a.kpair = 1;
+      __atomic_fetch_add(&g_kpair_products, 1, __ATOMIC_RELAXED);
       a.ksplit = kpair_splits(p, out_tiles, a.ntiles, ws_splits, &us);
       a.partial = a.ksplit > 1 ? static_cast<float*>(p->ws) : nullptr;
     }

@@ -22,13 +22,13 @@ int launch_kpair(const GemmArgs& a, int groups, hipStream_t st) {
 }
 
 template <typename TC>
-int tiles(const hap_gemm_problem* p, const GemmArgs& a, int bm, int groups, hipStream_t st) {
+int tiles(const hap_gemm_problem* p, const GemmArgs& a, int tile, int groups, hipStream_t st) {
   if (a.kpair) {
     if (p->a_kcontig && p->b_kcontig) return launch_kpair<TC, true, true>(a, groups, st);
     if (p->a_kcontig) return launch_kpair<TC, true, false>(a, groups, st);
     return launch_kpair<TC, false, false>(a, groups, st);     // (an M-contiguous A with a K-contiguous B is never paired)
   }
-  if (bm == 128) {
+  if (tile == 128) {
     if (p->a_kcontig && p->b_kcontig) return launch<TC, true, true, 128, 128, 2, 2>(a, groups, st);
     if (p->a_kcontig) return launch<TC, true, false, 128, 128, 2, 2>(a, groups, st);
     if (!p->b_kcontig) return launch<TC, false, false, 128, 128, 2, 2>(a, groups, st);
@@ -44,9 +44,8 @@ int tiles(const hap_gemm_problem* p, const GemmArgs& a, int bm, int groups, hipS
 
 }  // namespace
 
-int run_dma(const hap_gemm_problem* p, const GemmArgs& a, int bm, int bn, int groups, hipStream_t st) {
-  (void)bn;
-  return p->c_dtype == HAP_BF16 ? tiles<__bf16>(p, a, bm, groups, st) : tiles<float>(p, a, bm, groups, st);
+int run_dma(const hap_gemm_problem* p, const GemmArgs& a, int tile, int groups, hipStream_t st) {
+  return p->c_dtype == HAP_BF16 ? tiles<__bf16>(p, a, tile, groups, st) : tiles<float>(p, a, tile, groups, st);
 }
 
 }  // namespace hap_gemm_detail

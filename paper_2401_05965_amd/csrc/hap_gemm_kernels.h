@@ -1595,9 +1595,10 @@ int launch_lds_kernel(void (*kernel)(const GemmArgs), bool (&configured)[64], si
   return a.ksplit > 1 ? launch_splitk_reduce<__bf16, TC, BM, BN>(a, groups, st) : HAP_OK;
 }
 
-/* Defined in the translation unit that instantiates the kernels in question; bm x bn is one of the tiles the planner chooses from. */
-int run_pp(const hap_gemm_problem* p, const GemmArgs& a, int bm, int bn, int groups, hipStream_t st);    // hap_gemm_pp.hip: gemm_pp_kernel
-int run_dma(const hap_gemm_problem* p, const GemmArgs& a, int bm, int bn, int groups, hipStream_t st);   // hap_gemm_dma.hip: gemm_dma_kernel
+/* Defined in the translation unit that instantiates the kernels in question. */
+int run_pp(const hap_gemm_problem* p, const GemmArgs& a, int groups, hipStream_t st);             // hap_gemm_pp.hip: gemm_pp_kernel, 256 x 256
+int run_dma(const hap_gemm_problem* p, const GemmArgs& a, int tile, int groups, hipStream_t st);  // hap_gemm_dma.hip: gemm_dma_kernel of 128- or
+                                                                                                  // 256-tiles, gemm_kpair_kernel
 
 }  // namespace hap_gemm_detail
 

@@ -26,8 +26,7 @@ int layouts(const hap_gemm_problem* p, const GemmArgs& a, int groups, hipStream_
 
 }  // namespace
 
-int run_pp(const hap_gemm_problem* p, const GemmArgs& a, int bm, int bn, int groups, hipStream_t st) {
-  (void)bm; (void)bn;
+int run_pp(const hap_gemm_problem* p, const GemmArgs& a, int groups, hipStream_t st) {
   if (p->c_dtype == HAP_BF16) return layouts<__bf16, 256, 256, 2, 4>(p, a, groups, st);
   return layouts<float, 256, 256, 2, 4>(p, a, groups, st);
 }

@@ -36,6 +36,10 @@ int hap_gelu_bwd_grouped(int groups, int64_t rows, int64_t cols, int io_dtype, c
  * the engine has run in pieces so far in this process.  Process-wide, not thread-safe. */
 int64_t hap_debug_set_gemm_view_limit(int64_t bytes);
 
+/* Test hook, not part of the public interface: how many products the engine has handed to gemm_kpair_kernel so far in this process,
+ * so that a test can state which products it reaches it with. */
+int64_t hap_debug_kpair_products(void);
+
 #ifdef __cplusplus
 }
 #endif
