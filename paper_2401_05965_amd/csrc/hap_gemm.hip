@@ -324,20 +324,38 @@ double small_tiles_time(long long n) {
 
 inline long long cdiv(long long a, long long b) { return (a + b - 1) / b; }
 
+/* Into how many workgroups the launcher splits the contraction of `tiles` output tiles (1: not at all): over the idle slots, with at
+ * least min_steps K steps for each, at most sixteen, and as far as the caller's workspace holds the partial tiles. */
+long long workgroup_splits(const hap_gemm_problem* p, long long tiles, long long slots, long long steps, int min_steps, size_t tile_bytes) {
+  long long g = slots / tiles;
+  if (g > steps / min_steps) g = steps / min_steps;
+  if (g > 16) g = 16;
+  const long long held = p->ws ? (long long)(p->ws_bytes / ((size_t)tiles * tile_bytes)) : 0;
+  if (g > held) g = held;
+  return g < 2 ? 1 : g;
+}
+
+constexpr size_t kSmallTileBytes = 128 * 128 * sizeof(float);     // a partial tile
+
 /* Whether 128-tiles of this product run in gemm_kpair_kernel: at most one tile per compute unit, and two K tiles for each of its two
- * wave groups.  Against the 4-wave kernel, which fills the chip by splitting K over workgroups (microseconds, forward, MI355X):
- * 3940 x 1024 outputs over K = 1024 / 4096 29 / 47 -> 15 / 37, 1024 x 1024 over 1024 24 -> 12, 4096 x 1000 over 8192 77 -> 67.
- * The exceptions: tile counts that leave compute units idle here but not there (93 tiles: two splits 73 %, five half-size
- * workgroups 91 %) where the contraction is long enough for that to outweigh the reduction (3873 x 286 over 3648: 29 against 25.5;
- * 144 tiles over K = 768: 12 against 26), and short bwd-data products of very few tiles, where the launch is all there is (144 x 816
- * over 1088: 13.0 against 12.3).
+ * wave groups.  The alternative is the 4-wave kernel, which fills the chip by splitting K over workgroups where it has a workspace.
+ * The limits lie where the two cross (microseconds, 4-wave -> K-pair, three operand sets in turn, MI355X):
+ *   K tiles, 36 output tiles:  3: forward 8.6 -> 8.8, bwd-data 8.4 -> 9.0    4: 9.4 -> 8.8, 9.2 -> 9.1    5: 9.9 -> 9.4, 9.7 -> 9.6
+ *   output tiles, K = 1024:    256: 29.9 -> 15.6    272: 20.8 -> 25.9    320: 20.8 -> 25.4
+ *   without a workspace:       16 tiles over K = 512 / 1024 / 4096  11.1 -> 10.1 / 15.4 -> 12.3 / 46 -> 27
+ * Two ranges stay with the 4-wave kernel where it can split K:
+ *   - bwd-data of at most an eighth of the chip over 17 to 19 K tiles (24 tiles: 13.6 -> 14.4; four short splits there, three here, whose
+ *     sum takes longer).  On its sides: 16 and 20 K tiles 13.5 -> 12.9 and 15.4 -> 14.4 (24 tiles), 17 K tiles 15.5 -> 14.3 (36 tiles).
+ *   - past 128 K tiles, where the operands stream from HBM, tile counts that leave compute units idle here but not there (160 tiles:
+ *     62 %, as three splits 94 %; K = 4096 / 6144 / 8320 35.5 -> 30.5 / 44.6 -> 41.8 / 55.6 -> 58.3).
  * (An M-contiguous A with a K-contiguous B is a form no product of the path has; the kernel is not built for it.) */
 bool kpair_applies(const hap_gemm_problem* p, long long tiles, long long nk) {
   const long long cus = cu_count();
   if (p->in_dtype != HAP_BF16 || (!p->a_kcontig && p->b_kcontig) || tiles > cus || nk < 4) return false;
-  if (p->a_kcontig && p->b_kcontig && tiles * 8 <= cus && nk <= 20) return false;
+  if (workgroup_splits(p, tiles, 2 * cus, nk, 4, kSmallTileBytes) == 1) return true;
+  if (p->a_kcontig && p->b_kcontig && tiles * 8 <= cus && nk > 16 && nk < 20) return false;
   const long long here = cus / tiles * tiles * 2, there = 2 * cus / tiles * tiles;      // of 2 * cus wave groups
-  return nk <= 40 || !p->ws || here * 20 >= there * 17;
+  return nk <= 128 || here * 20 >= there * 17;
 }
 
 /* Into how many workgroups that kernel splits K (1: no partial tiles, no reduction launch) and the estimated time in microseconds.
@@ -346,8 +364,9 @@ bool kpair_applies(const hap_gemm_problem* p, long long tiles, long long nk) {
  * four); 6 for prologue, exchange and epilogue, 4 / 1.5 more for GeLU / its backward in an epilogue that runs on few compute units
  * only; a reduction launch 1.2 and 0.03 per partial tile written and read back.  128 tiles over K = 1024: whole 13, split in
  * two 23; 64 tiles over K = 4096: whole 28, split in four 23. */
-int kpair_splits(const hap_gemm_problem* p, long long tiles, long long nk, size_t ws_splits, double* us) {
+int kpair_splits(const hap_gemm_problem* p, long long tiles, long long nk, double* us) {
   const long long cus = cu_count();
+  const size_t ws_splits = p->ws ? p->ws_bytes / ((size_t)tiles * kSmallTileBytes) : 0;
   int best = 1;
   *us = 0.0;
   for (int s = 1; s <= 16; ++s) {
@@ -466,29 +485,28 @@ static int run_auto_tiled(const hap_gemm_problem* p, const Plan& pl, void* strea
   const long long tm = cdiv(Mp, 256), tn = cdiv(Np, 256);
   const long long sm = cdiv(Mp, 128), sn = cdiv(Np, 128);
   // A remainder strip of r big tiles can also stay on big tiles with its K range split over the idle CUs
-  // (needs workspace); that costs about a third of a round for the partial-tile traffic plus 1/g rounds.
-  const bool can_split_k = p->ws && p->ws_bytes >= (size_t)8 << 20;
+  // (as far as the workspace allows); that costs about a third of a round for the partial-tile traffic plus 1/g rounds.
   long long nk = 0;                 // K tiles of the contraction
   for (int s = 0; s < p->nseg; ++s) nk += p->k[s] > 0 ? cdiv(pl.skewK + p->k[s], 64) : 0;
   // A part whose big tiles cannot fill the chip: 128-tiles (two per CU) or 256-tiles, either with the K range split over
   // the idle slots as the launcher will do it.  Measured on this chip (microseconds): a workgroup spends 2.0 per K tile
   // on a 256-tile and 1.05 on a 128-tile that shares its CU, plus 7 / 5 for prologue and epilogue; a split costs 3 for
   // the reduction launch and 0.025 / 0.00625 per partial tile written and read back.  Returned in rounds of big tiles.
-  auto few_tiles_us = [&](long long tiles, long long slots, double per_ktile, double fixed, double per_partial) {
-    long long g = can_split_k ? slots / tiles : 1;
-    if (g > nk / 4) g = nk / 4;
-    if (g > 16) g = 16;
-    if (g < 1) g = 1;
+  auto few_tiles_us = [&](long long tiles, long long slots, size_t tile_bytes, double per_ktile, double fixed, double per_partial) {
+    const long long g = workgroup_splits(p, tiles, slots, nk, 4, tile_bytes);
     const double rounds = (double)cdiv(tiles * g, slots);
     return rounds * ((double)nk / (double)g * per_ktile + fixed) + (g > 1 ? 3.0 + (double)(tiles * g) * per_partial : 0.0);
   };
   auto strip_time = [&](long long big_tiles, long long small_tiles, int* tile) {
     if (big_tiles < kCUs && nk > 0) {
       const double round_us = (double)nk * 2.0 + 7.0;
-      const double tb = few_tiles_us(big_tiles, kCUs, 2.0, 7.0, 0.025);
-      double ts = few_tiles_us(small_tiles, 2 * kCUs, 1.05, 5.0, 0.00625);
-      if (kpair_applies(p, small_tiles, nk))
-        kpair_splits(p, small_tiles, nk, can_split_k ? p->ws_bytes / ((size_t)small_tiles * 128 * 128 * sizeof(float)) : 0, &ts);
+      const double tb = few_tiles_us(big_tiles, kCUs, 4 * kSmallTileBytes, 2.0, 7.0, 0.025);
+      double ts = few_tiles_us(small_tiles, 2 * kCUs, kSmallTileBytes, 1.05, 5.0, 0.00625);
+      if (kpair_applies(p, small_tiles, nk)) {     // (where it applies, it is at least as fast as the 4-wave kernel)
+        double pair;
+        kpair_splits(p, small_tiles, nk, &pair);
+        if (pair < ts || nk > 128) ts = pair;
+      }
       *tile = tb <= ts ? 256 : 128;
       return (tb <= ts ? tb : ts) / round_us;
     }
@@ -678,23 +696,14 @@ int hap_gemm_run(const hap_gemm_problem* p, void* stream) {
     const int kCUs = cu_count();
     const long long slots = pl.bm == 256 ? kCUs : (pl.bm == 128 ? 2 * kCUs : 4 * kCUs);
     const int min_tiles = pl.bm == 64 ? 2 : 4 * (64 / pl.bk);      // in K steps of the chosen kernel
-    long long g = slots / out_tiles;
-    if (g > a.ntiles / min_tiles) g = a.ntiles / min_tiles;
-    if (g > 16) g = 16;
-    const size_t per_split = (size_t)out_tiles * pl.bm * pl.bn * sizeof(float);
-    if (g >= 2 && p->ws && per_split * 2 <= p->ws_bytes) {
-      if (per_split * (size_t)g > p->ws_bytes) g = (long long)(p->ws_bytes / per_split);
-      a.ksplit = (int)g;
-      a.partial = static_cast<float*>(p->ws);
-    }
+    a.ksplit = (int)workgroup_splits(p, out_tiles, slots, a.ntiles, min_tiles, (size_t)pl.bm * pl.bn * sizeof(float));
     if (pl.dma && pl.bm == 128 && kpair_applies(p, out_tiles, a.ntiles)) {
-      const size_t ws_splits = p->ws ? p->ws_bytes / per_split : 0;
       double us;
       a.kpair = 1;
       __atomic_fetch_add(&g_kpair_products, 1, __ATOMIC_RELAXED);
-      a.ksplit = kpair_splits(p, out_tiles, a.ntiles, ws_splits, &us);
-      a.partial = a.ksplit > 1 ? static_cast<float*>(p->ws) : nullptr;
+      a.ksplit = kpair_splits(p, out_tiles, a.ntiles, &us);
     }
+    if (a.ksplit > 1) a.partial = static_cast<float*>(p->ws);
   }
   if (p->in_dtype == HAP_BF16 && p->c_dtype == HAP_BF16) return dispatch_tile<__bf16, __bf16>(p, pl, a, groups, st);
   if (p->in_dtype == HAP_BF16) return dispatch_tile<__bf16, float>(p, pl, a, groups, st);

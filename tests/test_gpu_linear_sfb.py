@@ -188,6 +188,38 @@ def test_linear_few_tiles_share_their_contraction_between_wave_groups(hap, k):
     run_linear_case(hap, "bf16", 130, 136, 1000, 1, [0, k, 1000], act=True, bias=True, full=True)
 
 
+@pytest.mark.parametrize("scratch", [0, 1 << 16, None])
+def test_linear_route_to_the_paired_wave_groups(hap, scratch):
+    """Products of at most one 128-tile per compute unit and at least four K tiles take the kernel with two wave groups, whatever the
+    workspace holds (nothing, too little for a single split, everything): few tiles over a short contraction, poorly filled tile counts
+    over a long one.  Fewer K tiles or more output tiles do not."""
+    torch = torch_mod()
+    cus, _ = hap.hap_device_info()
+    assert cus == 256
+    for tokens, in_f, out_f, want in [(250, 880, 500, [1, 1, 1]),         # 2 x 4 output tiles over 14 K tiles, 2 x 7 over 8, 7 x 4 over 4
+                                      (1270, 4090, 1140, [1, 0, 0])]:      # 10 x 9 over 64; 10 x 32 and 32 x 9 tiles are too many
+        Xh, Xd = gen(3, T.X, (tokens, in_f), 1.0, "bf16"); Wh, Wd = gen(3, T.W, (in_f, out_f), 0.05, "bf16"); Gh, Gd = gen(3, T.DY, (tokens, out_f), 1.0, "bf16")
+        ld = lambda n: (n + 7) // 8 * 8
+        wide = lambda t: torch.nn.functional.pad(t, (0, ld(t.shape[1]) - t.shape[1]))
+        Xd, Wd, Gd = wide(Xd), wide(Wd), wide(Gd)
+        desc = hap.LinearDesc(tokens, in_f, out_f, hap.REPLICATED, [0, 1], hap.BF16, ldx=ld(in_f), ldw=ld(out_f), ldy=ld(out_f), m=1)
+        ws = empty((scratch if scratch else hap.hap_linear_bwd_workspace(desc, 0),), "u8") if scratch != 0 else None
+        Y, dX, dW = empty(Gd.shape, "bf16", 0), empty(Xd.shape, "bf16", 0), empty(Wd.shape, "bf16", 0)
+        Yo, _ = olin.linear_fwd(Xh, Wh); dXo, dWo, _ = olin.linear_bwd(Xh, Wh, None, Gh)
+        n = [hap.hap_debug_kpair_products()]
+        hap.hap_sharded_linear_fwd(desc, 0, Xd, Wd, None, Y, None, ws); n.append(hap.hap_debug_kpair_products())
+        hap.hap_sharded_linear_bwd(desc, 0, Xd, Wd, None, Gd, dX, None, hap.BF16, None, ws); n.append(hap.hap_debug_kpair_products())
+        hap.hap_sharded_linear_bwd(desc, 0, Xd, Wd, None, Gd, None, dW, hap.BF16, None, ws); n.append(hap.hap_debug_kpair_products())
+        check("route Y", host(Y)[:, :out_f], Yo, "bf16"); check("route dX", host(dX)[:, :in_f], dXo, "bf16"); check("route dW", host(dW)[:, :out_f], dWo, "bf16")
+        assert [b - a for a, b in zip(n, n[1:])] == want, (tokens, in_f, out_f, n)
+    for tokens, in_f, out_f in [(250, 190, 500), (17 * 128, 256, 16 * 128)]:  # 3 K tiles; 17 x 16 output tiles
+        Xd, Wd, Y = empty((tokens, 256), "bf16", 0), empty((in_f, 2048), "bf16", 0), empty((tokens, 2048), "bf16", 1)
+        desc = hap.LinearDesc(tokens, in_f, out_f, hap.REPLICATED, [0, 1], hap.BF16, ldx=256, ldw=2048, ldy=2048, m=1)
+        before = hap.hap_debug_kpair_products()
+        hap.hap_sharded_linear_fwd(desc, 0, Xd, Wd, None, Y, None)
+        assert hap.hap_debug_kpair_products() == before and not host(Y)[:, :out_f].any()
+
+
 def test_linear_unaligned_leading_dimensions_take_the_scalar_kernel(hap):
     # compact slices whose leading dimension is not a multiple of 16 bytes
     run_linear_case(hap, "bf16", 70, 50, 90, 1, [0, 37, 90], act=True, bias=True, full=False, pad=3)
