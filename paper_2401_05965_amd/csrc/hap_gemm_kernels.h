@@ -654,7 +654,7 @@ __device__ __forceinline__ void epilogue_transposed_impl(const GemmArgs& args, f
   // DACT: all pre-activation chunks of the wave's tile are requested now, in one burst, so that the stores below wait for one
   // memory round trip instead of one per chunk
   // (an fp32 tile has twice the chunks: there the requests go out one row block at a time, ahead of that block's patch traffic)
-  constexpr int BURST = !DACT ? 0 : ES == 2 ? TM : 1;
+  constexpr int BURST = ES == 2 ? TM : 1;
   vec_t pvs[DACT ? BURST : 1][DACT ? ITS : 1];
   auto request_preact = [&](int i, int slot) {
 #pragma unroll
@@ -665,7 +665,7 @@ __device__ __forceinline__ void epilogue_transposed_impl(const GemmArgs& args, f
         pvs[slot][it] = *reinterpret_cast<const vec_t*>(static_cast<const TC*>(args.dact_preact) + (long long)m * args.ldd + n);
     }
   };
-  if constexpr (BURST == TM) {
+  if constexpr (DACT && BURST == TM) {
 #pragma unroll
     for (int i = 0; i < TM; ++i) request_preact(i, i);
   }
@@ -674,7 +674,7 @@ __device__ __forceinline__ void epilogue_transposed_impl(const GemmArgs& args, f
 #pragma unroll
     for (int pass = 0; pass < 2; ++pass) {
       if (pass == 0 && (DACT || ACTP || !P)) continue;
-      if constexpr (BURST == 1) request_preact(i, 0);
+      if constexpr (DACT && BURST < TM) request_preact(i, 0);
       TC* dst_base = pass == 0 ? P : C;
       const long long ldd = pass == 0 ? args.ldp : args.ldc;
       // registers -> LDS patch [32 rows][COLS]
