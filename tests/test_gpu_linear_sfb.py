@@ -180,12 +180,51 @@ def test_linear_deep_ragged_contractions(hap, full):
 
 @pytest.mark.parametrize("k", [193, 256, 257, 385, 449, 768])
 def test_linear_few_tiles_share_their_contraction_between_wave_groups(hap, k):
-    """Outputs of few 128-tiles: the two wave groups of a workgroup contract the same and different numbers of K tiles (4 to 13 of
-    64, odd and even, also an empty half), ranges that start and end inside a tile, in all three products; the forward without a
-    workspace (contraction whole), the backward with one (also split over workgroups)."""
-    run_linear_case(hap, "bf16", 130, 1000, 200, 2, [0, k, 1000], act=False, bias=False, full=True)
-    run_linear_case(hap, "bf16", 1000, 136, 264, 0, [0, k, 1000], act=True, bias=True, full=True, dw_dtype="f32")
-    run_linear_case(hap, "bf16", 130, 136, 1000, 1, [0, k, 1000], act=True, bias=True, full=True)
+    """Outputs of few 128-tiles over ranges that start and end inside a K tile: the two wave groups of a workgroup contract the same and
+    different numbers of K tiles (4 to 13 of 64, odd and even), in all three products; the forward without a workspace (contraction
+    whole), the backward with one (also split over workgroups).  The counts say how many of a call's products reach the kernel.  (Every
+    group has work here; a group without any needs a contraction that is shortened on the device, as in test_moe_few_experts_split_k.)"""
+    def reached(want, *args, **kw):
+        before = hap.hap_debug_kpair_products()
+        run_linear_case(hap, "bf16", *args, full=True, **kw)
+        assert hap.hap_debug_kpair_products() - before == want, (args, want)
+    # per shard: forward over k or 1000 - k columns of X, dX over 200; dW contracts 130 rows, too few
+    reached(4, 130, 1000, 200, 2, [0, k, 1000], act=False, bias=False)
+    # dX over 264, dW over k or 1000 - k rows; the forward contracts 136
+    reached(4, 1000, 136, 264, 0, [0, k, 1000], act=True, bias=True, dw_dtype="f32")
+    # dX over k or 1000 - k columns of dY and W, straight from the whole tensors and from the activation backward's copy
+    reached(2, 130, 136, 1000, 1, [0, k, 1000], act=False, bias=True)
+    reached(2, 130, 136, 1000, 1, [0, k, 1000], act=True, bias=True)
+
+
+@pytest.mark.parametrize("scratch", [True, False])
+@pytest.mark.parametrize("cut", [128, 333, 517])
+@pytest.mark.parametrize("tokens,out_f", [(130, 264), (1000, 1104), (140, 1600)])
+def test_linear_bwd_data_of_paired_wave_groups_into_column_ranges(hap, tokens, out_f, cut, scratch):
+    """bwd-data of a reduction shard of whole tensors: its columns of dX start on and off the output's 16-byte grid (`cut`), its rows of W
+    with them; contractions of 5, 18 and 25 K tiles, up to 8 x 5 output tiles, plain and with the producer's gelu' in the epilogue."""
+    from oracle import pointwise as opw
+    in_f = 1000
+    offsets = [0, cut, in_f]
+    Xh, Xd = gen(13, T.X, (tokens, in_f), 1.0, "bf16"); Wh, Wd = gen(13, T.W, (in_f, out_f), 0.05, "bf16")
+    dYh, dYd = gen(13, T.DY, (tokens, out_f), 1.0, "bf16"); Ph, Pd = gen(13, T.MISC, (tokens, in_f), 1.5, "bf16")
+    desc = hap.LinearDesc(tokens, in_f, out_f, olin.REDUCTION, offsets, hap.BF16)
+    tiles_m = -(-tokens // 128)
+    for j in range(2):
+        lo, hi = offsets[j], offsets[j + 1]
+        want, _, _ = olin.sharded_linear_bwd(olin.REDUCTION, offsets, j, Xh, Wh, None, dYh, False)
+        ws = empty((hap.hap_linear_bwd_workspace(desc, j),), "u8") if scratch else None
+        for act in (False, True):
+            dX = empty((tokens, in_f), "bf16", float("nan"))
+            before = hap.hap_debug_kpair_products()
+            hap.hap_sharded_linear_bwd_dact(desc, j, Xd, Wd, None, dYd, dX, None, hap.BF16, None, Pd if act else None, hap.ACT_GELU_ERF if act else hap.ACT_NONE, ws)
+            taken = hap.hap_debug_kpair_products() - before
+            got = host(dX)
+            check(f"dX act{int(act)} shard {j}", got[:, lo:hi], want * opw.gelu_grad(Ph[:, lo:hi]) if act else want, "bf16")
+            assert np.isnan(got[:, :lo]).all() and np.isnan(got[:, hi:]).all(), "columns outside the shard were written"
+            # 18 K tiles of at most 32 output tiles stay with the 4-wave kernel where a workspace lets that split K
+            few = tiles_m * -(-(hi - lo + 7) // 128) <= 32
+            assert taken == (0 if scratch and few and out_f == 1104 else 1), (tokens, out_f, lo, hi, taken)
 
 
 @pytest.mark.parametrize("scratch", [0, 1 << 16, None])
