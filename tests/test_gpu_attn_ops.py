@@ -197,18 +197,51 @@ def test_colsum_unaligned_base(hap, dtype):
         check("colsum skew", host(s), ah[:rows, off:off + cols].sum(0), dtype)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("rows", [1, 127, 128, 129])
 @pytest.mark.parametrize("off", [0, 3])
-def test_colsum_of_few_rows_is_one_launch(hap, rows, off):
-    """Up to 128 rows the first stage writes the sums themselves: both sides of that line, aligned and skewed, nothing past the end."""
+def test_colsum_of_few_rows_is_one_launch(hap, dtype, rows, off):
+    """Up to 128 rows the first stage writes the sums themselves and leaves the workspace alone, from 129 on its partial rows go there:
+    both sides of that line, aligned and skewed, nothing past the end."""
     ld, cols = 1024, 700
-    ah, ad = gen(6, T.DY, (rows, ld), 1.0, "bf16")
+    ah, ad = gen(6, T.DY, (rows, ld), 1.0, dtype)
     s = empty((cols + 8,), "f32", 768.0)
-    ws = empty((max(hap.hap_colsum_workspace(rows, cols), 16),), "u8")
-    hap.hap_colsum(rows, cols, 1, ad.data_ptr() + off * 2, ld, s, ws)
+    ws = empty((max(hap.hap_colsum_workspace(rows, cols), 16),), "u8", 77)
+    hap.hap_colsum(rows, cols, {"bf16": 1, "f32": 0}[dtype], ad.data_ptr() + off * {"bf16": 2, "f32": 4}[dtype], ld, s, ws)
     got = host(s)
-    check("colsum", got[:cols], ah[:, off:off + cols].sum(0), "bf16")
+    check("colsum", got[:cols], ah[:, off:off + cols].sum(0), dtype)
     assert (got[cols:] == 768).all()
+    assert (host(ws) == 77).all() == (rows <= 128)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("rows", [1, 128, 129])
+@pytest.mark.parametrize("gap", [0, 4])
+def test_grouped_colsum_of_few_rows(hap, dtype, rows, gap):
+    """Groups with row counts of their own (none, some, all): one launch only where the outputs lie as the partial rows would, without a
+    gap between the groups; what lies in a gap stays as it was."""
+    import ctypes as C
+    groups, ld, cols = 3, 256, 200
+    lens = [0, (rows + 1) // 2, rows]
+    ah, ad = gen(7, T.DY, (groups * rows, ld), 1.0, dtype)
+    torch = torch_mod()
+    dev_lens = torch.tensor(lens, dtype=torch.int32, device="cuda")
+    ldo = cols + gap
+    s = empty((groups * ldo,), "f32", 768.0)
+    lib = hap.lib
+    lib.hap_colsum_grouped_workspace.restype = C.c_size_t
+    nws = lib.hap_colsum_grouped_workspace(C.c_int(groups), C.c_int64(rows), C.c_int64(cols))
+    ws = empty((nws,), "u8", 77)
+    p = lambda t: C.c_void_p(t.data_ptr())
+    rc = lib.hap_colsum_grouped(C.c_int(groups), C.c_int64(rows), C.c_int64(cols), C.c_int({"bf16": 1, "f32": 0}[dtype]), p(ad), C.c_int64(ld),
+                                C.c_int64(rows * ld), p(dev_lens), p(s), C.c_int64(ldo), p(ws), C.c_size_t(nws),
+                                C.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert rc == 0
+    got = host(s).reshape(groups, ldo)
+    for g, n in enumerate(lens):
+        check(f"group {g}", got[g, :cols], ah[g * rows:g * rows + n, :cols].sum(0), dtype)
+    assert (got[:, cols:] == 768).all()
+    assert (host(ws) == 77).all() == (rows <= 128 and gap == 0)
 
 
 def test_row_ops_degenerate_sizes(hap):
