@@ -41,8 +41,8 @@ struct hap_gemm_problem {
   void* ws; size_t ws_bytes;           /* optional device scratch for split-K partial tiles (NULL: never split K)   */
   int tile;                            /* 0: engine chooses (and may split the problem); 128 / 256: fixed output tile */
   /* Grouped launch: `groups` independent products of the same shape in one launch, group g's operands
-   * g strides further on (the experts of an MoE layer, Sec. 7.6).  Needs nseg == 1; neither strip
-   * splitting nor split-K apply.  group_len (a DEVICE array, one int per group, or NULL) holds the valid
+   * g strides further on (the experts of an MoE layer, Sec. 7.6).  Needs nseg == 1; the output is not
+   * cut into strips, K is split where there are too few tiles over all groups.  group_len (a DEVICE array, one int per group, or NULL) holds the valid
    * length of the ragged axis per group, clamped to [0, the problem's extent]: group_ragged = 1 bounds M
    * (rows of A and C beyond it are neither read nor written), 2 bounds the contraction k[0]. */
   int groups;                          /* 0 or 1: a single product                               */

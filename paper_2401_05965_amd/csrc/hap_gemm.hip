@@ -52,7 +52,7 @@ typedef float f32x4_t __attribute__((ext_vector_type(4)));
 /* RB: 16-row blocks of a workgroup (blockIdx.y counts them).  1 where that still leaves every workgroup a compute unit of its own: 38
  * rows of a 1024-wide layer are 64 workgroups of three row blocks or 192 of one, each with a third of the MFMAs and of the A
  * traffic (the weight is then read three times, out of L2); with all rows in one workgroup (4) the weight is read once, for outputs
- * wide enough to fill the chip by themselves. */
+ * wide enough to fill the chip by themselves.  That layer's forward, backward and factor rebuild: 38.2 us with 4, 31.9 with 1. */
 template <bool BKC, int RB>
 __global__ __launch_bounds__(1024) void gemm_skinny_f32_kernel(const SkinnyArgs g) {
   __shared__ float red[16][16 * RB][16];             // one partial [rows][columns] tile per wave: 16 KB per row block
@@ -344,10 +344,11 @@ constexpr size_t kSmallTileBytes = 128 * 128 * sizeof(float);     // a partial t
  *   output tiles, K = 1024:    256: 29.9 -> 15.6    272: 20.8 -> 25.9    320: 20.8 -> 25.4
  *   without a workspace:       16 tiles over K = 512 / 1024 / 4096  11.1 -> 10.1 / 15.4 -> 12.3 / 46 -> 27
  * Two ranges stay with the 4-wave kernel where it can split K:
- *   - bwd-data of at most an eighth of the chip over 17 to 19 K tiles (24 tiles: 13.6 -> 14.4; four short splits there, three here, whose
- *     sum takes longer).  On its sides: 16 and 20 K tiles 13.5 -> 12.9 and 15.4 -> 14.4 (24 tiles), 17 K tiles 15.5 -> 14.3 (36 tiles).
+ *   - bwd-data of at most an eighth of the chip over 17 to 19 K tiles (24 tiles: 13.6 -> 14.3; four short splits there, three here, whose
+ *     sum takes longer).  On its sides: 16 and 20 K tiles 13.5 -> 12.6 and 15.4 -> 13.8 (24 tiles), 17 K tiles 15.5 -> 14.3 (36 tiles).
  *   - past 128 K tiles, where the operands stream from HBM, tile counts that leave compute units idle here but not there (160 tiles:
- *     62 %, as three splits 94 %; K = 4096 / 6144 / 8320 35.5 -> 30.5 / 44.6 -> 41.8 / 55.6 -> 58.3).
+ *     62 %, as three splits 94 %; forward over K = 6144 / 7680 / 10240 44.6 -> 41.8 / 52.3 -> 50.3 / 70.7 -> 78.2; in between the two are
+ *     within 5 %, and the line lies where kpair_splits() raises the cost of a step, so that the planner weighs the kernel that will run).
  * (An M-contiguous A with a K-contiguous B is a form no product of the path has; the kernel is not built for it.) */
 bool kpair_applies(const hap_gemm_problem* p, long long tiles, long long nk) {
   const long long cus = cu_count();
@@ -363,7 +364,9 @@ bool kpair_applies(const hap_gemm_problem* p, long long tiles, long long nk) {
  * contractions, whose operands stream from HBM (256 tiles, K = 50432: 462 in all against 345 for 64 256-tiles with K split in
  * four); 6 for prologue, exchange and epilogue, 4 / 1.5 more for GeLU / its backward in an epilogue that runs on few compute units
  * only; a reduction launch 1.2 and 0.03 per partial tile written and read back.  128 tiles over K = 1024: whole 13, split in
- * two 23; 64 tiles over K = 4096: whole 28, split in four 23. */
+ * two 23; 64 tiles over K = 4096: whole 28, split in four 23.  (Where the step cost rises: 240 and 256 tiles take 0.9 per step at 65 steps,
+ * 0.95 to 1.1 at 76, 1.1 at 84.  Between 65 and 76 some sizes are 5 to 20 % faster here than what the planner takes instead, single
+ * forward sizes as much slower, 180 tiles over 152 K tiles 85 against 71; 64 is where none of them loses.) */
 int kpair_splits(const hap_gemm_problem* p, long long tiles, long long nk, double* us) {
   const long long cus = cu_count();
   const size_t ws_splits = p->ws ? p->ws_bytes / ((size_t)tiles * kSmallTileBytes) : 0;

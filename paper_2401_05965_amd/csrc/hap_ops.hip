@@ -540,8 +540,9 @@ int hap_colsum_grouped(int groups, int64_t rows, int64_t cols, int io_dtype, con
   const dim3 grid((unsigned)((cols + skew + per_block - 1) / per_block), (unsigned)parts, (unsigned)groups);
   const int64_t rpb = kColsumRowsPerBlock;
   const int* gl = group_len;
-  // Few rows: one partial row is the result; stage 1 writes it where it belongs and the second launch (2 us and the gap before it)
-  // is saved.
+  // Few rows: one partial row is the result; stage 1 writes it where it belongs and the second launch is saved (forward, backward with
+  // bias gradient and factor rebuild of an fp32 layer of 38 rows, 1024 x 1024: 33.0 -> 31.2 us).  Several groups' partial rows lie
+  // `cols` apart: outputs further apart still take both stages.
   const bool direct = parts == 1 && (groups == 1 || ldo == cols);
   float* const part = direct ? out : static_cast<float*>(ws);
   if (io_dtype == HAP_BF16) {
