@@ -268,11 +268,13 @@ Plan make_plan(const hap_gemm_problem* p) {
     pl.dma = 1;
     // 256-tiles: the ping-pong kernel, except when both operands are K-contiguous (bwd-data), where the two-stage kernel
     // with 128-byte rows per K tile is the faster one
-    // ... and except short contractions: below about 20 K tiles of 64 the four-stage ring's fill does not pay off (measured at
-    // K = 512 / 768 / 1024: the two-stage kernel is 7 / 4 / 1 % faster, from K = 1536 on the ping-pong kernel wins)
+    // ... and except the shortest contractions, over which the four-stage ring does not fill.  Two-stage -> ping-pong, microseconds:
+    // forward 15360 rows x 3072 over K = 64 / 128 / 320: 31.3 -> 33.4 / 35.5 -> 37.3 / 52.8 -> 55.3, 16384 x 2048 over 384: 41.1 -> 42.6
+    // (with GeLU 63.1 -> 62.2); from seven K tiles on the ping-pong kernel is ahead: forward 15360 x 3072 over 512 / 768 / 1024:
+    // 71.4 -> 65.7 / 83.4 -> 78.2 / 100.1 -> 94.0, bwd-weight 4096 x 8192 over 256 / 400 / 768 rows: 33.1 -> 33.3 / 44.7 -> 41.6 / 61.1 -> 57.7
     long long nk64 = 0;
     for (int s = 0; s < p->nseg; ++s) nk64 += p->k[s] > 0 ? (pl.skewK + p->k[s] + 63) / 64 : 0;
-    const bool short_k = nk64 < 20 && !(!p->a_kcontig && p->b_kcontig);
+    const bool short_k = nk64 < 7 && !(!p->a_kcontig && p->b_kcontig);
     pl.pingpong = big && !(p->a_kcontig && p->b_kcontig) && !short_k;
     pl.bk = pl.pingpong ? kPingPongBK : 64;
   }

@@ -178,6 +178,14 @@ def test_linear_deep_ragged_contractions(hap, full):
     run_linear_case(hap, "bf16", 150, 264, 1210, 1, [0, 603, 1210], act=True, bias=True, full=full)        # bwd-data contracts 603 | 607 columns
 
 
+@pytest.mark.parametrize("k", [304, 384, 392, 448, 712])
+def test_linear_big_tiles_over_short_contractions(hap, k):
+    """Outputs that fill the chip with 256-tiles over 5 to 12 K tiles of 64: the two-stage kernel up to six of them, the ping-pong kernel
+    (ring of four stages) beyond; the forward contracts k features, bwd-weight k rows of the first shard and 150 of the second."""
+    run_linear_case(hap, "bf16", 3900, k, 4040, 3, [0, 1], act=True, bias=True, full=False)
+    run_linear_case(hap, "bf16", k + 150, 3904, 4040, 0, [0, k, k + 150], act=False, bias=True, full=True)
+
+
 @pytest.mark.parametrize("k", [193, 256, 257, 385, 449, 768])
 def test_linear_few_tiles_share_their_contraction_between_wave_groups(hap, k):
     """Outputs of few 128-tiles over ranges that start and end inside a K tile: the two wave groups of a workgroup contract the same and
