@@ -55,6 +55,10 @@ struct hap_gemm_problem {
 /* Validates nothing beyond what the kernels need (callers validate user input); returns hap_status. */
 int hap_gemm_run(const hap_gemm_problem* p, void* stream);
 
+/* The backward products of one fp32 layer together: dw (weight gradient), dx (data gradient, or NULL) and, when dbias is given, the
+ * column sums of dw's B operand.  Sets *taken to 0, having done nothing, where they are not small enough to gain by it. */
+int hap_gemm_run_bwd_f32(const hap_gemm_problem* dx, const hap_gemm_problem* dw, float* dbias, int* taken, void* stream);
+
 /* Scratch that lets every problem split K as far as the engine would like to (an upper bound). */
 #define HAP_GEMM_WS_BYTES ((size_t)64 << 20)
 

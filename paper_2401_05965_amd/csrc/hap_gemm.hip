@@ -21,8 +21,9 @@
  * 4-stage ring of direct-to-LDS K tiles (all layouts but "both operands K-contiguous").  gemm_dma_kernel: bf16, two-stage ring,
  * 256 x 256 (both operands K-contiguous) and 128 x 128 (small outputs, remainder strips).  gemm_kpair_kernel: bf16, 128 x 128, at
  * most one tile per compute unit, two wave groups that split the tile's contraction.  gemm_kernel: register-staged, fp32
- * and what the direct kernels cannot address.  gemm_skinny_f32_kernel: fp32 products of at most 64 rows, contraction split over
- * the waves of a workgroup.  gemm_generic_kernel: scalar fallback.  Epilogues: bias, GeLU, pre-activation copy, fp32
+ * and what the direct kernels cannot address.  gemm_skinny_f32_kernel: fp32 products of few rows, contraction split over
+ * the waves of a workgroup.  gemm_rank_f32_kernel: fp32 products over few k of two M-/N-contiguous operands; linear_bwd_f32_kernel:
+ * both in one launch.  gemm_generic_kernel: scalar fallback.  Epilogues: bias, GeLU, pre-activation copy, fp32
  * accumulation, or the product times gelu'(saved pre-activation) - the activation backward of the layer that produced the
  * output's tensor.
  */
@@ -31,10 +32,10 @@
 namespace hap_gemm_detail {
 
 /* ---------------------------------------------------------------------------------------------
- * fp32 products with at most 64 output rows (a layer whose batch shard is a few dozen samples: the single fully-connected layer
+ * fp32 products of few output rows (a layer whose batch shard is a few dozen samples: the single fully-connected layer
  * of the smallest workload, 38 / 26 rows of 64).  Such a product has far too few output tiles for the chip, and splitting its
  * contraction over workgroups costs a second, dependent launch for the reduction - on this machine about as long as the product
- * itself.  Here the split happens INSIDE a workgroup: one workgroup owns one 16-row block or all (<= 64) rows of 16 output columns, its 16 waves each
+ * itself.  Here the split happens INSIDE a workgroup: one workgroup owns one 16-row block or up to 64 rows of 16 output columns, its 16 waves each
  * contract 1/16 of K with v_mfma_f32_16x16x4_f32, and their partial tiles are summed through LDS in a fixed order (deterministic).
  *   A (K-contiguous): lane (row r = lane % 16, k-quad q = lane / 16) fetches the 4 consecutive k values 16c + 4q .. + 3 of a
  *   16-wide chunk c as one 16-byte load and feeds element s to step s; B's lane (k-quad q, column) supplies the same k, so the
@@ -54,10 +55,9 @@ typedef float f32x4_t __attribute__((ext_vector_type(4)));
  * traffic (the weight is then read three times, out of L2); with all rows in one workgroup (4) the weight is read once, for outputs
  * wide enough to fill the chip by themselves.  That layer's forward, backward and factor rebuild: 38.2 us with 4, 31.9 with 1. */
 template <bool BKC, int RB>
-__global__ __launch_bounds__(1024) void gemm_skinny_f32_kernel(const SkinnyArgs g) {
-  __shared__ float red[16][16 * RB][16];             // one partial [rows][columns] tile per wave: 16 KB per row block
+__device__ __forceinline__ void skinny_f32_tile(const SkinnyArgs& g, int bx, int by, float (*red)[16 * RB][16]) {
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, r = lane & 15, kq = lane >> 4;
-  const int n0 = blockIdx.x * 16, col = n0 + r, row0 = blockIdx.y * (16 * RB);
+  const int n0 = bx * 16, col = n0 + r, row0 = by * (16 * RB);
   const int rb = (g.M - row0 + 15) >> 4;             // 16-row blocks in use
   const int kslice = ((g.K + 255) >> 8) << 4;        // k values per wave, a multiple of 16
   const int kb0 = wave * kslice;
@@ -114,15 +114,206 @@ __global__ __launch_bounds__(1024) void gemm_skinny_f32_kernel(const SkinnyArgs 
   *dst = v;
 }
 
-/* Whether hap_gemm_run hands the product to gemm_skinny_f32_kernel (see there). */
-static bool skinny_f32_applies(const hap_gemm_problem* p) {
-  if (p->in_dtype != HAP_F32 || p->c_dtype != HAP_F32 || p->M > 64 || !p->a_kcontig || p->nseg != 1) return false;
-  if (p->groups > 1 || p->group_len || p->force_generic || p->tile || p->dact) return false;
+template <bool BKC, int RB>
+__global__ __launch_bounds__(1024) void gemm_skinny_f32_kernel(const SkinnyArgs g) {
+  __shared__ float red[16][16 * RB][16];             // one partial [rows][columns] tile per wave: 16 KB per row block
+  skinny_f32_tile<BKC, RB>(g, blockIdx.x, blockIdx.y, red);
+}
+
+/* ---------------------------------------------------------------------------------------------
+ * fp32 products of two M-/N-contiguous operands over few k (the weight gradient of a layer whose batch shard is a few dozen rows, the
+ * rebuild from such factors): dW[m][n] = sum over k of X[k][m] dY[k][n].
+ * Bound: latency.  The operands' rows are the MFMA's lanes, so fragments come straight from global memory, 128 bytes per row and half
+ * wave: no LDS, no barrier on the way, and a wave has the loads of 32 k values in flight before its first MFMA.  A wave owns one 32 x 32
+ * tile; with KG = 4 four waves share it, each takes every fourth chunk of 16 k values, and the four meet in LDS in a fixed order.  The
+ * waves of the first tile row also add up their columns of B where the caller asks (the bias gradient: B is in their registers anyway).
+ * ------------------------------------------------------------------------------------------- */
+struct RankArgs {
+  int M, N, nseg, accumulate;
+  int tiles_n;                      // workgroup tiles (64 x 64) along N
+  long long lda, ldb, ldc;
+  float* c;
+  float* colsum;                    // [N] sums over all k of B, or nullptr
+  const float* a[HAP_GEMM_MAX_SEG];
+  const float* b[HAP_GEMM_MAX_SEG];
+  int k[HAP_GEMM_MAX_SEG];          // > 0
+};
+
+/* CK: k values of a chunk.  FOLD: no chain of additions longer than 128 k values (left out where there are no more). */
+template <int KG, int CK, bool FOLD>
+__device__ __forceinline__ void rank_f32_tile(const RankArgs& g, int tile, float* red) {
+  const int lane = threadIdx.x & 63, wave = uni((int)threadIdx.x >> 6), cl = lane & 31, h = lane >> 5;
+  const int grp = wave >> 2, w = wave & 3;
+  const int tm = tile / g.tiles_n, tn = tile - tm * g.tiles_n;
+  const int m0 = (tm * 2 + (w >> 1)) * 32, n0 = (tn * 2 + (w & 1)) * 32;
+  const bool sums = g.colsum && m0 == 0;
+  // lane offsets of k = h; lanes beyond the matrix read out of range (zeros), and so do k beyond the segment
+  const unsigned va = m0 + cl < g.M ? (unsigned)((h * g.lda + m0 + cl) * 4) : kOobOffset;
+  const unsigned vb = n0 + cl < g.N ? (unsigned)((h * g.ldb + n0 + cl) * 4) : kOobOffset;
+  f32x16_t acc, folded;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) { acc[e] = 0.0f; folded[e] = 0.0f; }
+  float cs[2] = {0.0f, 0.0f}, cst = 0.0f;
+  int seg = 0, k0 = 0, k = g.nseg ? uni(g.k[0]) : 0;  // next chunk
+  auto skip = [&](int chunks) {
+    for (int i = 0; i < chunks && seg < g.nseg; ++i) {
+      k0 += CK;
+      if (k0 >= k) { seg = uni(seg + 1); k0 = 0; k = seg < g.nseg ? uni(g.k[seg]) : 0; }
+    }
+  };
+  float av[2][CK / 2], bv[2][CK / 2];
+  int len[2];                                        // k values of the two chunks in registers, 0: none
+  auto load = [&](auto which) {
+    constexpr int Q = decltype(which)::value;
+    len[Q] = 0;
+    if (seg >= g.nseg) return;
+    const __amdgpu_buffer_rsrc_t ra = make_rsrc(g.a[seg], (unsigned)(((long long)(k - 1) * g.lda + g.M) * 4));
+    const __amdgpu_buffer_rsrc_t rb = make_rsrc(g.b[seg], (unsigned)(((long long)(k - 1) * g.ldb + g.N) * 4));
+    len[Q] = k - k0 < CK ? k - k0 : CK;
+    // (the whole offset goes in the lanes' part: the range check does not hold for a scalar offset beyond the extent)
+    const unsigned oa = va + (unsigned)((long long)k0 * g.lda * 4), ob = vb + (unsigned)((long long)k0 * g.ldb * 4);
+#pragma unroll
+    for (int i = 0; i < CK / 2; ++i) {
+      av[Q][i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(ra, oa + i * (unsigned)(g.lda * 8), 0, 0));
+      bv[Q][i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rb, ob + i * (unsigned)(g.ldb * 8), 0, 0));
+    }
+    skip(KG);
+  };
+  auto contract = [&](auto which) {
+    constexpr int Q = decltype(which)::value;
+#pragma unroll
+    for (int i = 0; i < CK / 2; ++i) {
+      if (i % 2 == 0 && len[Q] <= 2 * i) break;
+      acc = mfma(av[Q][i], bv[Q][i], acc);
+      if (sums) cs[i & 1] += bv[Q][i];
+    }
+  };
+  if (m0 < g.M && n0 < g.N) {
+    skip(grp);
+    load(std::integral_constant<int, 0>());
+    load(std::integral_constant<int, 1>());
+    for (int done = 0; len[0] > 0; ++done) {
+      if (FOLD && done == 64 / CK) {
+        folded += acc; cst += cs[0] + cs[1];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[e] = 0.0f;
+        cs[0] = cs[1] = 0.0f;
+        done = 0;
+      }
+      contract(std::integral_constant<int, 0>());
+      load(std::integral_constant<int, 0>());
+      if (len[1] > 0) contract(std::integral_constant<int, 1>());
+      load(std::integral_constant<int, 1>());
+    }
+    if (FOLD) acc += folded;
+    cst += cs[0] + cs[1];
+  }
+  cst += __shfl_xor(cst, 32, 64);
+  constexpr int EW = 16 / KG;                        // accumulator elements that a wave stores
+  const int e0 = grp * EW;
+  if constexpr (KG > 1) {
+    float* const sums_at = red + KG * 4 * 16 * 64;   // [group][wave column][32]
+#pragma unroll
+    for (int e = 0; e < 16; ++e) red[((grp * 4 + w) * 16 + e) * 64 + lane] = acc[e];
+    if (sums && h == 0) sums_at[(grp * 2 + (w & 1)) * 32 + cl] = cst;
+    __syncthreads();
+    if (sums) {
+      cst = 0.0f;
+#pragma unroll
+      for (int q = 0; q < KG; ++q) cst += sums_at[(q * 2 + (w & 1)) * 32 + cl];
+    }
+  }
+  if (m0 >= g.M || n0 + cl >= g.N) return;
+  if (sums && grp == 0 && h == 0) g.colsum[n0 + cl] = cst;
+#pragma unroll
+  for (int x = 0; x < EW; ++x) {
+    const int e = KG > 1 ? e0 + x : x;
+    float v;
+    if constexpr (KG > 1) {
+      v = 0.0f;
+#pragma unroll
+      for (int q = 0; q < KG; ++q) v += red[((q * 4 + w) * 16 + e) * 64 + lane];
+    } else {
+      v = acc[x];
+    }
+    const int m = m0 + (e >> 2) * 8 + h * 4 + (e & 3);
+    if (m < g.M) {
+      float* dst = g.c + (long long)m * g.ldc + n0 + cl;
+      *dst = g.accumulate ? *dst + v : v;
+    }
+  }
+}
+
+constexpr int kRankRed = 4 * 4 * 16 * 64 + 4 * 2 * 32;     // floats of LDS with KG = 4
+
+template <int KG>
+__global__ __launch_bounds__(256 * KG) void gemm_rank_f32_kernel(const RankArgs g) {
+  __shared__ float red[KG > 1 ? kRankRed : 1];
+  rank_f32_tile<KG, 16, true>(g, blockIdx.x, red);
+}
+
+/* bwd-data of few rows and the weight (and bias) gradient of the same layer in one launch: neither fills the chip and neither needs the
+ * other.  The first `nrank` workgroups take the weight gradient, nx x (rows / 16) the data gradient. */
+__global__ __launch_bounds__(1024, 8) void linear_bwd_f32_kernel(const RankArgs w, const SkinnyArgs x, int nrank, int nx) {
+  __shared__ float red[kRankRed];
+  if ((int)blockIdx.x < nrank) { rank_f32_tile<4, 8, false>(w, blockIdx.x, red); return; }
+  const int id = blockIdx.x - nrank;
+  skinny_f32_tile<true, 1>(x, id % nx, id / nx, reinterpret_cast<float (*)[16][16]>(red));
+}
+
+/* Compute units of the current device (256 on MI355X), asked once per device; the planner's round arithmetic uses it. */
+int cu_count() {
+  static int cached[64] = {};
+  int device = 0;
+  if (hipGetDevice(&device) != hipSuccess || device < 0 || device >= 64) return 256;
+  if (cached[device] == 0) {     // benign race: every thread stores the same value
+    int n = 0;
+    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || n < 8) n = 256;
+    cached[device] = n;
+  }
+  return cached[device];
+}
+
+/* 16-row blocks per workgroup with which gemm_skinny_f32_kernel takes the product: 1, 4 (all rows, at most 64), or 0 where it does not.
+ * One row block each as long as that is at most a thousand workgroups of a million k values in all, and, for up to 64 rows, the columns
+ * alone would leave half of the compute units idle.  Microseconds, what ran before -> one row block:
+ *   forward, rows x in x out:  64 x 2048 x 2048 22.3 -> 16.3    100 x 1024 x 1024 13.1 -> 8.3    256 x 512 x 512: 11.2 -> 6.2    256 x 1024 x 1024 17.6 -> 14.2
+ *   bwd-data:  128 x 1024 x 1024 13.4 -> 9.2    512 x 512 x 512 12.4 -> 10.8 (1024 workgroups)
+ *   beyond:    128 x 2048 x 2048 27.0 -> 29.9 (1024 workgroups over K = 2048)    256 x 2048 x 512 16.5 -> 18.8 (2048 workgroups)
+ *   up to 64 rows, 256 column blocks and more, all rows -> one row block: 38 x 512 x 4096 7.0 -> 8.5    64 x 1024 x 4096 12.7 -> 16.1 */
+static int skinny_f32_row_blocks(const hap_gemm_problem* p) {
+  if (p->in_dtype != HAP_F32 || p->c_dtype != HAP_F32 || !p->a_kcontig || p->nseg != 1) return 0;
+  if (p->groups > 1 || p->group_len || p->force_generic || p->tile || p->dact) return 0;
   const int64_t K = p->k[0];
-  if (K < 256 || K % 4 || K > 0x7fffffff || (p->N + 63) / 64 >= 128) return false;      // enough 64-wide tiles: the tiled kernel fills the chip by itself
-  if (p->lda % 4 || (uintptr_t)p->a[0] % 16) return false;
-  if (p->b_kcontig && (p->ldb % 4 || (uintptr_t)p->b[0] % 16)) return false;
-  return true;
+  if (K < 256 || K % 4 || K > 0x7fffffff || (p->N + 63) / 64 >= 128) return 0;      // enough 64-wide tiles: the tiled kernel fills the chip by itself
+  if (p->lda % 4 || (uintptr_t)p->a[0] % 16) return 0;
+  if (p->b_kcontig && (p->ldb % 4 || (uintptr_t)p->b[0] % 16)) return 0;
+  const int64_t columns = (p->N + 15) / 16, rows = (p->M + 15) / 16, cus = cu_count();
+  if (p->M > 64) return rows <= 4 * cus && columns * rows <= 4 * cus && columns * rows * K <= 4096 * cus ? 1 : 0;
+  return columns * rows <= cus || columns * 2 <= cus ? 1 : 4;
+}
+
+/* Whether a product goes to gemm_rank_f32_kernel: as many k values as its waves contract in the time that the tiled kernel and, where it
+ * splits K, the reduction behind it take.  Microseconds, tiled -> this kernel:
+ *   1024 x 1024 (256 tiles of 64 x 64) over k = 38 / 256 / 512 / 2048: 8.2 -> 5.2 / 17.2 -> 9.0 / 25.2 -> 13.7 / 50.6 -> 43.0
+ *   512 x 512 (64 tiles) over 200 / 400 / 512 / 1024: 11.9 -> 7.5 / 12.8 -> 10.9 / 12.2 -> 13.0 / 17.7 -> 22.5    1024 x 512 over 2048: 34.2 -> 42.4
+ *   2048 x 2048 (1024 tiles) over 64 / 450 / 512: 14.4 -> 11.6 / 44.4 -> 40.6 / 45.9 -> 46.1    300 x 300 (25 tiles) over 448: 11.1 -> 12.0 */
+static bool rank_f32_applies(const hap_gemm_problem* p) {
+  if (p->in_dtype != HAP_F32 || p->c_dtype != HAP_F32 || p->a_kcontig || p->b_kcontig || p->M <= 0 || p->N <= 0) return false;
+  if (p->groups > 1 || p->group_len || p->force_generic || p->tile || p->dact || p->act != HAP_ACT_NONE || p->bias || p->preact) return false;
+  const int64_t tiles = ((p->M + 63) / 64) * ((p->N + 63) / 64);
+  int64_t most = tiles * 7 < 2048 ? tiles * 7 : 2048, k = 0;
+  if (tiles > 2 * cu_count()) most = 448;
+  else if (most < 256) most = 256;
+  if (tiles > 0x7fffffff || p->M > 0x7fffffff || p->N > 0x7fffffff) return false;
+  for (int s = 0; s < p->nseg; ++s) {
+    if (p->k[s] <= 0) continue;
+    if ((uintptr_t)p->a[s] % 4 || (uintptr_t)p->b[s] % 4) return false;
+    // every offset that a lane forms, also past the segment's end, stays below the out-of-range marker
+    if ((p->k[s] + 16) * p->lda * 4 + p->M * 4 >= kViewLimitBytes || (p->k[s] + 16) * p->ldb * 4 + p->N * 4 >= kViewLimitBytes) return false;
+    k += p->k[s];
+  }
+  return k <= most;
 }
 
 /* Scalar fallback for operand views the tiled kernel cannot address with aligned 16-byte chunks
@@ -169,19 +360,6 @@ __global__ __launch_bounds__(256) void gemm_generic_kernel(const GenericArgs g) 
   TC* dst = reinterpret_cast<TC*>(static_cast<char*>(g.c) + grp * g.gc) + (long long)m * g.ldc + n;
   if (g.accumulate) acc += load_s<TC>(dst);
   store_c<TC>(dst, acc);
-}
-
-/* Compute units of the current device (256 on MI355X), asked once per device; the planner's round arithmetic uses it. */
-int cu_count() {
-  static int cached[64] = {};
-  int device = 0;
-  if (hipGetDevice(&device) != hipSuccess || device < 0 || device >= 64) return 256;
-  if (cached[device] == 0) {     // benign race: every thread stores the same value
-    int n = 0;
-    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || n < 8) n = 256;
-    cached[device] = n;
-  }
-  return cached[device];
 }
 
 constexpr int kPingPongBK = 32;   // K step of the ping-pong kernel
@@ -572,6 +750,80 @@ static int run_auto_tiled(const hap_gemm_problem* p, const Plan& pl, void* strea
   }
 }
 
+static SkinnyArgs skinny_args(const hap_gemm_problem* p) {
+  SkinnyArgs g;
+  g.M = (int)p->M; g.N = (int)p->N; g.K = (int)p->k[0];
+  g.lda = p->lda; g.ldb = p->ldb; g.ldc = p->ldc; g.ldp = p->ldp;
+  g.a = static_cast<const float*>(p->a[0]); g.b = static_cast<const float*>(p->b[0]);
+  g.c = static_cast<float*>(p->c); g.preact = static_cast<float*>(p->preact); g.bias = static_cast<const float*>(p->bias);
+  g.act = p->act; g.accumulate = p->accumulate;
+  return g;
+}
+
+static RankArgs rank_args(const hap_gemm_problem* p, float* colsum) {
+  RankArgs g;
+  g.M = (int)p->M; g.N = (int)p->N; g.accumulate = p->accumulate;
+  g.lda = p->lda; g.ldb = p->ldb; g.ldc = p->ldc;
+  g.c = static_cast<float*>(p->c); g.colsum = colsum;
+  g.tiles_n = (int)cdiv(p->N, 64);
+  g.nseg = 0;
+  for (int s = 0; s < p->nseg; ++s) {
+    if (p->k[s] <= 0) continue;
+    g.a[g.nseg] = static_cast<const float*>(p->a[s]); g.b[g.nseg] = static_cast<const float*>(p->b[s]); g.k[g.nseg] = (int)p->k[s];
+    ++g.nseg;
+  }
+  return g;
+}
+
+static int run_rank_f32(const RankArgs& g, hipStream_t st) {
+  const dim3 grid((unsigned)(cdiv(g.M, 64) * g.tiles_n));
+  // (enough tiles to give every SIMD four waves: one wave each takes a whole tile, 2048 x 2048 over 64: 15.6 -> 11.6 us)
+  if (grid.x > 2u * cu_count()) hipLaunchKernelGGL(gemm_rank_f32_kernel<1>, grid, dim3(256), 0, st, g);
+  else hipLaunchKernelGGL(gemm_rank_f32_kernel<4>, grid, dim3(1024), 0, st, g);
+  const hipError_t e = hipGetLastError();
+  return e == hipSuccess ? HAP_OK : hap_fail(HAP_EDEVICE, "fp32 few-k gemm launch: %s", hipGetErrorString(e));
+}
+
+/* Whether two fp32 matrices (rows of `cols` elements, ld apart) share addresses; NULL or empty ones do not. */
+static bool overlap_f32(const void* a, int64_t rows_a, int64_t cols_a, int64_t lda, const void* b, int64_t rows_b, int64_t cols_b, int64_t ldb) {
+  if (!a || !b || rows_a <= 0 || cols_a <= 0 || rows_b <= 0 || cols_b <= 0) return false;
+  const char *pa = static_cast<const char*>(a), *pb = static_cast<const char*>(b);
+  return pa < pb + ((rows_b - 1) * ldb + cols_b) * 4 && pb < pa + ((rows_a - 1) * lda + cols_a) * 4;
+}
+
+int hap_gemm_run_bwd_f32(const hap_gemm_problem* dx, const hap_gemm_problem* dw, float* dbias, int* taken, void* stream) {
+  *taken = 0;
+  if (!rank_f32_applies(dw)) return HAP_OK;
+  {
+    // The products apart run one after the other, so that one may write where an earlier one has read; together they must not.
+    const int64_t tokens = dw->k[0], in = dw->M, out = dw->N;
+    const struct { const void* p; int64_t rows, cols, ld; } input[3] = {{dw->a[0], tokens, in, dw->lda}, {dw->b[0], tokens, out, dw->ldb},
+                                                                        {dx ? dx->b[0] : nullptr, in, out, dx ? dx->ldb : 0}},
+        output[3] = {{dw->c, in, out, dw->ldc}, {dbias, 1, out, out}, {dx ? dx->c : nullptr, tokens, in, dx ? dx->ldc : 0}};
+    for (int o = 0; o < 3; ++o) {
+      for (int i = 0; i < 3; ++i)
+        if (overlap_f32(output[o].p, output[o].rows, output[o].cols, output[o].ld, input[i].p, input[i].rows, input[i].cols, input[i].ld)) return HAP_OK;
+      for (int i = 0; i < o; ++i)
+        if (overlap_f32(output[o].p, output[o].rows, output[o].cols, output[o].ld, output[i].p, output[i].rows, output[i].cols, output[i].ld)) return HAP_OK;
+    }
+  }
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  const RankArgs w = rank_args(dw, dbias);
+  *taken = 1;
+  if (dx && dx->M > 0 && dx->N > 0 && dw->k[0] <= 512 && skinny_f32_row_blocks(dx) == 1) {
+    const long long nrank = cdiv(dw->M, 64) * w.tiles_n, nx = cdiv(dx->N, 16), rows = cdiv(dx->M, 16);
+    // (workgroups that the chip holds at once; twice as many over short contractions: 200 rows x 512 x 512 18.7 us apart, 9.1 together,
+    // 400 x 512 x 512 21.3 and 13.6; over k = 1024 100 x 1024 x 1024 15.1 and 15.6.  38 x 1024 x 1024: 11.0 and 8.0.)
+    if (nrank + nx * rows <= (dx->k[0] <= 512 ? 4 : 2) * cu_count()) {
+      hipLaunchKernelGGL(linear_bwd_f32_kernel, dim3((unsigned)(nrank + nx * rows)), dim3(1024), 0, st, w, skinny_args(dx), (int)nrank, (int)nx);
+      const hipError_t e = hipGetLastError();
+      return e == hipSuccess ? HAP_OK : hap_fail(HAP_EDEVICE, "fp32 layer backward launch: %s", hipGetErrorString(e));
+    }
+  }
+  if (dx) { const int rc = hap_gemm_run(dx, stream); if (rc) return rc; }
+  return run_rank_f32(w, st);
+}
+
 int hap_gemm_run(const hap_gemm_problem* p, void* stream) {
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (p->M <= 0 || p->N <= 0) return HAP_OK;
@@ -597,15 +849,11 @@ int hap_gemm_run(const hap_gemm_problem* p, void* stream) {
     int rc;
     if (run_large(p, stream, &rc)) return rc;
   }
-  if (skinny_f32_applies(p)) {
-    SkinnyArgs g;
-    g.M = (int)p->M; g.N = (int)p->N; g.K = (int)p->k[0];
-    g.lda = p->lda; g.ldb = p->ldb; g.ldc = p->ldc; g.ldp = p->ldp;
-    g.a = static_cast<const float*>(p->a[0]); g.b = static_cast<const float*>(p->b[0]);
-    g.c = static_cast<float*>(p->c); g.preact = static_cast<float*>(p->preact); g.bias = static_cast<const float*>(p->bias);
-    g.act = p->act; g.accumulate = p->accumulate;
+  if (rank_f32_applies(p)) return run_rank_f32(rank_args(p, nullptr), st);
+  if (const int row_blocks = skinny_f32_row_blocks(p)) {
+    const SkinnyArgs g = skinny_args(p);
     const unsigned nb = (unsigned)((p->N + 15) / 16), rb = (unsigned)((p->M + 15) / 16);
-    if (nb * rb <= (unsigned)cu_count()) {
+    if (row_blocks == 1) {
       if (p->b_kcontig) hipLaunchKernelGGL((gemm_skinny_f32_kernel<true, 1>), dim3(nb, rb), dim3(1024), 0, st, g);
       else hipLaunchKernelGGL((gemm_skinny_f32_kernel<false, 1>), dim3(nb, rb), dim3(1024), 0, st, g);
     } else if (p->b_kcontig) hipLaunchKernelGGL((gemm_skinny_f32_kernel<true, 4>), dim3(nb), dim3(1024), 0, st, g);

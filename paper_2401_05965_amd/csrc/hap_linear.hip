@@ -207,32 +207,34 @@ static int linear_bwd_impl(const hap_linear_desc* d, int shard_index, const void
   char* gemm_ws = colsum_ws + round_up((int64_t)hap_colsum_workspace(v.tok_n, v.out_n), 256);
   const size_t used = ws ? (size_t)(gemm_ws - static_cast<char*>(ws)) : 0;
   const size_t gemm_ws_bytes = (ws && ws_bytes > used) ? ws_bytes - used : 0;
+  hap_gemm_problem px = {}, pw = {};
   if (dX) {
-    hap_gemm_problem p = {};
-    p.M = v.tok_n; p.N = v.in_n;
-    p.nseg = 1; p.k[0] = v.out_n;
-    p.a[0] = dP; p.lda = lddp; p.a_kcontig = 1;
-    p.b[0] = at(W, o.w, es); p.ldb = d->ldw; p.b_kcontig = 1;   // B(k = out, n = in) = W[n*ldw + k]
-    p.in_dtype = d->io_dtype;
-    p.c = at(dX, o.x, es); p.ldc = d->ldx; p.c_dtype = d->io_dtype;
-    if (x_preact) { p.dact_preact = at(x_preact, o.x, es); p.ldd = d->ldx; p.dact = x_act; }
-    p.ws = gemm_ws_bytes ? gemm_ws : NULL; p.ws_bytes = gemm_ws_bytes;
-    rc = hap_gemm_run(&p, stream);
-    if (rc) return rc;
+    px.M = v.tok_n; px.N = v.in_n;
+    px.nseg = 1; px.k[0] = v.out_n;
+    px.a[0] = dP; px.lda = lddp; px.a_kcontig = 1;
+    px.b[0] = at(W, o.w, es); px.ldb = d->ldw; px.b_kcontig = 1;   // B(k = out, n = in) = W[n*ldw + k]
+    px.in_dtype = d->io_dtype;
+    px.c = at(dX, o.x, es); px.ldc = d->ldx; px.c_dtype = d->io_dtype;
+    if (x_preact) { px.dact_preact = at(x_preact, o.x, es); px.ldd = d->ldx; px.dact = x_act; }
+    px.ws = gemm_ws_bytes ? gemm_ws : NULL; px.ws_bytes = gemm_ws_bytes;
   }
   if (dW) {
     const int wes = esize(dW_dtype);
-    hap_gemm_problem p = {};
-    p.M = v.in_n; p.N = v.out_n;
-    p.nseg = 1; p.k[0] = v.tok_n;
-    p.a[0] = at(X, o.x, es); p.lda = d->ldx; p.a_kcontig = 0;   // A(m = in, k = token) = X[k*ldx + m]
-    p.b[0] = dP; p.ldb = lddp; p.b_kcontig = 0;
-    p.in_dtype = d->io_dtype;
-    p.c = at(dW, o.w, wes); p.ldc = d->ldw; p.c_dtype = dW_dtype;
-    p.ws = gemm_ws_bytes ? gemm_ws : NULL; p.ws_bytes = gemm_ws_bytes;
-    rc = hap_gemm_run(&p, stream);
-    if (rc) return rc;
+    pw.M = v.in_n; pw.N = v.out_n;
+    pw.nseg = 1; pw.k[0] = v.tok_n;
+    pw.a[0] = at(X, o.x, es); pw.lda = d->ldx; pw.a_kcontig = 0;   // A(m = in, k = token) = X[k*ldx + m]
+    pw.b[0] = dP; pw.ldb = lddp; pw.b_kcontig = 0;
+    pw.in_dtype = d->io_dtype;
+    pw.c = at(dW, o.w, wes); pw.ldc = d->ldw; pw.c_dtype = dW_dtype;
+    pw.ws = gemm_ws_bytes ? gemm_ws : NULL; pw.ws_bytes = gemm_ws_bytes;
   }
+  if (dW && d->io_dtype == HAP_F32) {
+    int taken;
+    rc = hap_gemm_run_bwd_f32(dX ? &px : NULL, &pw, dbias ? dbias + o.b : NULL, &taken, stream);
+    if (rc || taken) return rc;
+  }
+  if (dX && (rc = hap_gemm_run(&px, stream))) return rc;
+  if (dW && (rc = hap_gemm_run(&pw, stream))) return rc;
   if (dbias) {
     rc = hap_colsum(v.tok_n, v.out_n, d->io_dtype, dP, lddp, dbias + o.b, colsum_ws, hap_colsum_workspace(v.tok_n, v.out_n), stream);
     if (rc) return rc;

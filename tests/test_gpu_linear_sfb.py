@@ -178,6 +178,48 @@ def test_linear_deep_ragged_contractions(hap, full):
     run_linear_case(hap, "bf16", 150, 264, 1210, 1, [0, 603, 1210], act=True, bias=True, full=full)        # bwd-data contracts 603 | 607 columns
 
 
+@pytest.mark.parametrize("tokens,in_f,out_f", [(1, 300, 257), (8, 256, 64), (9, 288, 31), (38, 1024, 1024), (64, 292, 1000), (65, 256, 272), (113, 512, 260), (256, 264, 256),
+                                               (257, 512, 96), (449, 512, 512), (70, 2080, 1040), (40, 33, 4100)])
+@pytest.mark.parametrize("pad", [0, 1])
+def test_fp32_layers_of_few_rows(hap, tokens, in_f, out_f, pad):
+    """fp32 weight gradients over few rows (k chunks of 8 and 16, one or four waves per 32 x 32 tile), with and without the data gradient
+    of few rows in the same launch, the bias gradient from the same registers; pitches off the 16-byte grid take other kernels for dX."""
+    run_linear_case(hap, "f32", tokens, in_f, out_f, 3, [0, 1], act=False, bias=True, full=False, pad=pad)
+    run_linear_case(hap, "f32", tokens, in_f, out_f, 1, [0, out_f // 3 + 1, out_f], act=True, bias=True, full=True)
+
+
+@pytest.mark.parametrize("rows", [[38, 26], [0, 1, 17, 0, 64, 33], [0, 0], [200, 311]])
+@pytest.mark.parametrize("in_f,out_f", [(1024, 1024), (100, 95), (2049, 2080)])
+def test_fp32_sfb_over_few_rows(hap, rows, in_f, out_f):
+    """Segments that end inside a chunk, empty ones among them; the sums join what is there with accumulate, and padding is never read."""
+    cap = max(rows) + 2
+    Xh, Xd, dYh, dYd = [], [], [], []
+    for i in range(len(rows)):
+        a, b = gen(2, T.SFB_X + i, (cap, in_f), 1.0, "f32"); Xh.append(a); Xd.append(b)
+        a, b = gen(2, T.SFB_DY + i, (cap, out_f), 1.0, "f32"); dYh.append(a); dYd.append(b)
+        Xd[i][rows[i]:] = float("nan"); dYd[i][rows[i]:] = float("nan")
+    ref = osfb.sfb_grad(Xh, dYh, rows)
+    dW = empty((in_f, out_f + 3), "f32", 7)
+    for accumulate in (False, True):
+        hap.hap_sfb_grad(Xd, dYd, rows, in_f, out_f, in_f, out_f, hap.F32, dW, out_f + 3, accumulate=accumulate)
+        got = host(dW)
+        assert (got[:, out_f:] == 7).all(), "the pitch's padding was written"
+        if any(rows): check("fp32 sfb", got[:, :out_f], ref * (2 if accumulate else 1), "f32")
+        else: assert not got[:, :out_f].any()
+
+
+def test_fp32_backward_into_its_own_operands_keeps_the_order(hap):
+    """The weight gradient may overwrite the weight that the data gradient has read, the bias gradient a row of X that the weight gradient
+    has read: as by products that run one after the other."""
+    Xh, Xd = gen(5, T.X, (38, 1024), 1.0, "f32"); Wh, Wd = gen(5, T.W, (1024, 1024), 0.05, "f32"); Gh, Gd = gen(5, T.DY, (38, 1024), 1.0, "f32")
+    desc = hap.LinearDesc(38, 1024, 1024, hap.REPLICATED, [0, 1], hap.F32, m=1)
+    ws = empty((hap.hap_linear_bwd_workspace(desc, 0),), "u8")
+    dXo, dWo, dbo = olin.linear_bwd(Xh, Wh, None, Gh)
+    dX = empty((38, 1024), "f32", 0)
+    hap.hap_sharded_linear_bwd(desc, 0, Xd, Wd, None, Gd, dX, Wd, hap.F32, Xd[3], ws)
+    check("dX", host(dX), dXo, "f32"); check("dW over W", host(Wd), dWo, "f32"); check("db over X", host(Xd)[3], dbo, "f32")
+
+
 @pytest.mark.parametrize("k", [304, 384, 392, 448, 712])
 def test_linear_big_tiles_over_short_contractions(hap, k):
     """Outputs that fill the chip with 256-tiles over 5 to 12 K tiles of 64: the two-stage kernel up to six of them, the ping-pong kernel
