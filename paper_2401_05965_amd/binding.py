@@ -140,27 +140,35 @@ for _n in ("hap_linear_fwd_workspace", "hap_linear_bwd_workspace", "hap_sfb_work
         getattr(lib, _n).restype = C.c_size_t
 
 
-def _ptr(t) -> C.c_void_p:
-    if t is None:
-        return C.c_void_p(None)
-    if isinstance(t, int):
-        return C.c_void_p(t)
-    return C.c_void_p(t.data_ptr())
+# Signatures of the entry points that launch device work: with them ctypes converts plain integers itself, which costs a fraction of
+# wrapping every argument in an object (p pointer, i int, l int64, z size_t).
+for _n, _sig in (("hap_sharded_linear_fwd", "pipppppp" "zp"), ("hap_sharded_linear_bwd", "pippppppip" "pzp"),
+                 ("hap_sharded_linear_bwd_dact", "pippppppip" "pipzp"), ("hap_sfb_grad", "ippp" "llll" "ipli" "pzp"),
+                 ("hap_sfb_grad_static", "ippp" "llll" "ipli" "p"), ("hap_moe_linear_fwd", "pippppppp" "zp"),
+                 ("hap_moe_linear_bwd", "pipppppppip" "pzp"), ("hap_moe_linear_bwd_dact", "pipppppppip" "pipzp"),
+                 ("hap_allgather_pad", "piplplp"), ("hap_allgather_assemble", "ppp" "plp"), ("hap_reducescatter_split", "pplppp"),
+                 ("hap_sharded_attn_fwd", "pippppp" "pzp"), ("hap_sharded_attn_bwd", "pippppppppp" "pzp"),
+                 ("hap_layernorm_fwd", "lli" "ppppppp"), ("hap_layernorm_bwd", "lli" "ppppppppp" "pzp"),
+                 ("hap_gelu_bwd", "lliplplplp"), ("hap_add", "lliplplpplp"), ("hap_colsum", "lliplppzp")):
+    getattr(lib, _n).argtypes = [{"p": C.c_void_p, "i": C.c_int, "l": C.c_int64, "z": C.c_size_t}[c] for c in _sig]
 
 
-def _stream(stream) -> C.c_void_p:
+def _ptr(t):
+    """Address of a tensor (or the address itself), None for no tensor."""
+    return t if t is None or isinstance(t, int) else t.data_ptr()
+
+
+def _stream(stream):
     if stream is None:
-        import torch
-        return C.c_void_p(torch.cuda.current_stream().cuda_stream)
-    if isinstance(stream, int):
-        return C.c_void_p(stream)
-    return C.c_void_p(stream.cuda_stream)
+        # torch.cuda.current_stream().cuda_stream without the stream object around it
+        if torch.cuda.is_initialized():
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        return torch.cuda.current_stream().cuda_stream
+    return stream if isinstance(stream, int) else stream.cuda_stream
 
 
 def _ws(ws):
-    if ws is None:
-        return C.c_void_p(None), C.c_size_t(0)
-    return C.c_void_p(ws.data_ptr()), C.c_size_t(ws.numel() * ws.element_size())
+    return (None, 0) if ws is None else (ws.data_ptr(), ws.numel() * ws.element_size())
 
 
 def _check(status: int, where: str):
@@ -358,22 +366,22 @@ def hap_linear_bwd_workspace(desc: LinearDesc, shard_index: int) -> int:
 
 def hap_sharded_linear_fwd(desc: LinearDesc, shard_index, X, W, bias, Y, preact=None, ws=None, stream=None):
     wp, wb = _ws(ws)
-    _check(lib.hap_sharded_linear_fwd(C.byref(desc.c), C.c_int(shard_index), _ptr(X), _ptr(W), _ptr(bias), _ptr(Y),
+    _check(lib.hap_sharded_linear_fwd(C.byref(desc.c), shard_index, _ptr(X), _ptr(W), _ptr(bias), _ptr(Y),
                                       _ptr(preact), wp, wb, _stream(stream)), "hap_sharded_linear_fwd")
 
 
 def hap_sharded_linear_bwd(desc: LinearDesc, shard_index, X, W, preact, dY, dX, dW, dW_dtype, dbias, ws=None, stream=None):
     wp, wb = _ws(ws)
-    _check(lib.hap_sharded_linear_bwd(C.byref(desc.c), C.c_int(shard_index), _ptr(X), _ptr(W), _ptr(preact), _ptr(dY),
-                                      _ptr(dX), _ptr(dW), C.c_int(dW_dtype), _ptr(dbias), wp, wb, _stream(stream)),
+    _check(lib.hap_sharded_linear_bwd(C.byref(desc.c), shard_index, _ptr(X), _ptr(W), _ptr(preact), _ptr(dY),
+                                      _ptr(dX), _ptr(dW), dW_dtype, _ptr(dbias), wp, wb, _stream(stream)),
            "hap_sharded_linear_bwd")
 
 
 def hap_sharded_linear_bwd_dact(desc: LinearDesc, shard_index, X, W, preact, dY, dX, dW, dW_dtype, dbias, x_preact, x_act,
                                 ws=None, stream=None):
     wp, wb = _ws(ws)
-    _check(lib.hap_sharded_linear_bwd_dact(C.byref(desc.c), C.c_int(shard_index), _ptr(X), _ptr(W), _ptr(preact), _ptr(dY),
-                                           _ptr(dX), _ptr(dW), C.c_int(dW_dtype), _ptr(dbias), _ptr(x_preact), C.c_int(x_act),
+    _check(lib.hap_sharded_linear_bwd_dact(C.byref(desc.c), shard_index, _ptr(X), _ptr(W), _ptr(preact), _ptr(dY),
+                                           _ptr(dX), _ptr(dW), dW_dtype, _ptr(dbias), _ptr(x_preact), x_act,
                                            wp, wb, _stream(stream)), "hap_sharded_linear_bwd_dact")
 
 
@@ -382,8 +390,8 @@ def hap_sfb_grad(Xs, dYs, rows, in_features, out_features, ldx, ldy, in_dtype, d
     xp = (C.c_void_p * m)(*[_ptr(t) for t in Xs])
     yp = (C.c_void_p * m)(*[_ptr(t) for t in dYs])
     wp, wb = _ws(ws)
-    _check(lib.hap_sfb_grad(C.c_int(m), xp, yp, (C.c_int64 * m)(*map(int, rows)), C.c_int64(in_features), C.c_int64(out_features),
-                            C.c_int64(ldx), C.c_int64(ldy), C.c_int(in_dtype), _ptr(dW), C.c_int64(lddw), C.c_int(int(accumulate)),
+    _check(lib.hap_sfb_grad(m, xp, yp, (C.c_int64 * m)(*map(int, rows)), in_features, out_features,
+                            ldx, ldy, in_dtype, _ptr(dW), lddw, int(accumulate),
                             wp, wb, _stream(stream)), "hap_sfb_grad")
 
 
@@ -391,8 +399,8 @@ def hap_sfb_grad_static(Xs, dYs, rows, in_features, out_features, ldx, ldy, in_d
     m = len(rows)
     xp = (C.c_void_p * m)(*[_ptr(t) for t in Xs])
     yp = (C.c_void_p * m)(*[_ptr(t) for t in dYs])
-    _check(lib.hap_sfb_grad_static(C.c_int(m), xp, yp, (C.c_int64 * m)(*map(int, rows)), C.c_int64(in_features), C.c_int64(out_features),
-                                   C.c_int64(ldx), C.c_int64(ldy), C.c_int(in_dtype), _ptr(dW), C.c_int64(lddw), C.c_int(int(accumulate)),
+    _check(lib.hap_sfb_grad_static(m, xp, yp, (C.c_int64 * m)(*map(int, rows)), in_features, out_features,
+                                   ldx, ldy, in_dtype, _ptr(dW), lddw, int(accumulate),
                                    _stream(stream)), "hap_sfb_grad_static")
 
 
@@ -410,20 +418,20 @@ def hap_moe_linear_bwd_workspace(desc: MoeDesc, shard_index: int) -> int:
 
 def hap_moe_linear_fwd(desc: MoeDesc, shard_index, X, W, bias, rows, Y, preact=None, ws=None, stream=None):
     wp, wb = _ws(ws)
-    _check(lib.hap_moe_linear_fwd(C.byref(desc.c), C.c_int(shard_index), _ptr(X), _ptr(W), _ptr(bias), _ptr(rows), _ptr(Y),
+    _check(lib.hap_moe_linear_fwd(C.byref(desc.c), shard_index, _ptr(X), _ptr(W), _ptr(bias), _ptr(rows), _ptr(Y),
                                   _ptr(preact), wp, wb, _stream(stream)), "hap_moe_linear_fwd")
 
 
 def hap_moe_linear_bwd(desc: MoeDesc, shard_index, X, W, preact, dY, rows, dX, dW, dW_dtype, dbias, ws=None, stream=None):
     wp, wb = _ws(ws)
-    _check(lib.hap_moe_linear_bwd(C.byref(desc.c), C.c_int(shard_index), _ptr(X), _ptr(W), _ptr(preact), _ptr(dY), _ptr(rows),
-                                  _ptr(dX), _ptr(dW), C.c_int(dW_dtype), _ptr(dbias), wp, wb, _stream(stream)), "hap_moe_linear_bwd")
+    _check(lib.hap_moe_linear_bwd(C.byref(desc.c), shard_index, _ptr(X), _ptr(W), _ptr(preact), _ptr(dY), _ptr(rows),
+                                  _ptr(dX), _ptr(dW), dW_dtype, _ptr(dbias), wp, wb, _stream(stream)), "hap_moe_linear_bwd")
 
 
 def hap_moe_linear_bwd_dact(desc: MoeDesc, shard_index, X, W, preact, dY, rows, dX, dW, dW_dtype, dbias, x_preact, x_act, ws=None, stream=None):
     wp, wb = _ws(ws)
-    _check(lib.hap_moe_linear_bwd_dact(C.byref(desc.c), C.c_int(shard_index), _ptr(X), _ptr(W), _ptr(preact), _ptr(dY), _ptr(rows),
-                                       _ptr(dX), _ptr(dW), C.c_int(dW_dtype), _ptr(dbias), _ptr(x_preact), C.c_int(x_act), wp, wb,
+    _check(lib.hap_moe_linear_bwd_dact(C.byref(desc.c), shard_index, _ptr(X), _ptr(W), _ptr(preact), _ptr(dY), _ptr(rows),
+                                       _ptr(dX), _ptr(dW), dW_dtype, _ptr(dbias), _ptr(x_preact), x_act, wp, wb,
                                        _stream(stream)), "hap_moe_linear_bwd_dact")
 
 
@@ -432,21 +440,21 @@ def hap_allgather_capacity(desc: GatherDesc) -> int:
 
 
 def hap_allgather_pad(desc: GatherDesc, shard_index, shard, ld_shard, slot, ld_slot, stream=None):
-    _check(lib.hap_allgather_pad(C.byref(desc.c), C.c_int(shard_index), _ptr(shard), C.c_int64(ld_shard), _ptr(slot), C.c_int64(ld_slot),
+    _check(lib.hap_allgather_pad(C.byref(desc.c), shard_index, _ptr(shard), ld_shard, _ptr(slot), ld_slot,
                                  _stream(stream)), "hap_allgather_pad")
 
 
 def hap_allgather_assemble(desc: GatherDesc, pieces, ld_pieces, out, ld_out, stream=None):
     m = desc.m
     pp = (C.c_void_p * m)(*[_ptr(t) for t in pieces])
-    _check(lib.hap_allgather_assemble(C.byref(desc.c), pp, (C.c_int64 * m)(*map(int, ld_pieces)), _ptr(out), C.c_int64(ld_out),
+    _check(lib.hap_allgather_assemble(C.byref(desc.c), pp, (C.c_int64 * m)(*map(int, ld_pieces)), _ptr(out), ld_out,
                                       _stream(stream)), "hap_allgather_assemble")
 
 
 def hap_reducescatter_split(desc: GatherDesc, full, ld_full, slots, ld_slots, stream=None):
     m = desc.m
     pp = (C.c_void_p * m)(*[_ptr(t) for t in slots])
-    _check(lib.hap_reducescatter_split(C.byref(desc.c), _ptr(full), C.c_int64(ld_full), pp, (C.c_int64 * m)(*map(int, ld_slots)),
+    _check(lib.hap_reducescatter_split(C.byref(desc.c), _ptr(full), ld_full, pp, (C.c_int64 * m)(*map(int, ld_slots)),
                                        _stream(stream)), "hap_reducescatter_split")
 
 
@@ -456,18 +464,18 @@ def hap_attn_bwd_workspace(desc: AttnDesc, shard_index: int) -> int:
 
 def hap_sharded_attn_fwd(desc: AttnDesc, shard_index, Q, K, V, O, lse, ws=None, stream=None):
     wp, wb = _ws(ws)
-    _check(lib.hap_sharded_attn_fwd(C.byref(desc.c), C.c_int(shard_index), _ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(lse),
+    _check(lib.hap_sharded_attn_fwd(C.byref(desc.c), shard_index, _ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(lse),
                                     wp, wb, _stream(stream)), "hap_sharded_attn_fwd")
 
 
 def hap_sharded_attn_bwd(desc: AttnDesc, shard_index, Q, K, V, O, lse, dO, dQ, dK, dV, ws=None, stream=None):
     wp, wb = _ws(ws)
-    _check(lib.hap_sharded_attn_bwd(C.byref(desc.c), C.c_int(shard_index), _ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(lse),
+    _check(lib.hap_sharded_attn_bwd(C.byref(desc.c), shard_index, _ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(lse),
                                     _ptr(dO), _ptr(dQ), _ptr(dK), _ptr(dV), wp, wb, _stream(stream)), "hap_sharded_attn_bwd")
 
 
 def hap_layernorm_fwd(rows, n, io_dtype, x, gamma, beta, y, mean, rstd, stream=None):
-    _check(lib.hap_layernorm_fwd(C.c_int64(rows), C.c_int64(n), C.c_int(io_dtype), _ptr(x), _ptr(gamma), _ptr(beta), _ptr(y),
+    _check(lib.hap_layernorm_fwd(rows, n, io_dtype, _ptr(x), _ptr(gamma), _ptr(beta), _ptr(y),
                                  _ptr(mean), _ptr(rstd), _stream(stream)), "hap_layernorm_fwd")
 
 
@@ -477,18 +485,18 @@ def hap_layernorm_bwd_workspace(rows, n) -> int:
 
 def hap_layernorm_bwd(rows, n, io_dtype, x, gamma, mean, rstd, dy, dx, dgamma, dbeta, ws, stream=None, dresidual=None):
     wp, wb = _ws(ws)
-    _check(lib.hap_layernorm_bwd(C.c_int64(rows), C.c_int64(n), C.c_int(io_dtype), _ptr(x), _ptr(gamma), _ptr(mean), _ptr(rstd),
+    _check(lib.hap_layernorm_bwd(rows, n, io_dtype, _ptr(x), _ptr(gamma), _ptr(mean), _ptr(rstd),
                                  _ptr(dy), _ptr(dresidual), _ptr(dx), _ptr(dgamma), _ptr(dbeta), wp, wb, _stream(stream)), "hap_layernorm_bwd")
 
 
 def hap_gelu_bwd(rows, cols, io_dtype, preact, ldp, dy, lddy, out, ldo, stream=None):
-    _check(lib.hap_gelu_bwd(C.c_int64(rows), C.c_int64(cols), C.c_int(io_dtype), _ptr(preact), C.c_int64(ldp), _ptr(dy),
-                            C.c_int64(lddy), _ptr(out), C.c_int64(ldo), _stream(stream)), "hap_gelu_bwd")
+    _check(lib.hap_gelu_bwd(rows, cols, io_dtype, _ptr(preact), ldp, _ptr(dy),
+                            lddy, _ptr(out), ldo, _stream(stream)), "hap_gelu_bwd")
 
 
 def hap_add(rows, cols, io_dtype, a, lda, b, ldb, bias, out, ldo, stream=None):
-    _check(lib.hap_add(C.c_int64(rows), C.c_int64(cols), C.c_int(io_dtype), _ptr(a), C.c_int64(lda), _ptr(b), C.c_int64(ldb),
-                       _ptr(bias), _ptr(out), C.c_int64(ldo), _stream(stream)), "hap_add")
+    _check(lib.hap_add(rows, cols, io_dtype, _ptr(a), lda, _ptr(b), ldb,
+                       _ptr(bias), _ptr(out), ldo, _stream(stream)), "hap_add")
 
 
 def hap_colsum_workspace(rows, cols) -> int:
@@ -497,7 +505,7 @@ def hap_colsum_workspace(rows, cols) -> int:
 
 def hap_colsum(rows, cols, io_dtype, a, lda, out, ws, stream=None):
     wp, wb = _ws(ws)
-    _check(lib.hap_colsum(C.c_int64(rows), C.c_int64(cols), C.c_int(io_dtype), _ptr(a), C.c_int64(lda), _ptr(out), wp, wb,
+    _check(lib.hap_colsum(rows, cols, io_dtype, _ptr(a), lda, _ptr(out), wp, wb,
                           _stream(stream)), "hap_colsum")
 
 
