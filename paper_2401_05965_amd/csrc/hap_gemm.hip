@@ -20,7 +20,8 @@
  * Kernels.  gemm_pp_kernel: bf16, 256 x 256 tiles, two wave groups that alternate a memory phase and a matrix phase over a
  * 4-stage ring of direct-to-LDS K tiles (all layouts but "both operands K-contiguous").  gemm_dma_kernel: bf16, two-stage ring,
  * 256 x 256 (both operands K-contiguous) and 128 x 128 (small outputs, remainder strips).  gemm_kpair_kernel: bf16, 128 x 128, at
- * most one tile per compute unit, two wave groups that split the tile's contraction.  gemm_kernel: register-staged, fp32
+ * most one tile per compute unit, two wave groups that split the tile's contraction.  gemm_small_kernel: bf16, 32 x 64 and 64 x 64, the
+ * smallest outputs, eight waves that split the contraction.  gemm_kernel: register-staged, fp32
  * and what the direct kernels cannot address.  gemm_skinny_f32_kernel: fp32 products of few rows, contraction split over
  * the waves of a workgroup.  gemm_rank_f32_kernel: fp32 products over few k of two M-/N-contiguous operands; linear_bwd_f32_kernel:
  * both in one launch.  gemm_generic_kernel: scalar fallback.  Epilogues: bias, GeLU, pre-activation copy, fp32
@@ -371,11 +372,33 @@ struct Plan {
   int bk;           // K step of the kernel that will run (the K-tile counts handed to it are in this unit)
   int dma;          // 1: bf16, direct-to-LDS kernel; 0: fp32, register-staged kernel
   bool pingpong;    // 256 x 256 tiles run by gemm_pp_kernel
+  bool small;       // BM x 64 tiles run by gemm_small_kernel
 };
+
+/* Rows of the tiles with which gemm_small_kernel takes a bf16 product (32 or 64), 0 where it does not: at most one tile per compute unit
+ * (a workgroup's rings fill its LDS), of 32 rows where there are compute units for that, over contractions that a wave's eighth of does
+ * not take longer than the split over workgroups that the other kernels make.  Microseconds, what ran before -> this kernel:
+ *   tiles of 32, forward:  197 x 1024 x 1260 13.6 -> 6.7    512 x 512 x 512 9.9 -> 5.6    400 x 1024 x 1024 12.2 -> 7.0 (208 tiles)
+ *   tiles of 64:  forward 1024 x 1024 x 1024 12.4 -> 9.0, with GeLU 17.1 -> 10.7    bwd-weight 768 x 768 over 1500 rows 15.3 -> 8.9
+ *   beyond 256 tiles of 64:  1500 x 768 x 768 11.5 -> 13.6 (288)    2000 x 640 x 1024 11.1 -> 14.4
+ *   long contractions:  256 tiles of 64 over K = 3000 / 3940 / 4096 / 8192: 19.0 -> 14.8 / 20.1 -> 18.3 / 20.3 -> 21.1 / 26.4 -> 32.0; with half of the
+ *   compute units or fewer 64 x 1024 over 4096 14.2 -> 11.1, 512 x 512 over 4096 17.1 -> 11.3 and 8192 19.9 -> 26.3 (64 x 512: 16.3 -> 17.0) */
+int small_rows(const hap_gemm_problem* p, const Plan& pl) {
+  if (p->in_dtype != HAP_BF16 || p->tile == 256 || (!p->a_kcontig && p->b_kcontig)) return 0;
+  const long long cus = cu_count(), groups = p->groups > 1 ? p->groups : 1;
+  long long steps = 0;
+  for (int s = 0; s < p->nseg; ++s) steps += p->k[s] > 0 ? (pl.skewK + p->k[s] + 31) / 32 : 0;
+  const long long columns = groups * ((p->N + pl.skewN + 63) / 64);
+  for (int bm = p->a_kcontig ? 32 : 64; bm <= 64; bm *= 2) {      // (an M-contiguous operand's LDS rows are 128 bytes or more)
+    const long long tiles = columns * ((p->M + pl.skewM + bm - 1) / bm);
+    if (tiles <= cus) return steps <= (tiles * 2 > cus ? 124 : 160) ? bm : 0;
+  }
+  return 0;
+}
 
 /* Decides whether the aligned-chunk kernel can address the operands and with which skews. */
 Plan make_plan(const hap_gemm_problem* p) {
-  Plan pl = {false, 0, 0, 0, 0, 0, 64, 0, false};
+  Plan pl = {false, 0, 0, 0, 0, 0, 64, 0, false, false};
   if (p->force_generic) return pl;
   const int es = esize(p->in_dtype);
   if ((p->lda * es) % 16 || (p->ldb * es) % 16) return pl;
@@ -428,7 +451,11 @@ Plan make_plan(const hap_gemm_problem* p) {
   }
   pl.tiled = true;
   if (p->in_dtype == HAP_F32) pl.bm = pl.bn = 64;
-  else {
+  else if (const int rows = small_rows(p, pl)) {
+    pl.bm = rows; pl.bn = 64; pl.bk = 32;
+    pl.dma = 1;
+    pl.small = true;
+  } else {
     bool big = p->tile ? p->tile == 256 : (p->M + pl.skewM > 128 && p->N + pl.skewN > 128);
     if (big && !p->tile && (p->groups > 1 || p->group_len)) {
       const int kCUs = cu_count();
@@ -481,6 +508,7 @@ int dispatch_tile(const hap_gemm_problem* p, const Plan& pl, const GemmArgs& a, 
   if constexpr (sizeof(T) == 4) {
     return dispatch_layout<T, TC, 64, 64, 64, 2, 2>(p, a, groups, st);
   } else {
+    if (pl.small) return run_small(p, a, pl.bm, groups, st);
     return pl.pingpong ? run_pp(p, a, groups, st) : run_dma(p, a, pl.bm, groups, st);
   }
 }
@@ -584,7 +612,10 @@ hap_gemm_problem sub_problem(const hap_gemm_problem* p, int64_t m_lo, int64_t m_
 static int64_t g_view_limit = kViewLimitBytes;
 static int64_t g_cut_products = 0;      // products run in pieces so far (testing aid, not synchronised)
 
-static int64_t g_kpair_products = 0;    // products handed to gemm_kpair_kernel so far (testing aid)
+static int64_t g_kpair_products = 0;    // products so far for which kpair_applies() holds (testing aid)
+static int64_t g_small_products = 0;    // products handed to gemm_small_kernel so far (testing aid)
+
+extern "C" int64_t hap_debug_small_products(void) { return __atomic_load_n(&g_small_products, __ATOMIC_RELAXED); }
 
 extern "C" int64_t hap_debug_kpair_products(void) { return __atomic_load_n(&g_kpair_products, __ATOMIC_RELAXED); }
 
@@ -949,7 +980,14 @@ int hap_gemm_run(const hap_gemm_problem* p, void* stream) {
     const int kCUs = cu_count();
     const long long slots = pl.bm == 256 ? kCUs : (pl.bm == 128 ? 2 * kCUs : 4 * kCUs);
     const int min_tiles = pl.bm == 64 ? 2 : 4 * (64 / pl.bk);      // in K steps of the chosen kernel
-    a.ksplit = (int)workgroup_splits(p, out_tiles, slots, a.ntiles, min_tiles, (size_t)pl.bm * pl.bn * sizeof(float));
+    a.ksplit = pl.small ? 1 : (int)workgroup_splits(p, out_tiles, slots, a.ntiles, min_tiles, (size_t)pl.bm * pl.bn * sizeof(float));
+    if (pl.small) {
+      __atomic_fetch_add(&g_small_products, 1, __ATOMIC_RELAXED);
+      const long long tiles128 = cdiv(p->M + pl.skewM, 128) * cdiv(p->N + pl.skewN, 128) * groups;
+      long long nk = 0;
+      for (int s = 0; s < p->nseg; ++s) nk += p->k[s] > 0 ? cdiv(pl.skewK + p->k[s], 64) : 0;
+      if (kpair_applies(p, tiles128, nk)) __atomic_fetch_add(&g_kpair_products, 1, __ATOMIC_RELAXED);
+    }
     if (pl.dma && pl.bm == 128 && kpair_applies(p, out_tiles, a.ntiles)) {
       double us;
       a.kpair = 1;

@@ -336,10 +336,10 @@ struct FragReader {
       const int r = lane & 31, h = lane >> 5;
       at[0] = (unsigned)((wave_mn + r) * ROWB + ((h ^ swz<true, CPR>(r, 0)) << 4));
     } else {
-      static_assert(CPR >= 16, "M/N-contiguous fragment addressing assumes rows of 256 bytes or more");
+      static_assert(CPR >= 8, "M/N-contiguous fragment addressing assumes rows of 128 bytes or more");
       const int g = lane >> 4, i = lane & 15;
       const int x = i >> 2, cl = (g & 1) * 2 + ((i & 3) >> 1);
-      const unsigned lc = (unsigned)(((g >> 1) * 8 + x) * ROWB + (x << 6) + (cl << 4) + (i & 1) * 8);
+      const unsigned lc = (unsigned)(((g >> 1) * 8 + x) * ROWB) + ((unsigned)((x << (CPR >= 16 ? 6 : 5)) ^ (cl << 4)) | (unsigned)(i & 1) * 8u);
 #pragma unroll
       for (int b = 0; b < NBLK; ++b) at[b] = lc ^ (unsigned)(((wave_mn >> 5) + b) << 6);
     }
@@ -1525,6 +1525,185 @@ __global__ __launch_bounds__(512) void gemm_kpair_kernel(const GemmArgs args) {
   epilogue_transposed<T, TC, 1, TN>(group_outputs(args, gv, bp.grp), sum, m0 + wm, n0 + wn0, lane, patch);
 }
 
+/* Stores four consecutive columns n .. n + 3 of output row m (n may precede the first column or run past the last one) as the one-pass
+ * epilogues would: bias, pre-activation copy, activation or activation backward, accumulation, conversion. */
+template <typename T, typename TC>
+__device__ __forceinline__ void store_quad(const GemmArgs& args, int m, int n, const float (&sum)[4]) {
+  typedef TC quad_t __attribute__((ext_vector_type(4)));
+  TC* const C = static_cast<TC*>(args.c) + (long long)m * args.ldc + n;
+  TC* const P = args.preact ? static_cast<TC*>(args.preact) + (long long)m * args.ldp + n : nullptr;
+  const T* const bias = args.bias ? static_cast<const T*>(args.bias) + n : nullptr;
+  const TC* const dpre = args.dact_preact ? static_cast<const TC*>(args.dact_preact) + (long long)m * args.ldd + n : nullptr;
+  // whole quads: one access per tensor where their addresses allow it
+  constexpr uintptr_t MASK = 4 * sizeof(TC) - 1;
+  if (n >= 0 && n + 4 <= args.N && (((uintptr_t)C | (uintptr_t)P | (uintptr_t)dpre) & MASK) == 0) {
+    quad_t d, old, pre, out;
+    if (dpre) d = *reinterpret_cast<const quad_t*>(dpre);
+    if (args.accumulate) old = *reinterpret_cast<const quad_t*>(C);
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+      float v = sum[x];
+      if (bias) v += load_s<T>(bias + x);
+      pre[x] = (TC)v;
+      if (args.act == HAP_ACT_GELU_ERF) v = gelu_erf((float)(TC)v);     // the activation sees the value as stored
+      if (dpre) v *= gelu_erf_grad((float)d[x]);
+      if (args.accumulate) v += (float)old[x];
+      out[x] = (TC)v;
+    }
+    if (P) *reinterpret_cast<quad_t*>(P) = pre;
+    *reinterpret_cast<quad_t*>(C) = out;
+    return;
+  }
+#pragma unroll
+  for (int x = 0; x < 4; ++x) {
+    if (n + x < 0 || n + x >= args.N) continue;
+    float v = sum[x];
+    if (bias) v += load_s<T>(bias + x);
+    if (P) store_c<TC>(P + x, v);
+    if (args.act == HAP_ACT_GELU_ERF) v = gelu_erf((float)(TC)v);
+    if (dpre) v *= gelu_erf_grad(load_s<TC>(dpre + x));
+    if (args.accumulate) v += load_s<TC>(C + x);
+    store_c<TC>(C + x, v);
+  }
+}
+
+/* ---------------------------------------------------------------------------------------------
+ * bf16 kernel for the smallest outputs: eight waves share one BM x 64 tile, each contracts an eighth of K with a ring of its own.
+ *
+ * Bound: latency.  A product of a few hundred rows has a few dozen 128-tiles; spread over the chip by splitting K over workgroups it
+ * pays for fp32 partial tiles and a dependent reduction launch, longer together than the product.  Tiles of 32 or 64 rows give the chip
+ * enough workgroups without one, and with the contraction cut in eight a wave's share is a handful of steps, most of whose loads are in
+ * flight at once.  The rings are private to the waves, so nothing waits at a barrier before the partial sums meet in LDS.
+ * ------------------------------------------------------------------------------------------- */
+template <int BM> constexpr int kSmallStages = BM == 32 ? 3 : 2;
+template <int BM> constexpr int kSmallLds = 8 * kSmallStages<BM> * (BM + 64) * 32 * 2;
+
+template <typename TC, bool AKC, bool BKC, int BM>
+__global__ __launch_bounds__(512) void gemm_small_kernel(const GemmArgs args) {
+  typedef __bf16 T;
+  constexpr int BN = 64, BK = 32, NW = 8, STAGES = kSmallStages<BM>, KK = BK / 16;
+  constexpr int TM = BM / 32, TN = BN / 32;
+  constexpr int A_BYTES = BM * BK * 2, STAGE_BYTES = A_BYTES + BN * BK * 2;
+  typedef DmaLoader<AKC, BM, BK, 64> LA;
+  typedef DmaLoader<BKC, BN, BK, 64> LB;
+  constexpr int LPT = LA::CPT + LB::CPT;
+  static_assert(STAGES * STAGE_BYTES >= TM * TN * 16 * 64 * 4, "a wave's ring holds its partial sums");
+
+  extern __shared__ __attribute__((aligned(1024))) char smem_all[];
+  const int lane = threadIdx.x & 63, wave = uni((int)threadIdx.x >> 6);
+  char* const smem = smem_all + wave * (STAGES * STAGE_BYTES);
+  const BlockPos bp = block_pos(args);
+  const int m0 = bp.tm * BM, n0 = bp.tn * BN;
+  const GroupView gv = group_view(args, bp.grp);
+  const int m_lim = args.skewM + gv.M, n_lim = args.skewN + args.N;
+  if (args.ragged == 1 && (gv.M == 0 || m0 >= m_lim)) return;
+  const int all_tiles = gv.k >= 0 ? (args.skewK + gv.k + BK - 1 >= BK ? (args.skewK + gv.k + BK - 1) / BK : 1) : args.ntiles;
+
+  LA la; LB lb;
+  la.init(lane, m0, AKC ? args.skewM : 0, m_lim, args.lda);
+  lb.init(lane, n0, BKC ? args.skewN : 0, n_lim, args.ldb);
+  PinnedFrag<AKC, BM, BK, TM, 1> fra;
+  PinnedFrag<BKC, BN, BK, TN, 1> frb;
+  fra.init(lane, 0, lds_addr(smem));
+  frb.init(lane, 0, lds_addr(smem));
+
+  f32x16_t acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
+
+  // this wave's range of the K tiles of all segments laid end to end
+  const int first = (int)((long long)all_tiles * wave / NW), ntiles = (int)((long long)all_tiles * (wave + 1) / NW) - first;
+  int seg0 = 0, skip = first;
+  while (seg0 + 1 < args.nseg) {
+    const int in_seg = (args.skewK + args.seg[seg0].k + BK - 1) / BK;
+    if (skip < in_seg) break;
+    skip -= in_seg;
+    seg0 = uni(seg0 + 1);
+  }
+  int pseg = seg0, pk0 = skip * BK, pkend = uni(args.skewK + (gv.k >= 0 ? gv.k : args.seg[seg0].k)), issued = 0;
+  __amdgpu_buffer_rsrc_t ra = make_rsrc(static_cast<const char*>(args.seg[seg0].a) + gv.oa, args.seg[seg0].a_bytes);
+  __amdgpu_buffer_rsrc_t rb = make_rsrc(static_cast<const char*>(args.seg[seg0].b) + gv.ob, args.seg[seg0].b_bytes);
+  int lseg = seg0, lk0 = pk0, lkend = pkend;
+  auto request = [&](auto slot_tag) {
+    constexpr int SLOT = decltype(slot_tag)::value;
+    char* const pa = smem + SLOT * STAGE_BYTES;
+    const unsigned soa = LA::tile_offset(pk0, args.skewK, args.lda), sob = LB::tile_offset(pk0, args.skewK, args.ldb);
+    la.issue_edge(ra, pa, lane, soa, pk0, args.skewK, pkend);
+    lb.issue_edge(rb, pa + A_BYTES, lane, sob, pk0, args.skewK, pkend);
+    pk0 += BK;
+    ++issued;
+    if (pk0 >= pkend && pseg + 1 < args.nseg) {
+      pseg = uni(pseg + 1);
+      pk0 = 0;
+      pkend = uni(args.skewK + args.seg[pseg].k);
+      ra = make_rsrc(static_cast<const char*>(args.seg[pseg].a) + gv.oa, args.seg[pseg].a_bytes);
+      rb = make_rsrc(static_cast<const char*>(args.seg[pseg].b) + gv.ob, args.seg[pseg].b_bytes);
+    }
+  };
+  static_for<STAGES>([&](auto s) { if (s < ntiles) request(s); });
+  auto tile = [&](auto slot_tag, int u) __attribute__((always_inline)) {
+    constexpr int SLOT = decltype(slot_tag)::value;
+    const int newer = issued - (u + 1);              // tiles requested after this one: their loads may stay in flight
+    if (newer >= 2) wait_vmcnt<2 * LPT>();
+    else if (newer == 1) wait_vmcnt<LPT>();
+    else wait_vmcnt<0>();
+    if (lk0 < args.skewK || lk0 + BK > lkend) {      // zero the k elements outside the segment
+      char* const sa = smem + SLOT * STAGE_BYTES;
+      la.fixup(sa, lane, lk0, args.skewK, lkend);
+      lb.fixup(sa + A_BYTES, lane, lk0, args.skewK, lkend);
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    }
+    lk0 += BK;
+    if (lk0 >= lkend && lseg + 1 < args.nseg) { lseg = uni(lseg + 1); lk0 = 0; lkend = uni(args.skewK + args.seg[lseg].k); }
+    bf16x8_t fa[KK][TM], fb[KK][TN];
+    static_for<KK>([&](auto kk) {
+      static_for<TN>([&](auto j) { fb[kk][j] = frb.template read<SLOT * STAGE_BYTES + A_BYTES, j, kk>(); });
+      static_for<TM>([&](auto i) { fa[kk][i] = fra.template read<SLOT * STAGE_BYTES, i, kk>(); });
+    });
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    if (issued < ntiles) request(slot_tag);
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk)
+#pragma unroll
+      for (int x = 0; x < TM * TN; ++x) acc[x / TN][x % TN] = mfma(fb[kk][x % TN], fa[kk][x / TN], acc[x / TN][x % TN]);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  for (int u0 = 0; u0 < ntiles; u0 += STAGES)
+    static_for<STAGES>([&](auto s) { if (u0 + s < ntiles) tile(s, u0 + s); });
+
+  // the partial sums meet: register quad by register quad, 64 lanes next to each other, each wave's in its own ring
+  typedef float f32x4 __attribute__((ext_vector_type(4)));
+  f32x4* const mine = reinterpret_cast<f32x4*>(smem);
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        f32x4 v;
+#pragma unroll
+        for (int x = 0; x < 4; ++x) v[x] = acc[i][j][q * 4 + x];
+        mine[((i * TN + j) * 4 + q) * 64 + lane] = v;
+      }
+  __syncthreads();
+  const GemmArgs out = group_outputs(args, gv, bp.grp);
+#pragma unroll
+  for (int b = 0; b < TM * TN * 4 / NW; ++b) {
+    const int at = b * NW + wave, i = at / (TN * 4), j = at / 4 % TN, q = at % 4;
+    f32x4 t = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int w = 0; w < NW; ++w) t += reinterpret_cast<const f32x4*>(smem_all + w * (STAGES * STAGE_BYTES))[at * 64 + lane];
+    const int m = m0 + i * 32 + (lane & 31) - args.skewM, n = n0 + j * 32 + q * 8 + (lane >> 5) * 4 - args.skewN;
+    const float v[4] = {t[0], t[1], t[2], t[3]};
+    if (m >= 0 && m < out.M && n < out.N && n + 4 > 0) store_quad<T, TC>(out, m, n, v);
+  }
+}
+
 /* Split-K reduction: sums the ksplit fp32 partial tiles of every output tile and applies what the
  * one-pass epilogue would have (bias, pre-activation copy, activation, accumulation, conversion),
  * storing only the logical rows / columns.  One thread per 4 consecutive columns. */
@@ -1545,22 +1724,8 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const GemmArgs args_
   f32x4_t sum = {0.0f, 0.0f, 0.0f, 0.0f};
   const float* p = args.partial + ((long long)blockIdx.y * out_tiles + tile) * args.ksplit * (BM * BN) + r * BN + c4;
   for (int s = 0; s < args.ksplit; ++s) sum += *reinterpret_cast<const f32x4_t*>(p + (long long)s * (BM * BN));
-  TC* C = static_cast<TC*>(args.c);
-  TC* P = static_cast<TC*>(args.preact);
-  const T* bias = static_cast<const T*>(args.bias);
-#pragma unroll
-  for (int x = 0; x < 4; ++x) {
-    const int nn = n + x;
-    if (nn < 0 || nn >= args.N) continue;
-    float v = sum[x];
-    if (bias) v += load_s<T>(bias + nn);
-    if (P) store_c<TC>(P + (long long)m * args.ldp + nn, v);
-    if (args.act == HAP_ACT_GELU_ERF) v = gelu_erf((float)(TC)v);     // the activation sees the value as stored
-    if (args.dact_preact) v *= gelu_erf_grad(load_s<TC>(static_cast<const TC*>(args.dact_preact) + (long long)m * args.ldd + nn));
-    TC* dst = C + (long long)m * args.ldc + nn;
-    if (args.accumulate) v += load_s<TC>(dst);
-    store_c<TC>(dst, v);
-  }
+  const float v[4] = {sum[0], sum[1], sum[2], sum[3]};
+  store_quad<T, TC>(args, m, n, v);
 }
 
 /* ------------------------------------------------------------------------------------------- launching */
@@ -1580,7 +1745,7 @@ int launch_splitk_reduce(const GemmArgs& a, int groups, hipStream_t st) {
 
 /* Launches one of the direct-to-LDS kernels with `smem` bytes of LDS, and the reduction behind it when K is split.  `configured`
  * belongs to the kernel: the LDS attribute has to be set on the kernel's copy on every device (benign race: idempotent). */
-template <typename TC, int BM, int BN>
+template <typename TC, int BM, int BN, bool SPLITS = true>
 int launch_lds_kernel(void (*kernel)(const GemmArgs), bool (&configured)[64], size_t smem, int threads, const GemmArgs& a, int groups, hipStream_t st) {
   int device = 0;
   if (hipGetDevice(&device) != hipSuccess || device < 0 || device >= 64) device = -1;
@@ -1592,11 +1757,13 @@ int launch_lds_kernel(void (*kernel)(const GemmArgs), bool (&configured)[64], si
   hipLaunchKernelGGL(kernel, dim3(a.tiles_m * a.tiles_n * a.ksplit, groups), dim3(threads), smem, st, a);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hap_fail(HAP_EDEVICE, "gemm launch: %s", hipGetErrorString(e));
-  return a.ksplit > 1 ? launch_splitk_reduce<__bf16, TC, BM, BN>(a, groups, st) : HAP_OK;
+  if constexpr (SPLITS) return a.ksplit > 1 ? launch_splitk_reduce<__bf16, TC, BM, BN>(a, groups, st) : HAP_OK;
+  return HAP_OK;
 }
 
 /* Defined in the translation unit that instantiates the kernels in question. */
 int run_pp(const hap_gemm_problem* p, const GemmArgs& a, int groups, hipStream_t st);             // hap_gemm_pp.hip: gemm_pp_kernel, 256 x 256
+int run_small(const hap_gemm_problem* p, const GemmArgs& a, int bm, int groups, hipStream_t st);
 int run_dma(const hap_gemm_problem* p, const GemmArgs& a, int tile, int groups, hipStream_t st);  // hap_gemm_dma.hip: gemm_dma_kernel of 128- or
                                                                                                   // 256-tiles, gemm_kpair_kernel
 

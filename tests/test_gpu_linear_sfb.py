@@ -247,6 +247,43 @@ def test_linear_few_tiles_share_their_contraction_between_wave_groups(hap, k):
     reached(2, 130, 136, 1000, 1, [0, k, 1000], act=True, bias=True)
 
 
+@pytest.mark.parametrize("k", [193, 320, 449])
+def test_linear_paired_wave_groups_beyond_the_smallest_outputs(hap, k):
+    """The same ranges for outputs of more than 256 tiles of 64 x 64, which the kernel of the smallest outputs leaves to the paired wave
+    groups: per call the forward contracts k or 1000 - k features, bwd-data as many columns, bwd-weight as many rows."""
+    for mode, args in [(2, (1300, 1000, 1016)), (1, (1300, 1016, 1000)), (0, (1000, 1304, 1016))]:
+        before = hap.hap_debug_kpair_products() - hap.hap_debug_small_products()
+        run_linear_case(hap, "bf16", *args, mode, [0, k, 1000], act=False, bias=mode == 1, full=True)
+        assert hap.hap_debug_kpair_products() - hap.hap_debug_small_products() - before >= 2, (mode, k)
+
+
+@pytest.mark.parametrize("tokens,in_f,out_f", [(1, 40, 24), (31, 72, 64), (33, 520, 65), (64, 32, 200), (65, 1000, 63), (197, 1024, 315), (250, 248, 1001), (450, 130, 1030), (1000, 3900, 260)])
+def test_linear_smallest_outputs(hap, tokens, in_f, out_f):
+    """Outputs of at most 256 tiles of 32 x 64 or 64 x 64 around the tiles' edges, over contractions from less than one K step of 32 (waves
+    without any) to sixteen per wave, from whole tensors at odd columns and rows and from compact slices."""
+    for mode, dim in [(0, tokens), (1, out_f), (2, in_f)]:
+        before = hap.hap_debug_small_products()
+        run_linear_case(hap, "bf16", tokens, in_f, out_f, mode, [0, dim // 3, dim], act=mode != 2, bias=True, full=True)
+        if in_f % 8 == 0 and out_f % 8 == 0:      # (other pitches are not on the 16-byte grid: the scalar kernel)
+            assert hap.hap_debug_small_products() - before >= 4, mode
+    run_linear_case(hap, "bf16", tokens, in_f + 7 & ~7, out_f + 7 & ~7, 3, [0, 1], act=True, bias=True, full=False, dw_dtype="f32")
+
+
+def test_linear_smallest_outputs_route(hap):
+    """One tile per compute unit is the most: 256 tiles of 32 x 64, then of 64 x 64, then another kernel; the contraction has its limits."""
+    torch = torch_mod()
+    assert hap.hap_device_info()[0] == 256
+    for tokens, in_f, out_f, want in [(512, 256, 1024, 1), (513, 256, 1024, 1), (1024, 256, 1024, 1), (1025, 256, 1024, 0), (1024, 3968, 1024, 1), (1024, 3976, 1024, 0),
+                                      (128, 5120, 64, 1), (128, 5128, 64, 0), (40, 8, 8, 1)]:
+        X, W, Y = empty((tokens, in_f), "bf16", 0), empty((in_f, out_f), "bf16", 0), empty((tokens, out_f), "bf16", 1)
+        X[:, 0] = 1; W[0] = 2
+        desc = hap.LinearDesc(tokens, in_f, out_f, hap.REPLICATED, [0, 1], hap.BF16, m=1)
+        before = hap.hap_debug_small_products()
+        hap.hap_sharded_linear_fwd(desc, 0, X, W, None, Y, None, empty((1 << 20,), "u8"))
+        assert hap.hap_debug_small_products() - before == want, (tokens, in_f, out_f)
+        assert (host(Y) == 2).all()
+
+
 @pytest.mark.parametrize("scratch", [True, False])
 @pytest.mark.parametrize("cut", [128, 333, 517])
 @pytest.mark.parametrize("tokens,out_f", [(130, 264), (1000, 1104), (140, 1600)])
