@@ -9,7 +9,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libhap.so")
-HIP_SOURCES = ["hap_gemm_pp.hip", "hap_gemm_dma.hip", "hap_gemm_small.hip", "hap_gemm.hip", "hap_ops.hip", "hap_linear.hip", "hap_moe.hip", "hap_gather.hip", "hap_attn.hip"]
+HIP_SOURCES = ["hap_gemm_pp.hip", "hap_gemm_dma.hip", "hap_gemm_small.hip", "hap_gemm_trio.hip", "hap_gemm.hip", "hap_ops.hip", "hap_linear.hip", "hap_moe.hip", "hap_gather.hip", "hap_attn.hip"]
 C_SOURCES = ["hap_host.c", "hap_synth.c"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 HIP_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",

@@ -19,7 +19,8 @@
  *
  * Kernels.  gemm_pp_kernel: bf16, 256 x 256 tiles, two wave groups that alternate a memory phase and a matrix phase over a
  * 4-stage ring of direct-to-LDS K tiles (all layouts but "both operands K-contiguous").  gemm_dma_kernel: bf16, two-stage ring,
- * 256 x 256 (both operands K-contiguous) and 128 x 128 (small outputs, remainder strips).  gemm_kpair_kernel: bf16, 128 x 128, at
+ * 256 x 256 (both operands K-contiguous) and 128 x 128 (small outputs, remainder strips).  gemm_trio_kernel: bf16, 128 x 128, three
+ * workgroups per compute unit, short contractions.  gemm_kpair_kernel: bf16, 128 x 128, at
  * most one tile per compute unit, two wave groups that split the tile's contraction.  gemm_small_kernel: bf16, 32 x 64 and 64 x 64, the
  * smallest outputs, eight waves that split the contraction.  gemm_kernel: register-staged, fp32
  * and what the direct kernels cannot address.  gemm_skinny_f32_kernel: fp32 products of few rows, contraction split over
@@ -262,17 +263,20 @@ __global__ __launch_bounds__(1024, 8) void linear_bwd_f32_kernel(const RankArgs 
   skinny_f32_tile<true, 1>(x, id % nx, id / nx, reinterpret_cast<float (*)[16][16]>(red));
 }
 
-/* Compute units of the current device (256 on MI355X), asked once per device; the planner's round arithmetic uses it. */
-int cu_count() {
+/* Compute units of the current device (256 on MI355X); the planner's round arithmetic uses it.  Asked once per device, the device once per
+ * product (each question costs a small product's call some hundredths of a microsecond): look_up_cu_count() on entry, for its thread. */
+static thread_local int t_cus = 256;
+static inline int cu_count() { return t_cus; }
+static void look_up_cu_count() {
   static int cached[64] = {};
   int device = 0;
-  if (hipGetDevice(&device) != hipSuccess || device < 0 || device >= 64) return 256;
+  if (hipGetDevice(&device) != hipSuccess || device < 0 || device >= 64) { t_cus = 256; return; }
   if (cached[device] == 0) {     // benign race: every thread stores the same value
     int n = 0;
     if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || n < 8) n = 256;
     cached[device] = n;
   }
-  return cached[device];
+  t_cus = cached[device];
 }
 
 /* 16-row blocks per workgroup with which gemm_skinny_f32_kernel takes the product: 1, 4 (all rows, at most 64), or 0 where it does not.
@@ -362,6 +366,14 @@ __global__ __launch_bounds__(256) void gemm_generic_kernel(const GenericArgs g) 
   if (g.accumulate) acc += load_s<TC>(dst);
   store_c<TC>(dst, acc);
 }
+
+inline long long cdiv(long long a, long long b) { return (a + b - 1) / b; }
+
+/* What the planner weighs the kernels by (below). */
+bool kpair_applies(const hap_gemm_problem* p, long long tiles, long long nk);
+int kpair_splits(const hap_gemm_problem* p, long long tiles, long long nk, double* us);
+double us_256(const hap_gemm_problem* p, long long n, long long nk);
+bool trio_applies(const hap_gemm_problem* p, long long n, long long nk, double* us);
 
 constexpr int kPingPongBK = 32;   // K step of the ping-pong kernel
 
@@ -458,15 +470,15 @@ Plan make_plan(const hap_gemm_problem* p) {
   } else {
     bool big = p->tile ? p->tile == 256 : (p->M + pl.skewM > 128 && p->N + pl.skewN > 128);
     if (big && !p->tile && (p->groups > 1 || p->group_len)) {
-      const int kCUs = cu_count();
-      // A grouped launch is not cut into strips: compare whole rounds of big tiles (one per CU, time 1 each) with rounds
-      // of small ones (two per CU, a quarter of the work each at lower efficiency: 0.6 per round, 0.3 when half empty).
+      // A grouped launch is not cut into strips: all tiles of all groups, big or small
       const long long g = p->groups > 1 ? p->groups : 1;
       const long long nb = g * ((p->M + pl.skewM + 255) / 256) * ((p->N + pl.skewN + 255) / 256);
       const long long ns = g * ((p->M + pl.skewM + 127) / 128) * ((p->N + pl.skewN + 127) / 128);
-      // few big tiles: split-K can spread them over the chip at about a third of a round for the partial-tile traffic
-      const double tb = nb * 2 <= kCUs ? 0.35 + 1.0 / (double)(kCUs / nb) : (double)((nb + kCUs - 1) / kCUs);
-      const double ts = ns <= kCUs ? 0.3 : 0.6 * (double)((ns + 2 * kCUs - 1) / (2 * kCUs));
+      const long long nk = (pl.skewK + p->k[0] + 63) / 64;
+      double ts;
+      trio_applies(p, ns, nk, &ts);
+      if (kpair_applies(p, ns, nk)) kpair_splits(p, ns, nk, &ts);
+      const double tb = us_256(p, nb, nk);
       big = tb <= ts;
     }
     pl.bm = pl.bn = big ? 256 : 128;
@@ -513,24 +525,6 @@ int dispatch_tile(const hap_gemm_problem* p, const Plan& pl, const GemmArgs& a, 
   }
 }
 
-}  // namespace hap_gemm_detail
-
-using namespace hap_gemm_detail;
-
-namespace {
-
-/* Relative time of n output tiles of 128x128 (one 256x256 tile on one CU = 1): a small tile does a
- * quarter of the work at lower efficiency, and two of them share a CU. */
-double small_tiles_time(long long n) {
-  if (n <= 0) return 0.0;
-  const int kCUs = cu_count();
-  // measured: a round of 512 small tiles takes 0.58 of a round of 256 big ones; a last round that leaves every CU at
-  // most one small tile 0.36 (the tile has the CU to itself)
-  const long long full = n / (2 * kCUs), rest = n % (2 * kCUs);
-  return 0.58 * (double)full + (rest == 0 ? 0.0 : (rest <= kCUs ? 0.36 : 0.58));
-}
-
-inline long long cdiv(long long a, long long b) { return (a + b - 1) / b; }
 
 /* Into how many workgroups the launcher splits the contraction of `tiles` output tiles (1: not at all): over the idle slots, with at
  * least min_steps K steps for each, at most sixteen, and as far as the caller's workspace holds the partial tiles. */
@@ -591,6 +585,69 @@ int kpair_splits(const hap_gemm_problem* p, long long tiles, long long nk, doubl
   return best;
 }
 
+/* Relative time of n output tiles of 128x128 (one 256x256 tile on one CU = 1): a small tile does a
+ * quarter of the work at lower efficiency, and two of them share a CU. */
+static double small_tiles_time(long long n) {
+  if (n <= 0) return 0.0;
+  const int kCUs = cu_count();
+  // measured: a round of 512 small tiles takes 0.58 of a round of 256 big ones; a last round that leaves every CU at
+  // most one small tile 0.36 (the tile has the CU to itself)
+  const long long full = n / (2 * kCUs), rest = n % (2 * kCUs);
+  return 0.58 * (double)full + (rest == 0 ? 0.0 : (rest <= kCUs ? 0.36 : 0.58));
+}
+
+/* Estimated microseconds of the bf16 kernels, for the planner.  From least-squares fits over 240 random shapes (M, N 300 to 50000, K 64 to 8400,
+ * aligned and not) x five products, each forced through every kernel: standard error 3 to 10 %.  Over those of at most 24 K tiles the
+ * choice that these make is 1.0 to 1.5 % slower than the fastest kernel of each (geometric mean, by product), by whole rounds, whatever the
+ * epilogue and the contraction, 4 to 16 %.  Over 24 to 48 K tiles the two are alike, beyond 48 the rounds are 1 to 1.5 % better for bwd-data:
+ * there a tile's epilogue matters little and what the operands' pitches cost a kernel much. */
+constexpr long long kShortContraction = 24;
+enum { kPlain = 0, kGelu = 1, kDact = 2 };     // what the epilogue does
+
+int epilogue_kind(const hap_gemm_problem* p) { return p->act != HAP_ACT_NONE ? kGelu : (p->dact != HAP_ACT_NONE ? kDact : kPlain); }
+
+/* n 256-tiles.  A K tile of 64 takes 1.5 with all compute units at it (1.65 when both operands are K-contiguous), down to half with few;
+ * prologue, epilogue and stores of a round 9.5, with GeLU and the pre-activation copy or with the activation backward 20.  Fewer tiles
+ * than compute units, as the launcher splits K over the idle ones: 1.55 and 18 with the reduction (24 with
+ * GeLU in it), 0.025 per partial tile (88 tiles over K = 16384, split in two: 199; 68 over 1402 in three: 35, with GeLU 43; 80 over 5312: 68). */
+double us_256(const hap_gemm_problem* p, long long n, long long nk) {
+  const long long cus = cu_count();
+  const long long g = workgroup_splits(p, n, cus, nk, 4, 4 * kSmallTileBytes);
+  if (g > 1) return (double)nk / (double)g * 1.55 + (epilogue_kind(p) == kPlain ? 18.0 : 24.0) + 0.025 * (double)(n * g);
+  const double kt = (double)nk * (p->a_kcontig && p->b_kcontig ? 1.65 : 1.5), round = epilogue_kind(p) == kPlain ? 9.5 : 20.0;
+  const double rest = (double)(n % cus) / (double)cus;
+  return 5.5 + (double)(n / cus) * (kt + round) + (rest > 0.0 ? kt * (0.5 + 0.5 * rest) + round : 0.0);
+}
+
+/* Whether 128-tiles that do not run in gemm_kpair_kernel run in gemm_trio_kernel, and the estimated time either way.  n: tiles.  What
+ * separates the two is the price of a workgroup: with three of them on a compute unit one's prologue and epilogue lie behind the others'
+ * MFMAs; per K tile they are alike, or the two-workgroup kernel is ahead (both operands K-contiguous).  At most one tile per
+ * compute unit leaves nothing to overlap.  Microseconds, two -> three workgroups (2 x 64 KB of LDS against 3 x 48):
+ *   forward 50432 x 315 over 1024 61 -> 54, with GeLU 79 -> 68; 50432 x 1024 over 315 74 -> 60, 112 -> 91
+ *   bwd-data with the activation backward 17947 x 614 over 200 49.7 -> 30.7
+ *   long contractions:  forward 16384 x 2731 over 2048 209 -> 199, bwd-data 16384 x 2048 over 2731 188 -> 231 */
+bool trio_applies(const hap_gemm_problem* p, long long n, long long nk, double* us) {
+  static const double four_fixed[3] = {3.0, 4.0, 4.5}, four_tile[3] = {3.0, 5.7, 5.0}, trio_fixed[3] = {6.0, 7.0, 7.5}, trio_tile[3] = {1.7, 4.1, 3.3};
+  const long long cus = cu_count();
+  const int e = epilogue_kind(p);
+  const bool kk = p->a_kcontig && p->b_kcontig;
+  const long long g = workgroup_splits(p, n, 2 * cus, nk, 4, kSmallTileBytes);
+  if (g > 1) {
+    *us = (double)nk / (double)g * 1.05 + 5.0 + 3.0 + 0.00625 * (double)(n * g);
+    return false;
+  }
+  // tiles that a compute unit works through, a lone one at 1.4 and 1.3 times its share of a full load
+  const long long four_rest = cdiv(n % (2 * cus), cus), trio_rest = cdiv(n % (3 * cus), cus);
+  const double four_load = 2.0 * (double)(n / (2 * cus)) + (four_rest == 1 ? 1.4 : (double)four_rest);
+  const double trio_load = 3.0 * (double)(n / (3 * cus)) + (trio_rest == 1 ? 1.3 : (double)trio_rest);
+  const double four = four_fixed[e] + four_load * ((kk ? 0.44 : 0.475) * (double)nk + four_tile[e]);
+  const double trio = trio_fixed[e] + trio_load * ((kk ? 0.56 : 0.485) * (double)nk + trio_tile[e]);
+  const bool built = p->c_dtype == HAP_BF16 && p->in_dtype == HAP_BF16 && (p->a_kcontig || !p->b_kcontig);
+  const bool take = built && n > cus && nk <= kShortContraction && trio <= four;
+  *us = take ? trio : four;
+  return take;
+}
+
 /* The sub-problem of p over logical rows [m_lo, m_hi) and columns [n_lo, n_hi). */
 hap_gemm_problem sub_problem(const hap_gemm_problem* p, int64_t m_lo, int64_t m_hi, int64_t n_lo, int64_t n_hi, int tile) {
   hap_gemm_problem q = *p;
@@ -607,7 +664,9 @@ hap_gemm_problem sub_problem(const hap_gemm_problem* p, int64_t m_lo, int64_t m_
   return q;
 }
 
-}  // namespace
+}  // namespace hap_gemm_detail
+
+using namespace hap_gemm_detail;
 
 static int64_t g_view_limit = kViewLimitBytes;
 static int64_t g_cut_products = 0;      // products run in pieces so far (testing aid, not synchronised)
@@ -615,6 +674,9 @@ static int64_t g_cut_products = 0;      // products run in pieces so far (testin
 static int64_t g_kpair_products = 0;    // products so far for which kpair_applies() holds (testing aid)
 static int64_t g_small_products = 0;    // products handed to gemm_small_kernel so far (testing aid)
 
+static int64_t g_trio_products = 0;     // products handed to gemm_trio_kernel so far (testing aid)
+
+extern "C" int64_t hap_debug_trio_products(void) { return __atomic_load_n(&g_trio_products, __ATOMIC_RELAXED); }
 extern "C" int64_t hap_debug_small_products(void) { return __atomic_load_n(&g_small_products, __ATOMIC_RELAXED); }
 
 extern "C" int64_t hap_debug_kpair_products(void) { return __atomic_load_n(&g_kpair_products, __ATOMIC_RELAXED); }
@@ -692,66 +754,77 @@ static bool run_large(const hap_gemm_problem* p, void* stream, int* rc) {
 
 /* 256x256 tiles on 256 CUs quantise badly: 33 tile columns of 32 rows are 4.1 rounds of work that take
  * 5.  The engine therefore cuts the output into a part whose big tiles fill whole rounds and a
- * remainder strip computed with 128x128 tiles, when its cost model says that is faster. */
+ * remainder strip computed with 128x128 tiles (or 256-tiles whose K range is split over the idle compute units), when its cost model says
+ * that is faster: the sum of two launches, each with its fixed part. */
 static int run_auto_tiled(const hap_gemm_problem* p, const Plan& pl, void* stream) {
   const int kCUs = cu_count();
   const long long Mp = p->M + pl.skewM, Np = p->N + pl.skewN;
   const long long tm = cdiv(Mp, 256), tn = cdiv(Np, 256);
   const long long sm = cdiv(Mp, 128), sn = cdiv(Np, 128);
-  // A remainder strip of r big tiles can also stay on big tiles with its K range split over the idle CUs
-  // (as far as the workspace allows); that costs about a third of a round for the partial-tile traffic plus 1/g rounds.
   long long nk = 0;                 // K tiles of the contraction
   for (int s = 0; s < p->nseg; ++s) nk += p->k[s] > 0 ? cdiv(pl.skewK + p->k[s], 64) : 0;
-  // A part whose big tiles cannot fill the chip: 128-tiles (two per CU) or 256-tiles, either with the K range split over
+  // Time of n 256-tiles, and of a part that may run on either tile: microseconds for short contractions, rounds of 256-tiles for long ones.
+  const bool is_short = nk <= kShortContraction;
+  auto us_128 = [&](long long n) {
+    double us;
+    trio_applies(p, n, nk, &us);
+    if (kpair_applies(p, n, nk)) {     // (where it applies, it is at least as fast as the 4-wave kernel)
+      double pair;
+      kpair_splits(p, n, nk, &pair);
+      if (pair < us || nk > 128) us = pair;
+    }
+    return us;
+  };
+  // A part of few big tiles over a long contraction: 128-tiles (two per CU) or 256-tiles, either with the K range split over
   // the idle slots as the launcher will do it.  Measured on this chip (microseconds): a workgroup spends 2.0 per K tile
   // on a 256-tile and 1.05 on a 128-tile that shares its CU, plus 7 / 5 for prologue and epilogue; a split costs 3 for
-  // the reduction launch and 0.025 / 0.00625 per partial tile written and read back.  Returned in rounds of big tiles.
+  // the reduction launch and 0.025 / 0.00625 per partial tile written and read back.
   auto few_tiles_us = [&](long long tiles, long long slots, size_t tile_bytes, double per_ktile, double fixed, double per_partial) {
     const long long g = workgroup_splits(p, tiles, slots, nk, 4, tile_bytes);
     const double rounds = (double)cdiv(tiles * g, slots);
     return rounds * ((double)nk / (double)g * per_ktile + fixed) + (g > 1 ? 3.0 + (double)(tiles * g) * per_partial : 0.0);
   };
-  auto strip_time = [&](long long big_tiles, long long small_tiles, int* tile) {
-    if (big_tiles < kCUs && nk > 0) {
-      const double round_us = (double)nk * 2.0 + 7.0;
-      const double tb = few_tiles_us(big_tiles, kCUs, 4 * kSmallTileBytes, 2.0, 7.0, 0.025);
-      double ts = few_tiles_us(small_tiles, 2 * kCUs, kSmallTileBytes, 1.05, 5.0, 0.00625);
-      if (kpair_applies(p, small_tiles, nk)) {     // (where it applies, it is at least as fast as the 4-wave kernel)
+  const double round_us = (double)nk * 2.0 + 7.0;
+  auto big_time = [&](long long n) { return is_short ? us_256(p, n, nk) : (double)cdiv(n, kCUs); };
+  auto part_time = [&](long long big_tiles, long long small_tiles, int* tile) {
+    double tb, ts;
+    if (is_short) {
+      tb = us_256(p, big_tiles, nk);
+      ts = us_128(small_tiles);
+    } else if (big_tiles < kCUs) {
+      tb = few_tiles_us(big_tiles, kCUs, 4 * kSmallTileBytes, 2.0, 7.0, 0.025) / round_us;
+      ts = few_tiles_us(small_tiles, 2 * kCUs, kSmallTileBytes, 1.05, 5.0, 0.00625);
+      if (kpair_applies(p, small_tiles, nk)) {
         double pair;
         kpair_splits(p, small_tiles, nk, &pair);
         if (pair < ts || nk > 128) ts = pair;
       }
-      *tile = tb <= ts ? 256 : 128;
-      return (tb <= ts ? tb : ts) / round_us;
+      ts /= round_us;
+    } else {
+      tb = (double)cdiv(big_tiles, kCUs);
+      ts = small_tiles_time(small_tiles);
     }
-    *tile = 128;
-    return small_tiles_time(small_tiles);
+    *tile = tb <= ts ? 256 : 128;
+    return tb <= ts ? tb : ts;
   };
-  double best = (double)cdiv(tm * tn, kCUs);
-  int choice = 0;                 // 0: all big, 1: all small, 2: split columns, 3: split rows
-  int strip_tile = 128;
+  int strip_tile = 128, whole_tile;
+  double best = part_time(tm * tn, sm * sn, &whole_tile);
+  int choice = whole_tile == 128 ? 1 : 0;       // 0: all big, 1: all small, 2: split columns, 3: split rows
   long long cut = 0;
-  if (tm * tn < kCUs) {           // cannot fill the chip: small tiles, or big tiles with split-K (chosen at launch)
-    int tl;
-    const double t = strip_time(tm * tn, sm * sn, &tl);
-    if (t < best - 1e-9) { best = t; choice = tl == 128 ? 1 : 0; }
-  } else {
-    const double all_small = small_tiles_time(sm * sn);
-    if (all_small < best - 1e-9) { best = all_small; choice = 1; }
-  }
-  // a plan of two launches pays for the second one: the strip starts when the last big tile has finished (~10 us)
-  const double second_launch = nk > 0 ? 10.0 / ((double)nk * 2.0 + 7.0) : 0.0;
+  // a plan of two launches pays for the second one: the strip starts when the last big tile has finished (~10 us; part of every
+  // estimate in microseconds)
+  const double second_launch = is_short ? 0.0 : 10.0 / round_us;
   for (long long c = tn - 1; c >= 1; --c)
     if ((tm * c) % kCUs == 0) {
       int tl;
-      const double t = (double)(tm * c / kCUs) + strip_time(tm * (tn - c), sm * cdiv(Np - c * 256, 128), &tl) + second_launch;
+      const double t = big_time(tm * c) + part_time(tm * (tn - c), sm * cdiv(Np - c * 256, 128), &tl) + second_launch;
       if (t < best - 1e-9) { best = t; choice = 2; cut = c; strip_tile = tl; }
       break;
     }
   for (long long r = tm - 1; r >= 1; --r)
     if ((tn * r) % kCUs == 0) {
       int tl;
-      const double t = (double)(tn * r / kCUs) + strip_time(tn * (tm - r), sn * cdiv(Mp - r * 256, 128), &tl) + second_launch;
+      const double t = big_time(tn * r) + part_time(tn * (tm - r), sn * cdiv(Mp - r * 256, 128), &tl) + second_launch;
       if (t < best - 1e-9) { best = t; choice = 3; cut = r; strip_tile = tl; }
       break;
     }
@@ -824,6 +897,7 @@ static bool overlap_f32(const void* a, int64_t rows_a, int64_t cols_a, int64_t l
 
 int hap_gemm_run_bwd_f32(const hap_gemm_problem* dx, const hap_gemm_problem* dw, float* dbias, int* taken, void* stream) {
   *taken = 0;
+  look_up_cu_count();
   if (!rank_f32_applies(dw)) return HAP_OK;
   {
     // The products apart run one after the other, so that one may write where an earlier one has read; together they must not.
@@ -858,6 +932,7 @@ int hap_gemm_run_bwd_f32(const hap_gemm_problem* dx, const hap_gemm_problem* dw,
 int hap_gemm_run(const hap_gemm_problem* p, void* stream) {
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (p->M <= 0 || p->N <= 0) return HAP_OK;
+  look_up_cu_count();
   if (p->M > 0x7fffffff || p->N > 0x7fffffff) return hap_fail(HAP_EUNSUPPORTED, "GEMM extent exceeds 2^31");
   if (p->accumulate && p->c_dtype != HAP_F32) return hap_fail(HAP_EINVAL, "accumulate needs an fp32 output");
   if (p->in_dtype == HAP_F32 && p->c_dtype != HAP_F32) return hap_fail(HAP_EUNSUPPORTED, "fp32 inputs need fp32 output");
@@ -993,6 +1068,14 @@ int hap_gemm_run(const hap_gemm_problem* p, void* stream) {
       a.kpair = 1;
       __atomic_fetch_add(&g_kpair_products, 1, __ATOMIC_RELAXED);
       a.ksplit = kpair_splits(p, out_tiles, a.ntiles, &us);
+    }
+    double us;
+    if (pl.dma && pl.bm == 128 && !a.kpair && trio_applies(p, out_tiles, a.ntiles, &us)) {
+      a.ntiles = 0;                      // its K step is 32
+      for (int s = 0; s < a.nseg; ++s) a.ntiles += (pl.skewK + a.seg[s].k + 31) / 32;
+      if (a.ntiles == 0) a.ntiles = 1;
+      __atomic_fetch_add(&g_trio_products, 1, __ATOMIC_RELAXED);
+      return run_trio(p, a, groups, st);
     }
     if (a.ksplit > 1) a.partial = static_cast<float*>(p->ws);
   }

@@ -1313,6 +1313,149 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_pp_kernel(const GemmArgs 
 }
 
 /* ---------------------------------------------------------------------------------------------
+ * bf16 kernel for short contractions: 128 x 128 tiles, four waves, three workgroups per compute unit.
+ *
+ * Over a few hundred k a workgroup spends longer in its prologue (the first tiles' way from memory) and epilogue (activation, stores) than
+ * in its K loop, and a 256 x 256 tile, which has its compute unit to itself, overlaps neither with anything.  Here a K step of 32 in a
+ * three-stage ring takes 48 KB of LDS and the waves at most 168 registers, so that three independent workgroups share a compute unit and
+ * one's ends lie behind the others' MFMAs.  Bound: the operands' way from L2 (a tile of this size fetches twice what a 256-tile does per
+ * MFMA), which is why long contractions go elsewhere.  Two workgroups of 256 x 128 per compute unit, tried for the same end, fetch less and
+ * measured 5 to 10 % slower than three of 128 x 128 wherever either gained (50432 x 1024 over 315: 98 against 91 us, 74 before).
+ * Four per compute unit (128 registers) spill in the epilogue: 90 there, but 74 against 60 without GeLU.
+ *
+ * A tile's loads go out behind the previous tile's fragment reads, two tiles ahead of their use; fragments are fetched whole, by hand-
+ * ordered reads, and one barrier per tile separates a slot's last reader from its next request.
+ * ------------------------------------------------------------------------------------------- */
+template <typename TC, bool AKC, bool BKC>
+__global__ __launch_bounds__(256, 3) void gemm_trio_kernel(const GemmArgs args) {
+  typedef __bf16 T;
+  constexpr int BM = 128, BN = 128, BK = 32, STAGES = 3, WGM = 2, WGN = 2, NT = 256;
+  constexpr int WTM = BM / WGM, WTN = BN / WGN;
+  constexpr int TM = WTM / 32, TN = WTN / 32;
+  constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2, STAGE_BYTES = A_BYTES + B_BYTES;
+  typedef DmaLoader<AKC, BM, BK, NT> LA;
+  typedef DmaLoader<BKC, BN, BK, NT> LB;
+  constexpr int LPT = LA::CPT + LB::CPT;            // loads per thread and tile
+  constexpr int KK = BK / 16;
+
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
+  const int wm0 = (wave / WGN) * WTM, wn0 = (wave % WGN) * WTN;
+  const BlockPos bp = block_pos(args);
+  const int m0 = bp.tm * BM, n0 = bp.tn * BN;
+  const GroupView gv = group_view(args, bp.grp);
+  const int m_lim = args.skewM + gv.M, n_lim = args.skewN + args.N;
+  if (args.ragged == 1 && (gv.M == 0 || m0 >= m_lim)) return;
+  const int all_tiles = gv.k >= 0 ? (args.skewK + gv.k + BK - 1 >= BK ? (args.skewK + gv.k + BK - 1) / BK : 1) : args.ntiles;
+
+  LA la; LB lb;
+  la.init(tid, m0, AKC ? args.skewM : 0, m_lim, args.lda);
+  lb.init(tid, n0, BKC ? args.skewN : 0, n_lim, args.ldb);
+  PinnedFrag<AKC, BM, BK, TM, 1> fra;
+  PinnedFrag<BKC, BN, BK, TN, 1> frb;
+  fra.init(lane, wm0, lds_addr(smem));
+  frb.init(lane, wn0, lds_addr(smem));
+
+  f32x16_t acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
+
+  const int ntiles = all_tiles;                      // (K is not split over workgroups)
+  int pseg = 0, pk0 = 0, pkend = uni(args.skewK + (gv.k >= 0 ? gv.k : args.seg[0].k)), issued = 0;
+  __amdgpu_buffer_rsrc_t ra = make_rsrc(static_cast<const char*>(args.seg[0].a) + gv.oa, args.seg[0].a_bytes);
+  __amdgpu_buffer_rsrc_t rb = make_rsrc(static_cast<const char*>(args.seg[0].b) + gv.ob, args.seg[0].b_bytes);
+  int lseg = 0, lk0 = 0, lkend = pkend;
+
+  auto request = [&](auto slot_tag) {
+    constexpr int SLOT = decltype(slot_tag)::value;
+    char* pa = smem + SLOT * STAGE_BYTES;
+    char* pb = pa + A_BYTES;
+    const unsigned soa = LA::tile_offset(pk0, args.skewK, args.lda), sob = LB::tile_offset(pk0, args.skewK, args.ldb);
+    if (pk0 < args.skewK || pk0 + BK > pkend) {      // first / last tile of a segment: validity per chunk
+      la.issue_edge(ra, pa, tid, soa, pk0, args.skewK, pkend);
+      lb.issue_edge(rb, pb, tid, sob, pk0, args.skewK, pkend);
+    } else {
+      la.issue(ra, pa, wave << 6, soa);
+      lb.issue(rb, pb, wave << 6, sob);
+    }
+    pk0 += BK;
+    ++issued;
+    if (pk0 >= pkend && pseg + 1 < args.nseg) {
+      pseg = uni(pseg + 1);
+      pk0 = 0;
+      pkend = uni(args.skewK + args.seg[pseg].k);
+      ra = make_rsrc(static_cast<const char*>(args.seg[pseg].a) + gv.oa, args.seg[pseg].a_bytes);
+      rb = make_rsrc(static_cast<const char*>(args.seg[pseg].b) + gv.ob, args.seg[pseg].b_bytes);
+    }
+  };
+  auto land = [&](auto slot_tag, int newer) {
+    constexpr int SLOT = decltype(slot_tag)::value;
+    if (STAGES > 2 && newer >= 1) wait_vmcnt<(STAGES - 2) * LPT>();
+    else wait_vmcnt<0>();
+    if (lk0 < args.skewK || lk0 + BK > lkend) {
+      char* sa = smem + SLOT * STAGE_BYTES;
+      la.fixup(sa, tid, lk0, args.skewK, lkend);
+      lb.fixup(sa + A_BYTES, tid, lk0, args.skewK, lkend);
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    }
+    lk0 += BK;
+    if (lk0 >= lkend && lseg + 1 < args.nseg) { lseg = uni(lseg + 1); lk0 = 0; lkend = uni(args.skewK + args.seg[lseg].k); }
+  };
+
+  static_for<STAGES - 1>([&](auto s) { if (s < ntiles) request(s); });
+  if (ntiles > 0) land(std::integral_constant<int, 0>(), issued - 1);
+  __builtin_amdgcn_s_barrier();                      // tile 0 is in LDS for everybody
+
+  auto tile = [&](auto slot_tag, const bool fast, int u) __attribute__((always_inline)) {
+    constexpr int SLOT = decltype(slot_tag)::value;
+    constexpr int PREV = (SLOT + STAGES - 1) % STAGES, NEXT = (SLOT + 1) % STAGES;
+    bf16x8_t fa[KK][TM], fb[KK][TN];
+    static_for<KK>([&](auto kk) {
+      static_for<TN>([&](auto j) { fb[kk][j] = frb.template read<SLOT * STAGE_BYTES + A_BYTES, j, kk>(); });
+      static_for<TM>([&](auto i) { fa[kk][i] = fra.template read<SLOT * STAGE_BYTES, i, kk>(); });
+    });
+    if (fast) {
+      char* pa = smem + PREV * STAGE_BYTES;
+      la.issue(ra, pa, wave << 6, LA::tile_offset(pk0, args.skewK, args.lda));
+      lb.issue(rb, pa + A_BYTES, wave << 6, LB::tile_offset(pk0, args.skewK, args.ldb));
+      pk0 += BK;
+      ++issued;
+    } else {
+      if (issued < ntiles) request(std::integral_constant<int, PREV>());
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk)
+#pragma unroll
+      for (int x = 0; x < TM * TN; ++x) acc[x / TN][x % TN] = mfma(fb[kk][x % TN], fa[kk][x / TN], acc[x / TN][x % TN]);
+    __builtin_amdgcn_s_setprio(0);
+    __builtin_amdgcn_sched_barrier(0);
+    if (fast) {
+      wait_vmcnt<(STAGES - 2) * LPT>();
+      lk0 += BK;
+    } else {
+      if (u + 1 < ntiles) land(std::integral_constant<int, NEXT>(), issued - (u + 2));
+    }
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  for (int u0 = 0; u0 < ntiles; u0 += STAGES) {
+    const bool fast = issued + STAGES <= ntiles && pk0 >= args.skewK && pk0 + STAGES * BK < pkend &&
+                      lk0 >= args.skewK && lk0 + STAGES * BK < lkend;
+    static_for<STAGES>([&](auto s) { if (fast || u0 + s < ntiles) tile(s, fast, u0 + s); });
+  }
+
+  epilogue_transposed<T, TC, TM, TN>(group_outputs(args, gv, bp.grp), acc, m0 + wm0, n0 + wn0, lane, smem + wave * (32 * (TN * 32 * (int)sizeof(TC) + 16)));
+}
+
+/* ---------------------------------------------------------------------------------------------
  * bf16 kernel for outputs of few 128 x 128 tiles: two wave groups share ONE tile, each contracts its half of the workgroup's K
  * tiles in a ring of its own, and the halves meet in LDS before the epilogue, of which each group does one half.
  *
@@ -1763,7 +1906,8 @@ int launch_lds_kernel(void (*kernel)(const GemmArgs), bool (&configured)[64], si
 
 /* Defined in the translation unit that instantiates the kernels in question. */
 int run_pp(const hap_gemm_problem* p, const GemmArgs& a, int groups, hipStream_t st);             // hap_gemm_pp.hip: gemm_pp_kernel, 256 x 256
-int run_small(const hap_gemm_problem* p, const GemmArgs& a, int bm, int groups, hipStream_t st);
+int run_trio(const hap_gemm_problem* p, const GemmArgs& a, int groups, hipStream_t st);           // hap_gemm_trio.hip: gemm_trio_kernel
+int run_small(const hap_gemm_problem* p, const GemmArgs& a, int bm, int groups, hipStream_t st);  // hap_gemm_small.hip: gemm_small_kernel of bm rows
 int run_dma(const hap_gemm_problem* p, const GemmArgs& a, int tile, int groups, hipStream_t st);  // hap_gemm_dma.hip: gemm_dma_kernel of 128- or
                                                                                                   // 256-tiles, gemm_kpair_kernel
 

@@ -41,6 +41,7 @@ int64_t hap_debug_set_gemm_view_limit(int64_t bytes);
  * takes the smallest of them in its place; so that a test can state which products it reaches them with. */
 int64_t hap_debug_kpair_products(void);
 int64_t hap_debug_small_products(void);
+int64_t hap_debug_trio_products(void);      /* ... to gemm_trio_kernel */
 
 #ifdef __cplusplus
 }

@@ -92,3 +92,23 @@ def test_fragments_are_left_alone_until_their_wait(code):
                     reads += read
                     pending.append(registers(operands.split(",")[0]) if read else set())
             assert reads >= 32, (name, reads)
+
+
+def test_fragments_of_the_other_hand_ordered_kernels_are_left_alone(code):
+    """The same for the two kernels that read their fragments whole before a tile's MFMAs."""
+    for pattern in ("gemm_trio_kernel", "gemm_small_kernel"):
+        for name, lines in kernels(code, pattern).items():
+            pending, reads = [], 0
+            for line in lines:
+                op, _, operands = line.partition(" ")
+                if op == "s_waitcnt" and "lgkmcnt" in operands:
+                    n = int(re.search(r"lgkmcnt\((\d+)\)", operands).group(1))
+                    pending = pending[len(pending) - n:] if 0 < n < len(pending) else (pending if n else [])
+                    continue
+                used = registers(operands)
+                assert not any(p & used for p in pending), (name, line)
+                if op.startswith("ds_"):
+                    read = op.startswith("ds_read")
+                    reads += read
+                    pending.append(registers(operands.split(",")[0]) if read else set())
+            assert reads >= 12, (name, reads)

@@ -257,6 +257,29 @@ def test_linear_paired_wave_groups_beyond_the_smallest_outputs(hap, k):
         assert hap.hap_debug_kpair_products() - hap.hap_debug_small_products() - before >= 2, (mode, k)
 
 
+@pytest.mark.parametrize("k", [8, 24, 32, 40, 96, 104, 200, 328, 520])
+def test_linear_short_contractions_of_many_tiles(hap, k):
+    """More than 512 tiles of 128 x 128 over one to seventeen K steps of 32 (fewer than the ring has stages, as many, more), interior and cut
+    at both ends: the forward contracts k or 1040 - k features, bwd-data as many columns, with GeLU, its backward and without."""
+    before = hap.hap_debug_trio_products()
+    run_linear_case(hap, "bf16", 4300, 2104, k, 1, [0, k // 3, k], act=True, bias=True, full=True)        # dX over k // 3, k - k // 3
+    run_linear_case(hap, "bf16", 4300, k, 2104, 2, [0, k // 2, k], act=False, bias=False, full=True)      # Y over k // 2
+    run_linear_case(hap, "bf16", 4300, k, 2104, 3, [0, 1], act=True, bias=True, full=False)
+    assert hap.hap_debug_trio_products() - before >= 5
+    # the fused activation backward into columns that start on and off the output's 16-byte grid
+    from oracle import pointwise as opw
+    Xh, Xd = gen(13, T.X, (4300, 2104), 1.0, "bf16"); Wh, Wd = gen(13, T.W, (2104, k), 0.05, "bf16")
+    dYh, dYd = gen(13, T.DY, (4300, k), 1.0, "bf16"); Ph, Pd = gen(13, T.MISC, (4300, 2104), 1.5, "bf16")
+    for lo in (0, 3, 8):
+        desc = hap.LinearDesc(4300, 2104, k, olin.REDUCTION, [0, lo, 2104], hap.BF16)
+        want, _, _ = olin.sharded_linear_bwd(olin.REDUCTION, [0, lo, 2104], 1, Xh, Wh, None, dYh, False)
+        dX = empty((4300, 2104), "bf16", float("nan"))
+        hap.hap_sharded_linear_bwd_dact(desc, 1, Xd, Wd, None, dYd, dX, None, hap.BF16, None, Pd, hap.ACT_GELU_ERF, None)
+        got = host(dX)
+        check(f"dP k{k} lo{lo}", got[:, lo:], want * opw.gelu_grad(Ph[:, lo:]), "bf16")
+        assert np.isnan(got[:, :lo]).all()
+
+
 @pytest.mark.parametrize("tokens,in_f,out_f", [(1, 40, 24), (31, 72, 64), (33, 520, 65), (64, 32, 200), (65, 1000, 63), (197, 1024, 315), (250, 248, 1001), (450, 130, 1030), (1000, 3900, 260)])
 def test_linear_smallest_outputs(hap, tokens, in_f, out_f):
     """Outputs of at most 256 tiles of 32 x 64 or 64 x 64 around the tiles' edges, over contractions from less than one K step of 32 (waves
