@@ -33,42 +33,126 @@ struct PieceArgs {
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
-/* One thread per 16-byte chunk of a destination row, the chunks aligned in the DESTINATION's address space: whole
- * chunks are written with one aligned 16-byte store and read from wherever the source happens to lie (global
- * loads need no alignment on this target); the chunks that straddle the row's ends are copied bytewise.  A row has
- * at most (width + 30) / 16 chunks; rows whose start is aligned use fewer and leave the last index empty. */
-__global__ __launch_bounds__(256) void copy_pieces_kernel(const PieceArgs a) {
-  const int j = blockIdx.y;
-  const long long width = a.width[j], nch = (width + 30) / 16, total = a.rows[j] * nch;
-  const char* src = a.src[j];
-  char* dst = a.out + a.dst_off[j];
-  const long long lds = a.ld_src[j], ldd = a.ld_out;
-  for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < total; i += (long long)gridDim.x * 256) {
-    const long long r = i / nch, k = i - r * nch;
-    char* drow = dst + r * ldd;
-    const char* srow = src + r * lds;
-    const long long lo = 16 * k - (long long)(reinterpret_cast<uintptr_t>(drow) & 15), hi = lo + 16;   // byte range within the row
-    if (lo >= 0 && hi <= width) {
-      u32x4 v;
-      __builtin_memcpy(&v, srow + lo, 16);
-      *reinterpret_cast<u32x4*>(drow + lo) = v;
-    } else {
-      const long long b0 = lo < 0 ? 0 : lo, b1 = hi < width ? hi : width;
-      for (long long b = b0; b < b1; ++b) drow[b] = srow[b];
+/* One row range of a piece: rows x width bytes of dst, of which the first vrows x vwidth come from src and the rest is zeros. */
+struct Move {
+  const char* src;
+  char* dst;
+  long long lds, ldd;                // bytes
+  long long rows, width, vrows, vwidth;
+};
+
+/* 16-byte chunks of the destination's rows, aligned in the DESTINATION's address space: whole chunks are written with one aligned 16-byte
+ * store and read from wherever the source happens to lie (global loads need no alignment on this target); chunks that straddle the
+ * row's ends or the shard's edge go unit by unit (UNIT: 4, 2 or 1 bytes, whatever all addresses are
+ * multiples of).  A row has at most (width + 30) / 16 chunks: width / 16 rounded up where all rows start on one, and where
+ * only some do, these leave the last index empty.
+ * Bound: HBM.  A workgroup moves 256 * UNROLL consecutive chunks of the piece, row after row; a thread has UNROLL loads in flight before its
+ * first store.  Large moves (UNROLL 4) store non-temporally: what they write does not fit the caches that their reads go through.
+ * 8192 x 16384 bf16 between three column shards (8402 wide the widest), against one chunk at a time, a 64-bit division each, and plain
+ * stores: assemble 106.2 -> 90.4 us, split into slots 163.8 -> 110.6 (6.1 TB/s; four rows per thread instead of consecutive chunks: 93 and 113,
+ * with plain stores 114 and 147). */
+template <int UNROLL, typename UNIT>
+__device__ __forceinline__ void move_rows(const Move& m) {
+  constexpr bool STREAM = UNROLL > 1;
+  const bool aligned = ((reinterpret_cast<uintptr_t>(m.dst) | (uintptr_t)m.ldd) & 15) == 0;
+  const long long nch = (m.width + (aligned ? 15 : 30)) / 16, total = m.rows * nch, span = (long long)gridDim.x * (256 * UNROLL);
+  const double inv = 1.0 / (double)nch;
+  const int over = (int)(nch < 256 ? 256 / (unsigned)nch : 0), step = 256 - over * (int)(nch < 256 ? nch : 0);   // 256 chunks on: rows, chunks
+  for (long long base = (long long)blockIdx.x * (256 * UNROLL) + threadIdx.x; base < total; base += span) {
+    u32x4 v[UNROLL];
+    long long row[UNROLL], lo[UNROLL];
+    bool whole[UNROLL];               // a whole chunk, of data or of zeros; else units or nothing
+    // row and chunk of the linear index: the quotient from a reciprocal is off by one at most (total < 2^52)
+    long long r = (long long)((double)base * inv), k = base - r * nch;
+    if (k < 0) { --r; k += nch; }
+    if (k >= nch) { ++r; k -= nch; }
+#pragma unroll
+    for (int u = 0; u < UNROLL; ++u) {
+      if (u > 0) {
+        r += over; k += step;
+        if (k >= nch) { ++r; k -= nch; }
+      }
+      const long long i = base + u * 256;
+      row[u] = r;
+      lo[u] = 16 * k - (long long)(reinterpret_cast<uintptr_t>(m.dst + r * m.ldd) & 15);       // first byte of the chunk within the row
+      const long long hi = lo[u] + 16;
+      const bool data = r < m.vrows && hi <= m.vwidth, zeros = r >= m.vrows || lo[u] >= m.vwidth;
+      whole[u] = i < total && lo[u] >= 0 && hi <= m.width && (data || zeros);
+      v[u] = u32x4{0u, 0u, 0u, 0u};
+      if (whole[u] && data) __builtin_memcpy(&v[u], m.src + r * m.lds + lo[u], 16);
+    }
+#pragma unroll
+    for (int u = 0; u < UNROLL; ++u) {
+      if (base + u * 256 >= total) continue;
+      const long long r = row[u], at = lo[u];
+      char* const drow = m.dst + r * m.ldd;
+      if (whole[u]) {
+        if constexpr (STREAM) __builtin_nontemporal_store(v[u], reinterpret_cast<u32x4*>(drow + at));
+        else *reinterpret_cast<u32x4*>(drow + at) = v[u];
+      } else {
+        // units [first, last) of the chunk lie in the row, those before `data` in the shard; all are fetched before the first is stored:
+        // one trip to memory instead of up to sixteen
+        constexpr int N = 16 / (int)sizeof(UNIT);
+        const int first = at < 0 ? (int)-at / (int)sizeof(UNIT) : 0, last = at + 16 < m.width ? N : (int)((m.width - at) / (long long)sizeof(UNIT));
+        const long long left = r < m.vrows ? (m.vwidth - at) / (long long)sizeof(UNIT) : 0;
+        const int data = left < last ? (int)left : last;
+        const UNIT* const sp = reinterpret_cast<const UNIT*>(m.src + r * m.lds + at);           // dereferenced inside the shard only
+        UNIT* const dp = reinterpret_cast<UNIT*>(drow + at);
+        UNIT unit[N];
+#pragma unroll
+        for (int x = 0; x < N; ++x) {
+          unit[x] = 0;
+          if (x >= first && x < data) unit[x] = sp[x];
+        }
+#pragma unroll
+        for (int x = 0; x < N; ++x)
+          if (x >= first && x < last) dp[x] = unit[x];
+      }
     }
   }
 }
 
+template <int UNROLL, typename UNIT>
+__global__ __launch_bounds__(256) void copy_pieces_kernel(const PieceArgs a) {
+  const int j = blockIdx.y;
+  move_rows<UNROLL, UNIT>({a.src[j], a.out + a.dst_off[j], a.ld_src[j], a.ld_out, a.rows[j], a.width[j], a.rows[j], a.width[j]});
+}
+
+/* f(value of the widest unit type that every address is a multiple of) */
+template <typename F>
+void with_unit(uintptr_t phases, F&& f) {
+  if (phases % 4 == 0) f(uint32_t());
+  else if (phases % 2 == 0) f(uint16_t());
+  else f(uint8_t());
+}
+
+/* Chunks per thread: four where the largest piece is 8 MB and more, one below, where a thread's four would only queue up (3000 x 777 bf16 in two
+ * pieces: 7.3 us against 4.7). */
+inline int unroll_for(long long chunks) { return chunks >= (1 << 19) ? 4 : 1; }
+
+inline dim3 move_grid(long long chunks, int unroll, int pieces) {
+  long long gx = (chunks + 256 * unroll - 1) / (256 * unroll);
+  if (gx > 256 * 32) gx = 256 * 32;        // grid-stride beyond 32 blocks per CU and piece
+  return dim3((unsigned)gx, (unsigned)pieces);
+}
+
 int launch_pieces(const PieceArgs& a, hipStream_t s) {
   long long most = 0;
+  uintptr_t phases = (uintptr_t)a.out | (uintptr_t)a.ld_out;       // its lowest bits: what every address is a multiple of
   for (int j = 0; j < a.m; ++j) {
+    if (a.rows[j] <= 0 || a.width[j] <= 0) continue;
+    phases |= (uintptr_t)a.src[j] | (uintptr_t)a.ld_src[j] | (uintptr_t)a.dst_off[j] | (uintptr_t)a.width[j];
     const long long chunks = a.rows[j] * ((a.width[j] + 30) / 16);
-    if (a.rows[j] > 0 && a.width[j] > 0 && chunks > most) most = chunks;
+    most = chunks > most ? chunks : most;
   }
   if (most == 0) return HAP_OK;
-  long long gx = (most + 255) / 256;
-  if (gx > 256 * 32) gx = 256 * 32;        // grid-stride beyond 32 blocks per CU and piece
-  hipLaunchKernelGGL(copy_pieces_kernel, dim3((unsigned)gx, (unsigned)a.m), dim3(256), 0, s, a);
+  const int unroll = unroll_for(most);
+  const dim3 grid = move_grid(most, unroll, a.m);
+  with_unit(phases, [&](auto unit) {
+    using U = decltype(unit);
+    if (unroll == 4) hipLaunchKernelGGL((copy_pieces_kernel<4, U>), grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((copy_pieces_kernel<1, U>), grid, dim3(256), 0, s, a);
+  });
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hap_fail(HAP_EDEVICE, "piece copy launch: %s", hipGetErrorString(e));
   return HAP_OK;
@@ -85,34 +169,11 @@ struct SplitArgs {
   long long vwidth[kMaxPieces];
 };
 
-/* The reverse movement: slot j (blockIdx.y) receives shard j's range of the full tensor and zeros up to the slot's
- * extent.  Same chunking as above: 16-byte chunks aligned in the destination, the source read wherever it lies,
- * chunks that straddle the row's ends or the shard's edge byte by byte. */
+/* The reverse movement: slot j (blockIdx.y) receives shard j's range of the full tensor and zeros up to the slot's extent. */
+template <int UNROLL, typename UNIT>
 __global__ __launch_bounds__(256) void split_pieces_kernel(const SplitArgs a) {
   const int j = blockIdx.y;
-  const long long swidth = a.swidth, vwidth = a.vwidth[j], vrows = a.vrows[j];
-  const long long nch = (swidth + 30) / 16, total = a.srows * nch;
-  const char* src = a.src + a.src_off[j];
-  char* dst = a.dst[j];
-  const long long lds = a.ld_src, ldd = a.ld_dst[j];
-  for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < total; i += (long long)gridDim.x * 256) {
-    const long long r = i / nch, k = i - r * nch;
-    char* drow = dst + r * ldd;
-    const char* srow = src + r * lds;                       // dereferenced for rows of the shard only
-    const bool row_ok = r < vrows;
-    const long long lo = 16 * k - (long long)(reinterpret_cast<uintptr_t>(drow) & 15), hi = lo + 16;
-    if (lo >= 0 && hi <= swidth && row_ok && hi <= vwidth) {
-      u32x4 v;
-      __builtin_memcpy(&v, srow + lo, 16);
-      *reinterpret_cast<u32x4*>(drow + lo) = v;
-    } else if (lo >= 0 && hi <= swidth && (!row_ok || lo >= vwidth)) {
-      const u32x4 z = {0u, 0u, 0u, 0u};
-      *reinterpret_cast<u32x4*>(drow + lo) = z;
-    } else {
-      const long long b0 = lo < 0 ? 0 : lo, b1 = hi < swidth ? hi : swidth;
-      for (long long b = b0; b < b1; ++b) drow[b] = (row_ok && b < vwidth) ? srow[b] : (char)0;
-    }
-  }
+  move_rows<UNROLL, UNIT>({a.src + a.src_off[j], a.dst[j], a.ld_src, a.ld_dst[j], a.srows, a.swidth, a.vrows[j], a.vwidth[j]});
 }
 
 int check_desc(const hap_gather_desc* d) {
@@ -203,9 +264,16 @@ int hap_reducescatter_split(const hap_gather_desc* d, const void* full, int64_t 
     a.vrows[j] = d->dim == 0 ? hi - lo : d->rows;
     a.vwidth[j] = (d->dim == 0 ? d->cols : hi - lo) * d->elem_bytes;
   }
-  long long gx = (srows * ((a.swidth + 30) / 16) + 255) / 256;
-  if (gx > 256 * 32) gx = 256 * 32;
-  hipLaunchKernelGGL(split_pieces_kernel, dim3((unsigned)gx, (unsigned)d->m), dim3(256), 0, static_cast<hipStream_t>(stream), a);
+  const long long chunks = srows * ((a.swidth + 30) / 16);
+  const int unroll = unroll_for(chunks);
+  const dim3 grid = move_grid(chunks, unroll, d->m);
+  uintptr_t phases = (uintptr_t)a.src | (uintptr_t)a.ld_src | (uintptr_t)a.swidth;
+  for (int j = 0; j < d->m; ++j) phases |= (uintptr_t)a.dst[j] | (uintptr_t)a.ld_dst[j] | (uintptr_t)a.src_off[j] | (uintptr_t)a.vwidth[j];
+  with_unit(phases, [&](auto unit) {
+    using U = decltype(unit);
+    if (unroll == 4) hipLaunchKernelGGL((split_pieces_kernel<4, U>), grid, dim3(256), 0, static_cast<hipStream_t>(stream), a);
+    else hipLaunchKernelGGL((split_pieces_kernel<1, U>), grid, dim3(256), 0, static_cast<hipStream_t>(stream), a);
+  });
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hap_fail(HAP_EDEVICE, "slot split launch: %s", hipGetErrorString(e));
   return HAP_OK;

@@ -152,3 +152,31 @@ def test_all_to_all_reshard_from_rows_to_columns(hap, eb):
         got = back(out, NP[eb], (rows, cap))
         assert np.array_equal(got[:, :sizes_to[j]], want[j]), f"device {j}"
         assert not got[:, sizes_to[j]:].any()                     # the padding arrives as zeros
+
+
+@pytest.mark.parametrize("eb,cols,shift", [(1, 4099, 1), (2, 1030, 3), (2, 77, 5), (4, 601, 1), (8, 300, 0), (2, 9, 1), (2, 4096, 0), (1, 13, 7)])
+def test_large_pieces_move_whole_and_ragged_chunks(hap, eb, cols, shift):
+    """Pieces of 8 MB and more, four chunks per thread and streamed: rows of one to several hundred 16-byte chunks, on and off the 16-byte grid,
+    with pitches of their own; the slots' padding comes out as zeros and nothing beside them is written."""
+    import torch
+    dt = {1: torch.uint8, 2: torch.int16, 4: torch.int32, 8: torch.int64}[eb]
+    rows = (9 << 20) // (max(cols * 2 // 3 * eb, 16)) + 3
+    offs = [0, cols * 2 // 3, cols * 2 // 3, cols]
+    m, cap, ld = 3, max(offs[i + 1] - offs[i] for i in range(3)), cols + 2
+    g = torch.Generator().manual_seed(7)
+    full = torch.randint(-2 ** 62, 2 ** 62, (rows, cols), generator=g).to(dt)
+    src = torch.zeros(rows * ld + shift, dtype=dt); src[shift:].view(rows, ld)[:, :cols] = full
+    src = src.cuda()
+    slots = torch.full((m * rows * cap + shift + 4,), 7, dtype=dt, device="cuda")
+    at = lambda t, k: t.data_ptr() + k * eb
+    desc = hap.GatherDesc(rows, cols, 1, offs, eb)
+    hap.hap_reducescatter_split(desc, at(src, shift), ld, [at(slots, shift + j * rows * cap) for j in range(m)], [cap] * m)
+    got = slots.cpu()
+    assert (got[:shift] == 7).all() and (got[shift + m * rows * cap:] == 7).all()
+    for j in range(m):
+        want = torch.zeros((rows, cap), dtype=dt); want[:, :offs[j + 1] - offs[j]] = full[:, offs[j]:offs[j + 1]]
+        assert torch.equal(got[shift + j * rows * cap:shift + (j + 1) * rows * cap].view(rows, cap), want), j
+    out = torch.full((rows * ld + shift,), 9, dtype=dt, device="cuda")
+    hap.hap_allgather_assemble(desc, [at(slots, shift + j * rows * cap) for j in range(m)], [cap] * m, at(out, shift), ld)
+    back = out.cpu()
+    assert torch.equal(back[shift:].view(rows, ld)[:, :cols], full) and (back[:shift] == 9).all() and (back[shift:].view(rows, ld)[:, cols:] == 9).all()
