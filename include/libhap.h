@@ -345,6 +345,12 @@ int hap_layernorm_bwd(int64_t rows, int64_t n, int io_dtype, const void* x, cons
                       const float* rstd, const void* dy, const void* dresidual, void* dx, float* dgamma, float* dbeta,
                       void* ws, size_t ws_bytes, void* stream);
 size_t hap_layernorm_bwd_workspace(int64_t rows, int64_t n);
+/* The same with a residual gradient, and in the same pass the column sums of dresidual and of dx as stored (fp32 [n], overwritten): the
+ * bias gradients of the two layers whose outputs the residual stream joins.  ws from hap_layernorm_bwd_sums_workspace.   */
+int hap_layernorm_bwd_sums(int64_t rows, int64_t n, int io_dtype, const void* x, const void* gamma, const float* mean,
+                           const float* rstd, const void* dy, const void* dresidual, void* dx, float* dgamma, float* dbeta,
+                           float* sum_dresidual, float* sum_dx, void* ws, size_t ws_bytes, void* stream);
+size_t hap_layernorm_bwd_sums_workspace(int64_t rows, int64_t n);
 
 /* out[r,c] = dy[r,c] * gelu'(preact[r,c])   (erf form)                                            */
 int hap_gelu_bwd(int64_t rows, int64_t cols, int io_dtype, const void* preact, int64_t ldp, const void* dy,

@@ -137,7 +137,7 @@ lib.hap_debug_small_products.restype = C.c_int64
 lib.hap_debug_trio_products.restype = C.c_int64
 lib.hap_allgather_capacity.restype = C.c_int64
 for _n in ("hap_linear_fwd_workspace", "hap_linear_bwd_workspace", "hap_sfb_workspace", "hap_attn_bwd_workspace",
-           "hap_layernorm_bwd_workspace", "hap_colsum_workspace", "hap_moe_linear_fwd_workspace", "hap_moe_linear_bwd_workspace"):
+           "hap_layernorm_bwd_workspace", "hap_layernorm_bwd_sums_workspace", "hap_colsum_workspace", "hap_moe_linear_fwd_workspace", "hap_moe_linear_bwd_workspace"):
     if hasattr(lib, _n):
         getattr(lib, _n).restype = C.c_size_t
 
@@ -151,6 +151,7 @@ for _n, _sig in (("hap_sharded_linear_fwd", "pipppppp" "zp"), ("hap_sharded_line
                  ("hap_allgather_pad", "piplplp"), ("hap_allgather_assemble", "ppp" "plp"), ("hap_reducescatter_split", "pplppp"),
                  ("hap_sharded_attn_fwd", "pippppp" "pzp"), ("hap_sharded_attn_bwd", "pippppppppp" "pzp"),
                  ("hap_layernorm_fwd", "lli" "ppppppp"), ("hap_layernorm_bwd", "lli" "ppppppppp" "pzp"),
+                 ("hap_layernorm_bwd_sums", "lli" "ppppppppppp" "pzp"),
                  ("hap_gelu_bwd", "lliplplplp"), ("hap_add", "lliplplpplp"), ("hap_colsum", "lliplppzp")):
     getattr(lib, _n).argtypes = [{"p": C.c_void_p, "i": C.c_int, "l": C.c_int64, "z": C.c_size_t}[c] for c in _sig]
 
@@ -489,6 +490,16 @@ def hap_layernorm_bwd(rows, n, io_dtype, x, gamma, mean, rstd, dy, dx, dgamma, d
     wp, wb = _ws(ws)
     _check(lib.hap_layernorm_bwd(rows, n, io_dtype, _ptr(x), _ptr(gamma), _ptr(mean), _ptr(rstd),
                                  _ptr(dy), _ptr(dresidual), _ptr(dx), _ptr(dgamma), _ptr(dbeta), wp, wb, _stream(stream)), "hap_layernorm_bwd")
+
+
+def hap_layernorm_bwd_sums_workspace(rows, n) -> int:
+    return int(lib.hap_layernorm_bwd_sums_workspace(C.c_int64(rows), C.c_int64(n)))
+
+
+def hap_layernorm_bwd_sums(rows, n, io_dtype, x, gamma, mean, rstd, dy, dresidual, dx, dgamma, dbeta, sum_dresidual, sum_dx, ws, stream=None):
+    wp, wb = _ws(ws)
+    _check(lib.hap_layernorm_bwd_sums(rows, n, io_dtype, _ptr(x), _ptr(gamma), _ptr(mean), _ptr(rstd), _ptr(dy), _ptr(dresidual), _ptr(dx),
+                                      _ptr(dgamma), _ptr(dbeta), _ptr(sum_dresidual), _ptr(sum_dx), wp, wb, _stream(stream)), "hap_layernorm_bwd_sums")
 
 
 def hap_gelu_bwd(rows, cols, io_dtype, preact, ldp, dy, lddy, out, ldo, stream=None):

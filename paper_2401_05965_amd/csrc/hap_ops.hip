@@ -226,19 +226,25 @@ __global__ __launch_bounds__(256) void layernorm_fwd_kernel(int64_t rows, int n,
 /* LayerNorm backward.  Block = 4 waves, each wave walks rows (stride 4*gridDim.x); per row it forms dx
  * (plus the row of dres when given: the gradient that bypasses the normalisation on the residual path) and adds the row's contribution to its lanes' dgamma / dbeta accumulators; the four waves' sums meet
  * in LDS and go to part[block][2][n]; layernorm_bwd_final_kernel folds the blocks. */
-template <typename T, int V, int NCH>
+/* SUMS: also the column sums of dres and of dx as it is stored, part[block][4][n]: both rows are in registers, a pass of its own over each
+ * would read it again (3940 x 1024 bf16, fold included: 14.3 + 9.4 + 9.2 -> 15.9 us). */
+template <typename T, int V, int NCH, bool SUMS>
 __global__ __launch_bounds__(256) void layernorm_bwd_kernel(int64_t rows, int n, const T* x, const T* gamma, const float* mean,
                                                             const float* rstd, const T* dy, const T* dres, T* dx, float* part) {
   __shared__ float red[4][64 * V * NCH];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  float dg[NCH][V], db[NCH][V];
+  float dg[NCH][V], db[NCH][V], sr[SUMS ? NCH : 1][V], sx[SUMS ? NCH : 1][V];
   Pack<T, V> gm[NCH];
 #pragma unroll
   for (int i = 0; i < NCH; ++i) {
     const int c = (i * 64 + lane) * V;
     if (c < n) gm[i] = *reinterpret_cast<const Pack<T, V>*>(gamma + c);
 #pragma unroll
-    for (int e = 0; e < V; ++e) { dg[i][e] = 0.0f; db[i][e] = 0.0f; if (c >= n) gm[i].v[e] = (T)0.0f; }
+    for (int e = 0; e < V; ++e) {
+      dg[i][e] = 0.0f; db[i][e] = 0.0f;
+      if constexpr (SUMS) { sr[i][e] = 0.0f; sx[i][e] = 0.0f; }
+      if (c >= n) gm[i].v[e] = (T)0.0f;
+    }
   }
   for (int64_t row = (int64_t)blockIdx.x * 4 + wave; row < rows; row += (int64_t)gridDim.x * 4) {
     const float mu = mean[row], rs = rstd[row];
@@ -277,27 +283,31 @@ __global__ __launch_bounds__(256) void layernorm_bwd_kernel(int64_t rows, int n,
         if constexpr (kEarly) r = res[i];
         else if (dres) r = *reinterpret_cast<const Pack<T, V>*>(dres + row * n + c);
 #pragma unroll
-        for (int e = 0; e < V; ++e) o.v[e] = (T)(rs * (g[i][e] - s1 - xh[i][e] * s2) + (dres ? (float)r.v[e] : 0.0f));
+        for (int e = 0; e < V; ++e) {
+          o.v[e] = (T)(rs * (g[i][e] - s1 - xh[i][e] * s2) + (dres ? (float)r.v[e] : 0.0f));
+          if constexpr (SUMS) { sr[i][e] += (float)r.v[e]; sx[i][e] += (float)o.v[e]; }
+        }
         *reinterpret_cast<Pack<T, V>*>(dx + row * n + c) = o;
       }
     }
   }
 #pragma unroll
-  for (int pass = 0; pass < 2; ++pass) {
+  for (int pass = 0; pass < (SUMS ? 4 : 2); ++pass) {
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < NCH; ++i)
 #pragma unroll
-      for (int e = 0; e < V; ++e) red[wave][(i * 64 + lane) * V + e] = pass == 0 ? dg[i][e] : db[i][e];
+      for (int e = 0; e < V; ++e) red[wave][(i * 64 + lane) * V + e] = pass == 0 ? dg[i][e] : pass == 1 ? db[i][e] : pass == 2 ? sr[SUMS ? i : 0][e] : sx[SUMS ? i : 0][e];
     __syncthreads();
     for (int c = threadIdx.x; c < n; c += 256)
-      part[((int64_t)blockIdx.x * 2 + pass) * n + c] = red[0][c] + red[1][c] + red[2][c] + red[3][c];
+      part[((int64_t)blockIdx.x * (SUMS ? 4 : 2) + pass) * n + c] = red[0][c] + red[1][c] + red[2][c] + red[3][c];
   }
 }
 
-/* Folds layernorm_bwd partials: part[block][2][n] -> dgamma[n] (blockIdx.y = 0), dbeta[n] (1).  A block
+/* Folds layernorm_bwd partials: part[block][gridDim.y][n] -> out.p[blockIdx.y][n] (dgamma, dbeta, column sums of dres and dx).  A block
  * owns 16 columns; its 16 thread groups walk the partial rows 16 apart and meet in LDS. */
-__global__ __launch_bounds__(256) void layernorm_bwd_final_kernel(int n, int nblocks, const float* part, float* dgamma, float* dbeta) {
+struct LnSums { float* p[4]; };
+__global__ __launch_bounds__(256) void layernorm_bwd_final_kernel(int n, int nblocks, const float* part, const LnSums out) {
   __shared__ float red[16][17];
   const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
   const int c = blockIdx.x * 16 + tx;
@@ -306,12 +316,12 @@ __global__ __launch_bounds__(256) void layernorm_bwd_final_kernel(int n, int nbl
     float a1 = 0.0f, a2 = 0.0f, a3 = 0.0f;
     int p = ty;
     for (; p + 48 < nblocks; p += 64) {
-      a += part[((int64_t)p * 2 + blockIdx.y) * n + c];
-      a1 += part[((int64_t)(p + 16) * 2 + blockIdx.y) * n + c];
-      a2 += part[((int64_t)(p + 32) * 2 + blockIdx.y) * n + c];
-      a3 += part[((int64_t)(p + 48) * 2 + blockIdx.y) * n + c];
+      a += part[((int64_t)p * gridDim.y + blockIdx.y) * n + c];
+      a1 += part[((int64_t)(p + 16) * gridDim.y + blockIdx.y) * n + c];
+      a2 += part[((int64_t)(p + 32) * gridDim.y + blockIdx.y) * n + c];
+      a3 += part[((int64_t)(p + 48) * gridDim.y + blockIdx.y) * n + c];
     }
-    for (; p < nblocks; p += 16) a += part[((int64_t)p * 2 + blockIdx.y) * n + c];
+    for (; p < nblocks; p += 16) a += part[((int64_t)p * gridDim.y + blockIdx.y) * n + c];
     a = (a + a1) + (a2 + a3);
   }
   red[ty][tx] = a;
@@ -320,7 +330,7 @@ __global__ __launch_bounds__(256) void layernorm_bwd_final_kernel(int n, int nbl
     float t = 0.0f;
 #pragma unroll
     for (int r = 0; r < 16; ++r) t += red[r][tx];
-    (blockIdx.y == 0 ? dgamma : dbeta)[c] = t;
+    out.p[blockIdx.y][c] = t;
   }
 }
 
@@ -426,19 +436,32 @@ int layernorm_fwd_t(int64_t rows, int n, const void* x, const void* g, const voi
   return check_launch("layernorm_fwd");
 }
 
+/* sums.p[2], sums.p[3]: NULL, or column sums of dres and dx as well (*sums_taken says whether this layout gives them). */
 template <typename T>
 int layernorm_bwd_t(int64_t rows, int n, const void* x, const void* g, const float* mean, const float* rstd, const void* dy,
-                    const void* dres, void* dx, float* dgamma, float* dbeta, float* part, hipStream_t s) {
+                    const void* dres, void* dx, const LnSums& sums, bool* sums_taken, float* part, hipStream_t s) {
   const int nblocks = (int)((rows + 3) / 4 < kLnBlocks ? (rows + 3) / 4 : kLnBlocks);
   const bool vec_ok = aligned16(x) && aligned16(dy) && aligned16(dx) && aligned16(g) && aligned16(dres);
+  const bool want = sums.p[2] != nullptr;
+  bool took = false;
   const bool ok = ln_dispatch<T>(n, vec_ok, [&](auto v, auto nch) {
-    hipLaunchKernelGGL((layernorm_bwd_kernel<T, decltype(v)::value, decltype(nch)::value>), dim3(nblocks), dim3(256), 0, s, rows, n, (const T*)x,
-                       (const T*)g, mean, rstd, (const T*)dy, (const T*)dres, (T*)dx, part);
+    constexpr int V = decltype(v)::value, NCH = decltype(nch)::value;
+    // (rows of up to 1024 elements: beyond, the four sums of a lane take its last registers and the loads in flight with them - 2048
+    // elements: 64 -> 119 us, more than the two passes that it saves)
+    if constexpr (V > 1 && V * NCH <= 16) {
+      if (want) {
+        took = true;
+        hipLaunchKernelGGL((layernorm_bwd_kernel<T, V, NCH, true>), dim3(nblocks), dim3(256), 0, s, rows, n, (const T*)x, (const T*)g, mean, rstd, (const T*)dy, (const T*)dres, (T*)dx, part);
+        return;
+      }
+    }
+    hipLaunchKernelGGL((layernorm_bwd_kernel<T, V, NCH, false>), dim3(nblocks), dim3(256), 0, s, rows, n, (const T*)x, (const T*)g, mean, rstd, (const T*)dy, (const T*)dres, (T*)dx, part);
   });
   if (!ok) return hap_fail(HAP_EUNSUPPORTED, "layernorm row of %d elements is too long for this layout", n);
   int rc = check_launch("layernorm_bwd");
   if (rc) return rc;
-  hipLaunchKernelGGL(layernorm_bwd_final_kernel, dim3((n + 15) / 16, 2), dim3(256), 0, s, n, nblocks, part, dgamma, dbeta);
+  *sums_taken = took;
+  hipLaunchKernelGGL(layernorm_bwd_final_kernel, dim3((n + 15) / 16, took ? 4 : 2), dim3(256), 0, s, n, nblocks, part, sums);
   return check_launch("layernorm_bwd_final");
 }
 
@@ -594,9 +617,41 @@ int hap_layernorm_bwd(int64_t rows, int64_t n, int io_dtype, const void* x, cons
   const size_t need = hap_layernorm_bwd_workspace(rows, n);
   if (!ws || ws_bytes < need) return hap_fail(HAP_EWORKSPACE, "layernorm_bwd needs %zu workspace bytes", need);
   hipStream_t s = (hipStream_t)stream;
-  if (io_dtype == HAP_BF16) return layernorm_bwd_t<__bf16>(rows, (int)n, x, gamma, mean, rstd, dy, dresidual, dx, dgamma, dbeta, (float*)ws, s);
-  if (io_dtype == HAP_F32) return layernorm_bwd_t<float>(rows, (int)n, x, gamma, mean, rstd, dy, dresidual, dx, dgamma, dbeta, (float*)ws, s);
+  const LnSums out = {{dgamma, dbeta, NULL, NULL}};
+  bool took;
+  if (io_dtype == HAP_BF16) return layernorm_bwd_t<__bf16>(rows, (int)n, x, gamma, mean, rstd, dy, dresidual, dx, out, &took, (float*)ws, s);
+  if (io_dtype == HAP_F32) return layernorm_bwd_t<float>(rows, (int)n, x, gamma, mean, rstd, dy, dresidual, dx, out, &took, (float*)ws, s);
   return hap_fail(HAP_EINVAL, "bad dtype %d", io_dtype);
+}
+
+size_t hap_layernorm_bwd_sums_workspace(int64_t rows, int64_t n) {
+  const size_t ln = 2 * hap_layernorm_bwd_workspace(rows, n), cs = hap_colsum_workspace(rows, n);
+  return ln > cs ? ln : cs;
+}
+
+int hap_layernorm_bwd_sums(int64_t rows, int64_t n, int io_dtype, const void* x, const void* gamma, const float* mean,
+                           const float* rstd, const void* dy, const void* dresidual, void* dx, float* dgamma, float* dbeta,
+                           float* sum_dresidual, float* sum_dx, void* ws, size_t ws_bytes, void* stream) {
+  hap_clear_error();
+  if (!sum_dresidual || !sum_dx || (!dresidual && rows > 0)) return hap_fail(HAP_EINVAL, "NULL pointer");
+  if (rows > 0 && n >= 1 && (!ws || ws_bytes < hap_layernorm_bwd_sums_workspace(rows, n)))
+    return hap_fail(HAP_EWORKSPACE, "layernorm_bwd_sums needs %zu workspace bytes", hap_layernorm_bwd_sums_workspace(rows, n));
+  // rows that the one kernel has the registers for; dx over dresidual is fine there, each element is read before it is written
+  const int v = io_dtype == HAP_BF16 ? 8 : 4;
+  const bool one = rows > 0 && (io_dtype == HAP_BF16 || io_dtype == HAP_F32) && n % v == 0 && n <= 16 * 64 && x && gamma && mean && rstd && dy && dx && dgamma && dbeta &&
+                   aligned16(x) && aligned16(gamma) && aligned16(dy) && aligned16(dresidual) && aligned16(dx);
+  if (one) {
+    const LnSums out = {{dgamma, dbeta, sum_dresidual, sum_dx}};
+    bool took = false;
+    hipStream_t s = (hipStream_t)stream;
+    const int rc = io_dtype == HAP_BF16 ? layernorm_bwd_t<__bf16>(rows, (int)n, x, gamma, mean, rstd, dy, dresidual, dx, out, &took, (float*)ws, s)
+                                        : layernorm_bwd_t<float>(rows, (int)n, x, gamma, mean, rstd, dy, dresidual, dx, out, &took, (float*)ws, s);
+    return rc == HAP_OK && !took ? hap_fail(HAP_EDEVICE, "internal: layernorm backward without its column sums") : rc;
+  }
+  int rc = hap_colsum(rows, n, io_dtype, dresidual, n, sum_dresidual, ws, ws_bytes, stream);      // (before dx, which may take its place)
+  if (rc) return rc;
+  if ((rc = hap_layernorm_bwd(rows, n, io_dtype, x, gamma, mean, rstd, dy, dresidual, dx, dgamma, dbeta, ws, ws_bytes, stream))) return rc;
+  return hap_colsum(rows, n, io_dtype, dx, n, sum_dx, ws, ws_bytes, stream);
 }
 
 }  // extern "C"

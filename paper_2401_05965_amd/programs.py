@@ -271,7 +271,7 @@ class EncoderShard:
         self.d_attn = hap.AttnDesc(self.B, max(self.nh, 1), S, d, True, [0, max(self.nh, 1)], stride_b=S * 3 * hd, stride_s=3 * hd, stride_h=d,
                                    o_strides=(S * hd, hd, d)) if hd and self.B else None    # no (batch entry, head) pair: no attention call
         nws = max([hap.hap_linear_bwd_workspace(x, 0) for x in (self.d_qkv, self.d_wo, self.d_fc1, self.d_fc2)] +
-                  [hap.hap_layernorm_bwd_workspace(N, hidden), hap.hap_colsum_workspace(N, hidden),
+                  [hap.hap_layernorm_bwd_sums_workspace(N, hidden), hap.hap_colsum_workspace(N, hidden),
                    hap.hap_attn_bwd_workspace(self.d_attn, 0) if self.d_attn is not None else 0, 256])
         self.ws = torch.empty((nws,), dtype=torch.uint8, device=dev)
 
@@ -322,6 +322,12 @@ class EncoderShard:
         _call(timer, "ln2_bwd", lambda: hap.hap_layernorm_bwd(self.N, self.hidden, self.io, x1, self.g2, self.mean2, self.rstd2, dln2, dx1,
                                                               self.dg2, self.dbe2, self.ws, dresidual=dres))
 
+    def ln2_backward_with_bias_grads(self, x1, dln2, dres, dx1, db2, dbo, timer=None):
+        """ln2_backward() that also leaves colsum(dres) in db2 and colsum(dx1) in dbo: the gradients of the MLP's and the attention's output
+        biases, whose layers end at the residual stream."""
+        _call(timer, "ln2_bwd", lambda: hap.hap_layernorm_bwd_sums(self.N, self.hidden, self.io, x1, self.g2, self.mean2, self.rstd2, dln2, dres, dx1,
+                                                                   self.dg2, self.dbe2, db2, dbo, self.ws))
+
     def attn_backward(self, dx1, timer=None):
         """dx1: gradient at the residual stream after attention.  Leaves the QKV bwd-data product in dln1_part."""
         hd = self.hd
@@ -349,10 +355,8 @@ class EncoderShard:
         add = lambda a, b, bias, out: hap.hap_add(N, h, self.io, a, h, b, h, bias, out, h)
         self.attn_forward(x); add(x, self.attn_part, bo, buf["x1"])
         self.mlp_forward(buf["x1"]); add(buf["x1"], self.mlp_part, b2, buf["y"])
-        self.mlp_backward(dy); self.ln2_backward(buf["x1"], self.dln2_part, dy, buf["dx1"])
+        self.mlp_backward(dy); self.ln2_backward_with_bias_grads(buf["x1"], self.dln2_part, dy, buf["dx1"], buf["db2"], buf["dbo"])
         self.attn_backward(buf["dx1"]); self.ln1_backward(x, self.dln1_part, buf["dx1"], buf["dx"])
-        hap.hap_colsum(N, h, self.io, dy, h, buf["db2"], self.ws)
-        hap.hap_colsum(N, h, self.io, buf["dx1"], h, buf["dbo"], self.ws)
 
 
 class EncoderLayerProgram:

@@ -275,3 +275,36 @@ def test_row_ops_degenerate_sizes(hap):
         hap.hap_add(0, 9, io, keep, 9, keep, 9, None, keep, 9)
         hap.hap_add(4, 0, io, keep, 9, keep, 9, None, keep, 9)
         assert (host(keep) == 3).all()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("n", [8, 77, 512, 1000, 1024, 1032, 2056])
+@pytest.mark.parametrize("rows", [0, 1, 5, 2100])
+@pytest.mark.parametrize("inplace", [False, True])
+def test_layernorm_bwd_with_column_sums(hap, dtype, n, rows, inplace):
+    """The sums of the residual gradient's and of the stored dx's columns beside the plain backward's results, which stay what they are bit
+    for bit: rows of up to 1024 elements in one pass, longer and scalar ones in passes of their own, one to several rows per wave."""
+    from oracle import pointwise as opw
+    if dtype == "f32" and n > 2048:
+        n = 2047      # (fp32 rows end at 2048 elements)
+    io = {"bf16": 1, "f32": 0}[dtype]
+    xh, xd = gen(21, T.X, (max(rows, 1), n), 1.0, dtype); gh, gd = gen(21, T.W, (n,), 0.5, dtype)
+    dyh, dyd = gen(21, T.DY, (max(rows, 1), n), 1.0, dtype); rh, rd = gen(21, T.MISC, (max(rows, 1), n), 1.0, dtype)
+    bd = empty((n,), dtype, 0); y = empty((max(rows, 1), n), dtype, 0); mean, rstd = empty((max(rows, 1),), "f32", 0), empty((max(rows, 1),), "f32", 0)
+    hap.hap_layernorm_fwd(rows, n, io, xd, gd, bd, y, mean, rstd)
+    out = lambda *s: empty(s, "f32", 5)
+    dg, db, dg2, db2, sr, sx = (out(n) for _ in range(6))
+    dx = empty((max(rows, 1), n), dtype, 3)
+    hap.hap_layernorm_bwd(rows, n, io, xd, gd, mean, rstd, dyd, dx, dg, db, empty((max(hap.hap_layernorm_bwd_workspace(rows, n), 16),), "u8"), dresidual=rd)
+    dx2 = rd.clone() if inplace else empty((max(rows, 1), n), dtype, 3)
+    hap.hap_layernorm_bwd_sums(rows, n, io, xd, gd, mean, rstd, dyd, dx2 if inplace else rd, dx2, dg2, db2, sr, sx,
+                               empty((max(hap.hap_layernorm_bwd_sums_workspace(rows, n), 16),), "u8"))
+    if rows:
+        assert np.array_equal(host(dx), host(dx2))
+    assert np.array_equal(host(dg), host(dg2)) and np.array_equal(host(db), host(db2))
+    # fp32 sums of `rows` terms: within rows * eps of the sum of magnitudes, measured against that
+    for name, got, terms in (("dres", sr, rh[:rows]), ("dx", sx, host(dx)[:rows])):
+        bound = 1e-7 * (rows + 8) * np.abs(terms).sum(0) + 1e-30
+        assert (np.abs(host(got) - terms.sum(0)) <= bound).all(), name
+    with pytest.raises(hap.HapError):
+        hap.hap_layernorm_bwd_sums(7, n, io, xd, gd, mean, rstd, dyd, rd, dx2, dg2, db2, sr, sx, empty((16,), "u8"))
