@@ -143,7 +143,8 @@ for _n in ("hap_linear_fwd_workspace", "hap_linear_bwd_workspace", "hap_sfb_work
 
 
 # Signatures of the entry points that launch device work: with them ctypes converts plain integers itself, which costs a fraction of
-# wrapping every argument in an object (p pointer, i int, l int64, z size_t).
+# wrapping every argument in an object (p pointer, i int, l int64, z size_t).  Every entry point that is handed an address has to be
+# here: without a signature ctypes passes a plain integer as a C int and cuts it to 32 bits.
 for _n, _sig in (("hap_sharded_linear_fwd", "pipppppp" "zp"), ("hap_sharded_linear_bwd", "pippppppip" "pzp"),
                  ("hap_sharded_linear_bwd_dact", "pippppppip" "pipzp"), ("hap_sfb_grad", "ippp" "llll" "ipli" "pzp"),
                  ("hap_sfb_grad_static", "ippp" "llll" "ipli" "p"), ("hap_moe_linear_fwd", "pippppppp" "zp"),
@@ -152,7 +153,8 @@ for _n, _sig in (("hap_sharded_linear_fwd", "pipppppp" "zp"), ("hap_sharded_line
                  ("hap_sharded_attn_fwd", "pippppp" "pzp"), ("hap_sharded_attn_bwd", "pippppppppp" "pzp"),
                  ("hap_layernorm_fwd", "lli" "ppppppp"), ("hap_layernorm_bwd", "lli" "ppppppppp" "pzp"),
                  ("hap_layernorm_bwd_sums", "lli" "ppppppppppp" "pzp"),
-                 ("hap_gelu_bwd", "lliplplplp"), ("hap_add", "lliplplpplp"), ("hap_colsum", "lliplppzp")):
+                 ("hap_gelu_bwd", "lliplplplp"), ("hap_add", "lliplplpplp"), ("hap_colsum", "lliplppzp"),
+                 ("hap_probe_mfma_bf16", "iippp")):
     getattr(lib, _n).argtypes = [{"p": C.c_void_p, "i": C.c_int, "l": C.c_int64, "z": C.c_size_t}[c] for c in _sig]
 
 
@@ -554,6 +556,6 @@ def hap_device_info():
 def hap_probe_mfma_bf16(random_operands: bool, iters: int, scratch, stream=None) -> float:
     """Launches the MFMA issue-rate probe; returns the flops of the launch (the caller times it)."""
     fl = C.c_double()
-    _check(lib.hap_probe_mfma_bf16(C.c_int(int(bool(random_operands))), C.c_int(iters), _ptr(scratch), C.byref(fl), _stream(stream)),
+    _check(lib.hap_probe_mfma_bf16(int(bool(random_operands)), iters, _ptr(scratch), C.byref(fl), _stream(stream)),
            "hap_probe_mfma_bf16")
     return fl.value

@@ -31,6 +31,18 @@ def test_every_declared_symbol_is_exported(hap):
     assert hap.hap_strerror(0) and hap.hap_last_error() is not None
 
 
+def test_launching_entry_points_carry_the_signature_of_the_header(hap):
+    """The binding hands addresses over as plain integers, which ctypes cuts to 32 bits where an entry point has no argument types."""
+    text = open(os.path.join(os.path.dirname(__file__), "..", "include", "libhap.h")).read()
+    text = re.sub(r"/\*.*?\*/", "", text, flags=re.S)
+    prototypes = re.findall(r"\b(?:int|size_t)\s+(hap_[a-z0-9_]+)\s*\(([^)]*void\s*\*\s*stream)\)", text)
+    assert len(prototypes) >= 20
+    for name, args in prototypes:
+        want = [C.c_void_p if "*" in a else {"int": C.c_int, "int64_t": C.c_int64, "size_t": C.c_size_t}.get(a.split()[-2], C.c_int)
+                for a in args.split(",")]
+        assert getattr(hap.binding.lib, name).argtypes == want, name
+
+
 def test_lp_matches_oracle_on_random_problems(hap):
     rng = np.random.default_rng(3)
     for trial in range(40):
