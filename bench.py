@@ -381,7 +381,7 @@ def main():
         del flush
         c1["sfb_rebuild_us"] = round(timeit(lambda: hap.hap_sfb_grad([X1[:s1[0]], X1[s1[0]:]], [dY1[:s1[0]], dY1[s1[0]:]], s1, 1024, 1024, 1024, 1024,
                                                                    hap.F32, dW1c, 1024, ws=ws1), n=50) * 1e6, 1)
-        # the whole config-1 step (forward + backward of both devices, SFB rebuild: 11 small kernels), eager and replayed from a HIP graph
+        # the whole config-1 step (forward + backward of both devices, SFB rebuild: five small kernels), eager and replayed from a HIP graph
         def step1():
             for j1 in range(2):
                 hap.hap_sharded_linear_fwd(d1, j1, X1, W1c, None, Y1, None, ws1)
