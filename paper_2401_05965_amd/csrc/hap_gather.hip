@@ -15,6 +15,7 @@
 #include <stdint.h>
 
 #include "hap_internal.h"
+#include "hap_move.h"
 
 namespace {
 
@@ -55,9 +56,9 @@ template <int UNROLL, typename UNIT>
 __device__ __forceinline__ void move_rows(const Move& m) {
   constexpr bool STREAM = UNROLL > 1;
   const bool aligned = ((reinterpret_cast<uintptr_t>(m.dst) | (uintptr_t)m.ldd) & 15) == 0;
-  const long long nch = (m.width + (aligned ? 15 : 30)) / 16, total = m.rows * nch, span = (long long)gridDim.x * (256 * UNROLL);
+  const hap_move::Walk w = hap_move::walk_of(m.rows, m.width, aligned);
+  const long long nch = w.per_row, total = w.total, span = (long long)gridDim.x * (256 * UNROLL);
   const double inv = 1.0 / (double)nch;
-  const int over = (int)(nch < 256 ? 256 / (unsigned)nch : 0), step = 256 - over * (int)(nch < 256 ? nch : 0);   // 256 chunks on: rows, chunks
   for (long long base = (long long)blockIdx.x * (256 * UNROLL) + threadIdx.x; base < total; base += span) {
     u32x4 v[UNROLL];
     long long row[UNROLL], lo[UNROLL];
@@ -69,7 +70,7 @@ __device__ __forceinline__ void move_rows(const Move& m) {
 #pragma unroll
     for (int u = 0; u < UNROLL; ++u) {
       if (u > 0) {
-        r += over; k += step;
+        r += w.over; k += w.step;
         if (k >= nch) { ++r; k -= nch; }
       }
       const long long i = base + u * 256;
