@@ -91,23 +91,20 @@ __device__ __forceinline__ void move_rows(const Move& m) {
         if constexpr (STREAM) __builtin_nontemporal_store(v[u], reinterpret_cast<u32x4*>(drow + at));
         else *reinterpret_cast<u32x4*>(drow + at) = v[u];
       } else {
-        // units [first, last) of the chunk lie in the row, those before `data` in the shard; all are fetched before the first is stored:
-        // one trip to memory instead of up to sixteen
+        // all units are fetched before the first is stored: one trip to memory instead of up to sixteen
         constexpr int N = 16 / (int)sizeof(UNIT);
-        const int first = at < 0 ? (int)-at / (int)sizeof(UNIT) : 0, last = at + 16 < m.width ? N : (int)((m.width - at) / (long long)sizeof(UNIT));
-        const long long left = r < m.vrows ? (m.vwidth - at) / (long long)sizeof(UNIT) : 0;
-        const int data = left < last ? (int)left : last;
+        const hap_move::Units c = hap_move::units_of(at, m.width, r < m.vrows ? m.vwidth : 0, (int)sizeof(UNIT));
         const UNIT* const sp = reinterpret_cast<const UNIT*>(m.src + r * m.lds + at);           // dereferenced inside the shard only
         UNIT* const dp = reinterpret_cast<UNIT*>(drow + at);
         UNIT unit[N];
 #pragma unroll
         for (int x = 0; x < N; ++x) {
           unit[x] = 0;
-          if (x >= first && x < data) unit[x] = sp[x];
+          if (x >= c.first && x < c.data) unit[x] = sp[x];
         }
 #pragma unroll
         for (int x = 0; x < N; ++x)
-          if (x >= first && x < last) dp[x] = unit[x];
+          if (x >= c.first && x < c.last) dp[x] = unit[x];
       }
     }
   }

@@ -1,5 +1,5 @@
 """The index arithmetic of the piece copies (csrc/hap_move.h), compiled for the host with the undefined-behaviour sanitizer and compared with
-counting: moves of devices that own nothing, rows of one chunk to 2^31 bytes and more."""
+counting: moves of devices that own nothing, rows longer than 2^31 bytes, cut chunks of all phases."""
 import os
 import subprocess
 
@@ -33,12 +33,29 @@ int main() {
           }
         }
       }
+  // byte by byte: which units of a chunk lie in the row, which of those in the shard
+  for (int unit = 1; unit <= 4; unit *= 2)
+    for (int phase = 0; phase < 16; phase += unit)
+      for (long long width : {4LL, 16LL, 20LL, 48LL, (3LL << 31) + 4})
+        for (long long vwidth : {0LL, 4LL, 12LL, 16LL, 20LL, 44LL, 3LL << 31, (3LL << 31) + 4}) {
+          if (vwidth > width) continue;
+          const long long chunks = (width + phase + 15) / 16;
+          for (long long k = 0; k < chunks; k = k == 3 && chunks > 8 ? chunks - 3 : k + 1) {
+            const long long at = 16 * k - phase;
+            const Units c = units_of(at, width, vwidth, unit);
+            for (int x = 0; x < 16 / unit; ++x) {
+              const long long b = at + x * unit;
+              if ((x >= c.first && x < c.last) != (b >= 0 && b < width)) fail("in the row", unit, at, width, vwidth);
+              if ((x >= c.first && x < c.data) != (b >= 0 && b < vwidth)) fail("in the shard", unit, at, width, vwidth);
+            }
+          }
+        }
   std::puts("ok");
 }
 """
 
 
-def test_chunks_of_empty_moves_and_of_long_rows(tmp_path):
+def test_chunks_of_empty_moves_and_of_rows_beyond_2_gib(tmp_path):
     src, exe = tmp_path / "move.cpp", tmp_path / "move"
     src.write_text(SOURCE)
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Wextra", "-fsanitize=undefined", "-fno-sanitize-recover=all", "-I", CSRC, str(src), "-o", str(exe)], check=True)
