@@ -154,13 +154,15 @@ def test_all_to_all_reshard_from_rows_to_columns(hap, eb):
         assert not got[:, sizes_to[j]:].any()                     # the padding arrives as zeros
 
 
+@pytest.mark.parametrize("mb", [6, 50])
 @pytest.mark.parametrize("eb,cols,shift", [(1, 4099, 1), (2, 1030, 3), (2, 77, 5), (4, 601, 1), (8, 300, 0), (2, 9, 1), (2, 4096, 0), (1, 13, 7)])
-def test_large_pieces_move_whole_and_ragged_chunks(hap, eb, cols, shift):
-    """Pieces of 8 MB and more, four chunks per thread and streamed: rows of one to several hundred 16-byte chunks, on and off the 16-byte grid,
-    with pitches of their own; the slots' padding comes out as zeros and nothing beside them is written."""
+def test_large_pieces_move_whole_and_ragged_chunks(hap, eb, cols, shift, mb):
+    """A largest piece of 50 MB, 75 MB and more in all (streamed from 72 MB on), and one of 6 MB: rows of one to several hundred 16-byte chunks, on
+    and off the 16-byte grid, with pitches of their own; the slots' padding comes out as zeros and nothing beside them is written."""
     import torch
     dt = {1: torch.uint8, 2: torch.int16, 4: torch.int32, 8: torch.int64}[eb]
-    rows = (9 << 20) // (max(cols * 2 // 3 * eb, 16)) + 3
+    rows = (mb << 20) // (cols * 2 // 3 * eb) + 3
+    assert (rows * cols * eb >= 72 << 20) == (mb == 50)
     offs = [0, cols * 2 // 3, cols * 2 // 3, cols]
     m, cap, ld = 3, max(offs[i + 1] - offs[i] for i in range(3)), cols + 2
     g = torch.Generator().manual_seed(7)
