@@ -531,8 +531,7 @@ def hap_debug_set_gemm_view_limit(nbytes: int) -> int:
 
 
 def hap_debug_kpair_products() -> int:
-    """Testing aid: how many products of the kind that gemm_kpair_kernel is for the GEMM engine has run so far (the smallest of them in
-    gemm_small_kernel)."""
+    """Testing aid: how many products the GEMM engine has handed to gemm_kpair_kernel so far."""
     return int(lib.hap_debug_kpair_products())
 
 

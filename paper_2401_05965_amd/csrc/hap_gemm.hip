@@ -671,15 +671,12 @@ using namespace hap_gemm_detail;
 static int64_t g_view_limit = kViewLimitBytes;
 static int64_t g_cut_products = 0;      // products run in pieces so far (testing aid, not synchronised)
 
-static int64_t g_kpair_products = 0;    // products so far for which kpair_applies() holds (testing aid)
-static int64_t g_small_products = 0;    // products handed to gemm_small_kernel so far (testing aid)
-
-static int64_t g_trio_products = 0;     // products handed to gemm_trio_kernel so far (testing aid)
-
-extern "C" int64_t hap_debug_trio_products(void) { return __atomic_load_n(&g_trio_products, __ATOMIC_RELAXED); }
-extern "C" int64_t hap_debug_small_products(void) { return __atomic_load_n(&g_small_products, __ATOMIC_RELAXED); }
+// Launches of gemm_kpair_kernel, gemm_small_kernel and gemm_trio_kernel so far (testing aid)
+static int64_t g_kpair_products = 0, g_small_products = 0, g_trio_products = 0;
 
 extern "C" int64_t hap_debug_kpair_products(void) { return __atomic_load_n(&g_kpair_products, __ATOMIC_RELAXED); }
+extern "C" int64_t hap_debug_small_products(void) { return __atomic_load_n(&g_small_products, __ATOMIC_RELAXED); }
+extern "C" int64_t hap_debug_trio_products(void) { return __atomic_load_n(&g_trio_products, __ATOMIC_RELAXED); }
 
 /* Test hook (declared in hap_internal.h, not part of the public interface): lowers the reach at which operand views are
  * cut so the cutting can be exercised on small inputs; returns how many products have run in pieces so far. */
@@ -1056,13 +1053,7 @@ int hap_gemm_run(const hap_gemm_problem* p, void* stream) {
     const long long slots = pl.bm == 256 ? kCUs : (pl.bm == 128 ? 2 * kCUs : 4 * kCUs);
     const int min_tiles = pl.bm == 64 ? 2 : 4 * (64 / pl.bk);      // in K steps of the chosen kernel
     a.ksplit = pl.small ? 1 : (int)workgroup_splits(p, out_tiles, slots, a.ntiles, min_tiles, (size_t)pl.bm * pl.bn * sizeof(float));
-    if (pl.small) {
-      __atomic_fetch_add(&g_small_products, 1, __ATOMIC_RELAXED);
-      const long long tiles128 = cdiv(p->M + pl.skewM, 128) * cdiv(p->N + pl.skewN, 128) * groups;
-      long long nk = 0;
-      for (int s = 0; s < p->nseg; ++s) nk += p->k[s] > 0 ? cdiv(pl.skewK + p->k[s], 64) : 0;
-      if (kpair_applies(p, tiles128, nk)) __atomic_fetch_add(&g_kpair_products, 1, __ATOMIC_RELAXED);
-    }
+    if (pl.small) __atomic_fetch_add(&g_small_products, 1, __ATOMIC_RELAXED);
     if (pl.dma && pl.bm == 128 && kpair_applies(p, out_tiles, a.ntiles)) {
       double us;
       a.kpair = 1;

@@ -36,12 +36,11 @@ int hap_gelu_bwd_grouped(int groups, int64_t rows, int64_t cols, int io_dtype, c
  * the engine has run in pieces so far in this process.  Process-wide, not thread-safe. */
 int64_t hap_debug_set_gemm_view_limit(int64_t bytes);
 
-/* Test hooks, not part of the public interface: how many products so far in this process were of the kind that gemm_kpair_kernel is for
- * (few 128-tiles, whose contraction the waves of a workgroup share), and how many the engine has handed to gemm_small_kernel, which
- * takes the smallest of them in its place; so that a test can state which products it reaches them with. */
+/* Test hooks, not part of the public interface: how many products so far in this process ran in gemm_kpair_kernel, gemm_small_kernel and
+ * gemm_trio_kernel, so that a test can state which products it reaches them with. */
 int64_t hap_debug_kpair_products(void);
 int64_t hap_debug_small_products(void);
-int64_t hap_debug_trio_products(void);      /* ... to gemm_trio_kernel */
+int64_t hap_debug_trio_products(void);
 
 #ifdef __cplusplus
 }

@@ -228,33 +228,51 @@ def test_linear_big_tiles_over_short_contractions(hap, k):
     run_linear_case(hap, "bf16", k + 150, 3904, 4040, 0, [0, k, k + 150], act=False, bias=True, full=True)
 
 
+def kernel_counts(hap):
+    """Products so far in gemm_kpair_kernel, gemm_small_kernel and gemm_trio_kernel."""
+    return np.array([hap.hap_debug_kpair_products(), hap.hap_debug_small_products(), hap.hap_debug_trio_products()])
+
+
 @pytest.mark.parametrize("k", [193, 256, 257, 385, 449, 768])
-def test_linear_few_tiles_share_their_contraction_between_wave_groups(hap, k):
-    """Outputs of few 128-tiles over ranges that start and end inside a K tile: the two wave groups of a workgroup contract the same and
-    different numbers of K tiles (4 to 13 of 64, odd and even), in all three products; the forward without a workspace (contraction
-    whole), the backward with one (also split over workgroups).  The counts say how many of a call's products reach the kernel.  (Every
-    group has work here; a group without any needs a contraction that is shortened on the device, as in test_moe_few_experts_split_k.)"""
-    def reached(want, *args, **kw):
-        before = hap.hap_debug_kpair_products()
+def test_linear_smallest_outputs_over_ranges_inside_a_k_tile(hap, k):
+    """The smallest outputs over ranges that start and end inside a K tile: the eight waves of a workgroup contract the same and different
+    numbers of K steps (7 to 32 of 32), in all three products, without a workspace (forward) and with one (backward)."""
+    def reached(*args, **kw):
+        before = kernel_counts(hap)
         run_linear_case(hap, "bf16", *args, full=True, **kw)
-        assert hap.hap_debug_kpair_products() - before == want, (args, want)
-    # per shard: forward over k or 1000 - k columns of X, dX over 200; dW contracts 130 rows, too few
-    reached(4, 130, 1000, 200, 2, [0, k, 1000], act=False, bias=False)
-    # dX over 264, dW over k or 1000 - k rows; the forward contracts 136
-    reached(4, 1000, 136, 264, 0, [0, k, 1000], act=True, bias=True, dw_dtype="f32")
-    # dX over k or 1000 - k columns of dY and W, straight from the whole tensors and from the activation backward's copy
-    reached(2, 130, 136, 1000, 1, [0, k, 1000], act=False, bias=True)
-    reached(2, 130, 136, 1000, 1, [0, k, 1000], act=True, bias=True)
+        assert (kernel_counts(hap) - before == [0, 6, 0]).all(), args
+    reached(130, 1000, 200, 2, [0, k, 1000], act=False, bias=False)
+    reached(1000, 136, 264, 0, [0, k, 1000], act=True, bias=True, dw_dtype="f32")
+    reached(130, 136, 1000, 1, [0, k, 1000], act=False, bias=True)
+    reached(130, 136, 1000, 1, [0, k, 1000], act=True, bias=True)
 
 
-@pytest.mark.parametrize("k", [193, 320, 449])
-def test_linear_paired_wave_groups_beyond_the_smallest_outputs(hap, k):
-    """The same ranges for outputs of more than 256 tiles of 64 x 64, which the kernel of the smallest outputs leaves to the paired wave
-    groups: per call the forward contracts k or 1000 - k features, bwd-data as many columns, bwd-weight as many rows."""
-    for mode, args in [(2, (1300, 1000, 1016)), (1, (1300, 1016, 1000)), (0, (1000, 1304, 1016))]:
-        before = hap.hap_debug_kpair_products() - hap.hap_debug_small_products()
-        run_linear_case(hap, "bf16", *args, mode, [0, k, 1000], act=False, bias=mode == 1, full=True)
-        assert hap.hap_debug_kpair_products() - hap.hap_debug_small_products() - before >= 2, (mode, k)
+@pytest.mark.parametrize("k", [193, 256, 257, 320, 385, 449, 768])
+def test_linear_few_tiles_share_their_contraction_between_wave_groups(hap, k):
+    """Outputs of few 128-tiles, but more than 256 tiles of 64 x 64 (the smallest outputs have a kernel of their own), over ranges that start
+    and end inside a K tile: the two wave groups of a workgroup contract the same and different numbers of K tiles (4 to 13 of 64, odd
+    and even).  Per shard one product contracts k or 1000 - k and has an output of 88 tiles; the others take this kernel or that of the
+    smallest outputs.  (A group without any K tile needs a contraction that is shortened on the device: test_moe_few_tiles_per_expert.)"""
+    def reached(*args, **kw):
+        before = kernel_counts(hap)
+        run_linear_case(hap, "bf16", *args, full=True, **kw)
+        pair, small, trio = kernel_counts(hap) - before
+        assert pair >= 2 and pair + small == 6, (args, pair, small, trio)
+    reached(1300, 1000, 1016, 2, [0, k, 1000], act=False, bias=False)      # forward over k features
+    reached(1300, 1016, 1000, 1, [0, k, 1000], act=True, bias=True)        # dX over k columns of the activation backward's copy
+    reached(1300, 1016, 1000, 1, [0, k, 1000], act=False, bias=True)       # ... of the whole dY
+    reached(1000, 1304, 1016, 0, [0, k, 1000], act=True, bias=True, dw_dtype="f32")    # dW over k rows
+
+
+@pytest.mark.parametrize("k", [200, 264, 520, 1000])
+def test_linear_paired_wave_groups_with_bias_gelu_and_preactivation(hap, k):
+    """The forward's epilogue in the kernel of the paired wave groups: bias, GeLU and the pre-activation copy of unsplit contractions of 4 to 16
+    K tiles, into columns on and off the output's 16-byte grid and into a compact slice."""
+    for args, kw in [((1300, k, 2040, 1, [0, 1003, 2040]), dict(full=True)), ((1300, k, 2040, 1, [0, 1000, 2040]), dict(full=True)), ((1300, k, 1016, 3, [0, 1]), dict(full=False))]:
+        shards = len(args[4]) - 1
+        before = kernel_counts(hap)
+        run_linear_case(hap, "bf16", *args, act=True, bias=True, **kw)
+        assert kernel_counts(hap)[0] - before[0] >= shards, (args, kernel_counts(hap) - before)
 
 
 @pytest.mark.parametrize("k", [8, 24, 32, 40, 96, 104, 200, 328, 520])
@@ -308,44 +326,43 @@ def test_linear_smallest_outputs_route(hap):
 
 
 @pytest.mark.parametrize("scratch", [True, False])
-@pytest.mark.parametrize("cut", [128, 333, 517])
-@pytest.mark.parametrize("tokens,out_f", [(130, 264), (1000, 1104), (140, 1600)])
-def test_linear_bwd_data_of_paired_wave_groups_into_column_ranges(hap, tokens, out_f, cut, scratch):
+@pytest.mark.parametrize("tokens,in_f,cut", [(130, 1000, 128), (130, 1000, 333), (130, 1000, 517), (1000, 1000, 128), (1000, 1000, 333), (1000, 1000, 517),
+                                             (1300, 2040, 1000), (1300, 2040, 1003), (1300, 2040, 1037)])
+@pytest.mark.parametrize("out_f", [264, 1104, 1600])
+def test_linear_bwd_data_into_column_ranges(hap, tokens, in_f, cut, out_f, scratch):
     """bwd-data of a reduction shard of whole tensors: its columns of dX start on and off the output's 16-byte grid (`cut`), its rows of W
-    with them; contractions of 5, 18 and 25 K tiles, up to 8 x 5 output tiles, plain and with the producer's gelu' in the epilogue."""
+    with them; contractions of 5, 18 and 25 K tiles, plain and with the producer's gelu' in the epilogue.  1300 tokens (11 x 8 and 11 x 9 tiles of 128)
+    take the kernel of the paired wave groups, fewer that of the smallest outputs, with a workspace and without."""
     from oracle import pointwise as opw
-    in_f = 1000
     offsets = [0, cut, in_f]
     Xh, Xd = gen(13, T.X, (tokens, in_f), 1.0, "bf16"); Wh, Wd = gen(13, T.W, (in_f, out_f), 0.05, "bf16")
     dYh, dYd = gen(13, T.DY, (tokens, out_f), 1.0, "bf16"); Ph, Pd = gen(13, T.MISC, (tokens, in_f), 1.5, "bf16")
     desc = hap.LinearDesc(tokens, in_f, out_f, olin.REDUCTION, offsets, hap.BF16)
-    tiles_m = -(-tokens // 128)
     for j in range(2):
         lo, hi = offsets[j], offsets[j + 1]
         want, _, _ = olin.sharded_linear_bwd(olin.REDUCTION, offsets, j, Xh, Wh, None, dYh, False)
         ws = empty((hap.hap_linear_bwd_workspace(desc, j),), "u8") if scratch else None
         for act in (False, True):
             dX = empty((tokens, in_f), "bf16", float("nan"))
-            before = hap.hap_debug_kpair_products()
+            before = kernel_counts(hap)
             hap.hap_sharded_linear_bwd_dact(desc, j, Xd, Wd, None, dYd, dX, None, hap.BF16, None, Pd if act else None, hap.ACT_GELU_ERF if act else hap.ACT_NONE, ws)
-            taken = hap.hap_debug_kpair_products() - before
+            taken = kernel_counts(hap) - before
             got = host(dX)
             check(f"dX act{int(act)} shard {j}", got[:, lo:hi], want * opw.gelu_grad(Ph[:, lo:hi]) if act else want, "bf16")
             assert np.isnan(got[:, :lo]).all() and np.isnan(got[:, hi:]).all(), "columns outside the shard were written"
-            # 18 K tiles of at most 32 output tiles stay with the 4-wave kernel where a workspace lets that split K
-            few = tiles_m * -(-(hi - lo + 7) // 128) <= 32
-            assert taken == (0 if scratch and few and out_f == 1104 else 1), (tokens, out_f, lo, hi, taken)
+            assert (taken == ([1, 0, 0] if tokens == 1300 else [0, 1, 0])).all(), (lo, hi, taken)
 
 
 @pytest.mark.parametrize("scratch", [0, 1 << 16, None])
 def test_linear_route_to_the_paired_wave_groups(hap, scratch):
     """Products of at most one 128-tile per compute unit and at least four K tiles take the kernel with two wave groups, whatever the
     workspace holds (nothing, too little for a single split, everything): few tiles over a short contraction, poorly filled tile counts
-    over a long one.  Fewer K tiles or more output tiles do not."""
+    over a long one.  Fewer K tiles or more output tiles do not, and neither do the smallest outputs."""
     torch = torch_mod()
     cus, _ = hap.hap_device_info()
     assert cus == 256
-    for tokens, in_f, out_f, want in [(250, 880, 500, [1, 1, 1]),         # 2 x 4 output tiles over 14 K tiles, 2 x 7 over 8, 7 x 4 over 4
+    for tokens, in_f, out_f, want in [(250, 880, 500, [0, 0, 0]),         # at most 14 x 8 tiles of 64
+                                      (1300, 1016, 1104, [1, 1, 1]),       # 11 x 9 output tiles over 16 K tiles, 11 x 8 over 18, 8 x 9 over 21
                                       (1270, 4090, 1140, [1, 0, 0])]:      # 10 x 9 over 64; 10 x 32 and 32 x 9 tiles are too many
         Xh, Xd = gen(3, T.X, (tokens, in_f), 1.0, "bf16"); Wh, Wd = gen(3, T.W, (in_f, out_f), 0.05, "bf16"); Gh, Gd = gen(3, T.DY, (tokens, out_f), 1.0, "bf16")
         ld = lambda n: (n + 7) // 8 * 8
@@ -361,7 +378,7 @@ def test_linear_route_to_the_paired_wave_groups(hap, scratch):
         hap.hap_sharded_linear_bwd(desc, 0, Xd, Wd, None, Gd, None, dW, hap.BF16, None, ws); n.append(hap.hap_debug_kpair_products())
         check("route Y", host(Y)[:, :out_f], Yo, "bf16"); check("route dX", host(dX)[:, :in_f], dXo, "bf16"); check("route dW", host(dW)[:, :out_f], dWo, "bf16")
         assert [b - a for a, b in zip(n, n[1:])] == want, (tokens, in_f, out_f, n)
-    for tokens, in_f, out_f in [(250, 190, 500), (17 * 128, 256, 16 * 128)]:  # 3 K tiles; 17 x 16 output tiles
+    for tokens, in_f, out_f in [(1300, 190, 1000), (17 * 128, 256, 16 * 128)]:  # 3 K tiles; 17 x 16 output tiles
         Xd, Wd, Y = empty((tokens, 256), "bf16", 0), empty((in_f, 2048), "bf16", 0), empty((tokens, 2048), "bf16", 1)
         desc = hap.LinearDesc(tokens, in_f, out_f, hap.REPLICATED, [0, 1], hap.BF16, ldx=256, ldw=2048, ldy=2048, m=1)
         before = hap.hap_debug_kpair_products()

@@ -191,3 +191,18 @@ def test_moe_few_experts_split_k(hap, dtype):
     split over workgroups - also where the token count (known only on the device) leaves some workgroups without any K tile."""
     run_moe_case(hap, dtype, 2, 1024, 256, 384, [0, 1, 2], [700, 130], act=True, bias=True, full=True, fwd_ws=True)
     run_moe_case(hap, dtype, 3, 1024, 512, 128, [0, 1, 3], [0, 1024, 65], act=False, bias=True, full=False, fwd_ws=True, dw_dtype="f32")
+
+
+@pytest.mark.parametrize("full", [True, False])
+def test_moe_few_tiles_per_expert(hap, full):
+    """Experts whose outputs together are at most 256 tiles of 128 x 128, but more than 256 of 64 x 64: all three grouped products take the kernel
+    whose two wave groups share a tile's contraction, which the weight gradient's token count shortens on the device - to nothing, to
+    one K tile (the second group has none), to two, to an odd number - and, over long buffers, splits over workgroups, most of them without any K tile."""
+    def reached(want, *args, **kw):
+        before = hap.hap_debug_kpair_products()
+        run_moe_case(hap, "bf16", *args, bias=True, full=full, fwd_ws=True, **kw)
+        assert hap.hap_debug_kpair_products() - before == want, args
+    reached(3, 4, 1024, 1000, 1016, [0, 4], [0, 1024, 40, 65], act=True)
+    reached(3, 3, 1000, 1096, 1000, [0, 3], [1000, 449, 1], act=False, dw_dtype="f32")
+    reached(1, 1, 6400, 1096, 1000, [0, 1], [130], act=True)
+    reached(1, 1, 6400, 1096, 1000, [0, 1], [4900], act=True, dw_dtype="f32")
