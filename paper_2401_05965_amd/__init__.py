@@ -14,5 +14,5 @@ from .binding import (  # noqa: F401
     hap_layernorm_fwd, hap_layernorm_bwd, hap_layernorm_bwd_workspace, hap_layernorm_bwd_sums, hap_layernorm_bwd_sums_workspace,
     hap_moe_linear_fwd, hap_moe_linear_bwd, hap_moe_linear_bwd_dact, hap_moe_linear_fwd_workspace, hap_moe_linear_bwd_workspace,
     hap_allgather_capacity, hap_allgather_pad, hap_allgather_assemble, hap_reducescatter_split,
-    hap_gelu_bwd, hap_add, hap_colsum, hap_colsum_workspace, hap_probe_mfma_bf16, hap_debug_set_gemm_view_limit, hap_debug_kpair_products, hap_debug_small_products, hap_debug_trio_products, hap_device_info,
+    hap_gelu_bwd, hap_add, hap_colsum, hap_colsum_workspace, hap_probe_mfma_bf16, hap_debug_set_gemm_view_limit, hap_debug_kpair_products, hap_debug_small_products, hap_debug_trio_products, hap_debug_split_products, hap_device_info,
 )

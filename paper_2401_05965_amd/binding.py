@@ -135,6 +135,7 @@ lib.hap_debug_set_gemm_view_limit.restype = C.c_int64
 lib.hap_debug_kpair_products.restype = C.c_int64
 lib.hap_debug_small_products.restype = C.c_int64
 lib.hap_debug_trio_products.restype = C.c_int64
+lib.hap_debug_split_products.restype = C.c_int64
 lib.hap_allgather_capacity.restype = C.c_int64
 for _n in ("hap_linear_fwd_workspace", "hap_linear_bwd_workspace", "hap_sfb_workspace", "hap_attn_bwd_workspace",
            "hap_layernorm_bwd_workspace", "hap_layernorm_bwd_sums_workspace", "hap_colsum_workspace", "hap_moe_linear_fwd_workspace", "hap_moe_linear_bwd_workspace"):
@@ -543,6 +544,11 @@ def hap_debug_small_products() -> int:
 def hap_debug_trio_products() -> int:
     """Testing aid: how many products the GEMM engine has handed to gemm_trio_kernel so far."""
     return int(lib.hap_debug_trio_products())
+
+
+def hap_debug_split_products() -> int:
+    """Testing aid: how many products the GEMM engine has split over workgroups, with a reduction launch behind them, so far."""
+    return int(lib.hap_debug_split_products())
 
 
 def hap_device_info():

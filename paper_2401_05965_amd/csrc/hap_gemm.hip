@@ -671,12 +671,13 @@ using namespace hap_gemm_detail;
 static int64_t g_view_limit = kViewLimitBytes;
 static int64_t g_cut_products = 0;      // products run in pieces so far (testing aid, not synchronised)
 
-// Launches of gemm_kpair_kernel, gemm_small_kernel and gemm_trio_kernel so far (testing aid)
-static int64_t g_kpair_products = 0, g_small_products = 0, g_trio_products = 0;
+// Launches of gemm_kpair_kernel, gemm_small_kernel, gemm_trio_kernel and splitk_reduce_kernel so far (testing aid)
+static int64_t g_kpair_products = 0, g_small_products = 0, g_trio_products = 0, g_split_products = 0;
 
 extern "C" int64_t hap_debug_kpair_products(void) { return __atomic_load_n(&g_kpair_products, __ATOMIC_RELAXED); }
 extern "C" int64_t hap_debug_small_products(void) { return __atomic_load_n(&g_small_products, __ATOMIC_RELAXED); }
 extern "C" int64_t hap_debug_trio_products(void) { return __atomic_load_n(&g_trio_products, __ATOMIC_RELAXED); }
+extern "C" int64_t hap_debug_split_products(void) { return __atomic_load_n(&g_split_products, __ATOMIC_RELAXED); }
 
 /* Test hook (declared in hap_internal.h, not part of the public interface): lowers the reach at which operand views are
  * cut so the cutting can be exercised on small inputs; returns how many products have run in pieces so far. */
@@ -1068,7 +1069,10 @@ int hap_gemm_run(const hap_gemm_problem* p, void* stream) {
       __atomic_fetch_add(&g_trio_products, 1, __ATOMIC_RELAXED);
       return run_trio(p, a, groups, st);
     }
-    if (a.ksplit > 1) a.partial = static_cast<float*>(p->ws);
+    if (a.ksplit > 1) {
+      a.partial = static_cast<float*>(p->ws);
+      __atomic_fetch_add(&g_split_products, 1, __ATOMIC_RELAXED);
+    }
   }
   if (p->in_dtype == HAP_BF16 && p->c_dtype == HAP_BF16) return dispatch_tile<__bf16, __bf16>(p, pl, a, groups, st);
   if (p->in_dtype == HAP_BF16) return dispatch_tile<__bf16, float>(p, pl, a, groups, st);

@@ -37,10 +37,11 @@ int hap_gelu_bwd_grouped(int groups, int64_t rows, int64_t cols, int io_dtype, c
 int64_t hap_debug_set_gemm_view_limit(int64_t bytes);
 
 /* Test hooks, not part of the public interface: how many products so far in this process ran in gemm_kpair_kernel, gemm_small_kernel and
- * gemm_trio_kernel, so that a test can state which products it reaches them with. */
+ * gemm_trio_kernel, and how many split their contraction over workgroups, so that a test can state which products it reaches them with. */
 int64_t hap_debug_kpair_products(void);
 int64_t hap_debug_small_products(void);
 int64_t hap_debug_trio_products(void);
+int64_t hap_debug_split_products(void);
 
 #ifdef __cplusplus
 }

@@ -444,11 +444,13 @@ def test_sfb_ragged_segments_padding_never_read(hap):
     assert not host(dW1).any()
 
 
-def test_sfb_split_k_over_segment_boundaries(hap):
-    """With workspace the engine splits the contracted axis over idle compute units; the split points fall
-    inside and between the devices' ragged segments.  Result must equal the one-pass result."""
-    rows = [300, 0, 77, 512, 130]
-    cap, in_f, out_f = 512, 264, 392
+# Outputs (rows, columns) and contractions that are split over workgroups where there is a workspace: the K-pair kernel in three, 128-tiles in
+# five (eight wave groups short of a full chip otherwise), 256-tiles in three.
+SPLITS = [(1000, 1096, 4104), (1000, 1304, 8200), (1800, 2200, 4104)]
+
+
+def run_sfb_case(hap, rows, in_f, out_f, splits):
+    cap = max(rows)
     Xh, Xd, dYh, dYd = [], [], [], []
     for i in range(len(rows)):
         a, b = gen(9, T.SFB_X + i, (cap, in_f), 1.0, "bf16"); Xh.append(a); Xd.append(b)
@@ -456,19 +458,120 @@ def test_sfb_split_k_over_segment_boundaries(hap):
         Xd[i][rows[i]:] = float("nan"); dYd[i][rows[i]:] = float("nan")
     ref = osfb.sfb_grad(Xh, dYh, rows)
     ws = empty((hap.hap_sfb_workspace(len(rows), rows, in_f, out_f),), "u8")
+    n = [hap.hap_debug_split_products()]
     dW = empty((in_f, out_f), "f32", float("nan"))
-    hap.hap_sfb_grad(Xd, dYd, rows, in_f, out_f, in_f, out_f, hap.BF16, dW, out_f, ws=ws)
-    check("sfb split-k", host(dW), ref, "bf16")
+    hap.hap_sfb_grad(Xd, dYd, rows, in_f, out_f, in_f, out_f, hap.BF16, dW, out_f, ws=ws); n.append(hap.hap_debug_split_products())
+    check("sfb with a workspace", host(dW), ref, "bf16")
     dW1 = empty((in_f, out_f), "f32", float("nan"))
-    hap.hap_sfb_grad(Xd, dYd, rows, in_f, out_f, in_f, out_f, hap.BF16, dW1, out_f)
+    hap.hap_sfb_grad(Xd, dYd, rows, in_f, out_f, in_f, out_f, hap.BF16, dW1, out_f); n.append(hap.hap_debug_split_products())
     assert np.abs(host(dW1) - host(dW)).max() <= 1e-5 * np.abs(ref).max()      # fp32 partial sums, different order only
-    hap.hap_sfb_grad(Xd, dYd, rows, in_f, out_f, in_f, out_f, hap.BF16, dW, out_f, accumulate=True, ws=ws)
-    check("sfb split-k accumulate", host(dW), 2 * ref, "bf16")
+    hap.hap_sfb_grad(Xd, dYd, rows, in_f, out_f, in_f, out_f, hap.BF16, dW, out_f, accumulate=True, ws=ws); n.append(hap.hap_debug_split_products())
+    check("sfb accumulate", host(dW), 2 * ref, "bf16")
+    # a pitch and a base off the 16-byte grid: element by element
+    flat = empty((in_f * (out_f + 3) + 1,), "f32", 5)
+    hap.hap_sfb_grad(Xd, dYd, rows, in_f, out_f, in_f, out_f, hap.BF16, flat.data_ptr() + 4, out_f + 3, accumulate=True, ws=ws); n.append(hap.hap_debug_split_products())
+    got = host(flat)
+    assert got[0] == 5 and (got[1:].reshape(in_f, out_f + 3)[:, out_f:] == 5).all()
+    check("sfb off the grid", got[1:].reshape(in_f, out_f + 3)[:, :out_f], 5 + ref, "bf16")
+    assert [b - a for a, b in zip(n, n[1:])] == ([1, 0, 1, 1] if splits else [0, 0, 0, 0])
 
 
-def test_linear_split_k_with_bias_gelu_and_ragged_view(hap):
-    """Deep contraction, few output tiles, bias + GeLU + saved pre-activation, misaligned column range:
-    the forward goes through split-K when given workspace."""
+@pytest.mark.parametrize("in_f,out_f,k", SPLITS)
+def test_sfb_split_k_over_segment_boundaries(hap, in_f, out_f, k):
+    """With workspace the engine splits the contracted axis over idle compute units; the split points fall
+    inside and between the devices' ragged segments.  Result must equal the one-pass result."""
+    run_sfb_case(hap, [k // 3 + 5, 0, 77, k // 2, k - k // 3 - k // 2 - 82], in_f, out_f, True)
+
+
+def test_sfb_of_the_smallest_outputs_over_ragged_segments(hap):
+    """Eight waves share a tile's contraction; their ranges start and end inside and between the segments, whatever the workspace."""
+    run_sfb_case(hap, [300, 0, 77, 512, 130], 264, 392, False)
+
+
+@pytest.mark.parametrize("m,n,k", SPLITS)
+@pytest.mark.parametrize("dn", [0, 2, 5])
+@pytest.mark.parametrize("y_phase,p_phase", [(0, 0), (4, 4), (3, 3), (0, 2)])
+def test_linear_split_k_with_bias_gelu_and_preactivation(hap, m, n, k, dn, y_phase, p_phase):
+    """The reduction behind a forward that is split over workgroups: bias, GeLU and the saved pre-activation, with columns that are and are not
+    a multiple of four and output rows that start on the 8-byte grid (whole quads) and off it (elements)."""
+    n -= dn
+    Xh, Xd = gen(5, T.X, (m, k), 1.0, "bf16"); Wh, Wd = gen(5, T.W, (k, n), 0.05, "bf16"); bh, bd = gen(5, T.BIAS, (n,), 0.5, "bf16")
+    ld = (n + 7) // 8 * 8
+    Wd = torch_mod().nn.functional.pad(Wd, (0, ld - n), value=float("nan"))
+    desc = hap.LinearDesc(m, k, n, hap.REPLICATED, [0, 1], hap.BF16, act=hap.ACT_GELU_ERF, has_bias=True, ldx=k, ldw=ld, ldy=ld, m=1)
+    ws = empty((hap.lib.hap_linear_fwd_workspace(None, 0),), "u8")
+    Y, P = empty((m * ld + 8,), "bf16", 9), empty((m * ld + 8,), "bf16", 9)
+    before = hap.hap_debug_split_products()
+    hap.hap_sharded_linear_fwd(desc, 0, Xd, Wd, bd, Y.data_ptr() + 2 * y_phase, P.data_ptr() + 2 * p_phase, ws)
+    assert hap.hap_debug_split_products() - before == 1
+    Yo, preo = olin.linear_fwd(Xh, Wh, bh, True)
+    for name, t, phase, want in (("Y", Y, y_phase, Yo), ("preact", P, p_phase, preo)):
+        got = host(t)
+        assert (got[:phase] == 9).all() and (got[phase + m * ld:] == 9).all(), name
+        got = got[phase:phase + m * ld].reshape(m, ld)
+        assert (got[:, n:] == 9).all(), "the pitch's padding was written"
+        check("split-k " + name, got[:, :n], want, "bf16")
+
+
+@pytest.mark.parametrize("m,n,k", SPLITS[:2])
+@pytest.mark.parametrize("cut", [0, 3, 8])
+def test_linear_split_k_with_activation_backward_into_column_ranges(hap, m, n, k, cut):
+    """The reduction behind a split bwd-data with the producer's gelu', into columns of a whole tensor that start on and off the 16-byte grid;
+    without a workspace the same product in one pass, and the weight gradient of the same shard split over the same rows."""
+    from oracle import pointwise as opw
+    Xh, Xd = gen(13, T.X, (m, n), 1.0, "bf16"); Wh, Wd = gen(13, T.W, (n, k), 0.05, "bf16")
+    dYh, dYd = gen(13, T.DY, (m, k), 1.0, "bf16"); Ph, Pd = gen(13, T.MISC, (m, n), 1.5, "bf16")
+    desc = hap.LinearDesc(m, n, k, olin.REDUCTION, [0, cut, n], hap.BF16)
+    want, _, _ = olin.sharded_linear_bwd(olin.REDUCTION, [0, cut, n], 1, Xh, Wh, None, dYh, False)
+    for scratch in (True, False):
+        dX = empty((m, n), "bf16", float("nan"))
+        before = hap.hap_debug_split_products()
+        hap.hap_sharded_linear_bwd_dact(desc, 1, Xd, Wd, None, dYd, dX, None, hap.BF16, None, Pd, hap.ACT_GELU_ERF,
+                                        empty((hap.hap_linear_bwd_workspace(desc, 1),), "u8") if scratch else None)
+        assert hap.hap_debug_split_products() - before == int(scratch)
+        got = host(dX)
+        assert np.isnan(got[:, :cut]).all()
+        check(f"dP scratch {scratch}", got[:, cut:], want * opw.gelu_grad(Ph[:, cut:]), "bf16")
+
+
+@pytest.mark.parametrize("m,n,k", SPLITS)
+@pytest.mark.parametrize("dw_dtype", ["bf16", "f32"])
+def test_linear_split_k_weight_gradient_into_column_ranges(hap, m, n, k, dw_dtype):
+    """Weight gradients split over workgroups, into a whole tensor's columns off the 16-byte grid."""
+    Xh, Xd = gen(4, T.X, (k, m), 1.0, "bf16"); dYh, dYd = gen(4, T.DY, (k, n), 1.0, "bf16")
+    W = empty((m, n), "bf16", 0)
+    desc = hap.LinearDesc(k, m, n, olin.FEATURE, [0, 3, n], hap.BF16)
+    dW = empty((m, n), dw_dtype, 9)
+    before = hap.hap_debug_split_products()
+    hap.hap_sharded_linear_bwd(desc, 1, Xd, W, None, dYd, None, dW, DT[dw_dtype], None, empty((hap.hap_linear_bwd_workspace(desc, 1),), "u8"))
+    assert hap.hap_debug_split_products() - before == 1
+    assert (host(dW)[:, :3] == 9).all()
+    check("dW", host(dW)[:, 3:], Xh.T @ dYh[:, 3:], dw_dtype if dw_dtype == "bf16" else "bf16")
+
+
+@pytest.mark.parametrize("scratch", [True, False])
+def test_fp32_split_k_with_workspace(hap, scratch):
+    """fp32 products whose 64-tiles cannot occupy the chip and whose rows are too many for the kernels of the few-row layers: split over
+    workgroups where there is a workspace (forward with bias + GeLU, bwd-data, a weight gradient over many rows); same 1e-5 bar."""
+    for tokens, in_f, out_f, want in [(512, 2048, 512, (1, 1, 0)), (700, 3000, 520, (1, 0, 0)), (4100, 264, 260, (1, 1, 1))]:
+        Xh, Xd = gen(0, T.X, (tokens, in_f), 1.0, "f32"); Wh, Wd = gen(0, T.W, (in_f, out_f), 0.02, "f32"); dYh, dYd = gen(0, T.DY, (tokens, out_f), 1.0, "f32")
+        bh, bd = gen(0, T.BIAS, (out_f,), 0.5, "f32")
+        fwd = hap.LinearDesc(tokens, in_f, out_f, hap.REPLICATED, [0, 1], hap.F32, act=hap.ACT_GELU_ERF, has_bias=True, m=1)
+        bwd = hap.LinearDesc(tokens, in_f, out_f, hap.REPLICATED, [0, 1], hap.F32, m=1)
+        ws = empty((hap.hap_linear_bwd_workspace(bwd, 0),), "u8") if scratch else None
+        nan = float("nan")
+        Y, P, dX, dW = empty((tokens, out_f), "f32", nan), empty((tokens, out_f), "f32", nan), empty((tokens, in_f), "f32", nan), empty((in_f, out_f), "f32", nan)
+        n = [hap.hap_debug_split_products()]
+        hap.hap_sharded_linear_fwd(fwd, 0, Xd, Wd, bd, Y, P, ws); n.append(hap.hap_debug_split_products())
+        hap.hap_sharded_linear_bwd(bwd, 0, Xd, Wd, None, dYd, dX, None, hap.F32, None, ws); n.append(hap.hap_debug_split_products())
+        hap.hap_sharded_linear_bwd(bwd, 0, Xd, Wd, None, dYd, None, dW, hap.F32, None, ws); n.append(hap.hap_debug_split_products())
+        Yo, Po = olin.linear_fwd(Xh, Wh, bh, True); dXo, dWo, _ = olin.linear_bwd(Xh, Wh, None, dYh)
+        check("Y", host(Y), Yo, "f32"); check("preact", host(P), Po, "f32"); check("dX", host(dX), dXo, "f32"); check("dW", host(dW), dWo, "f32")
+        assert tuple(b - a for a, b in zip(n, n[1:])) == (want if scratch else (0, 0, 0)), (tokens, in_f, out_f, n)
+
+
+def test_linear_smallest_outputs_with_bias_gelu_and_ragged_view(hap):
+    """Deep contraction, few output tiles, bias + GeLU + saved pre-activation, misaligned column range, into one pair of whole tensors."""
     tokens, in_f, out_f = 200, 1024, 520
     offs = [0, 137, 391, 520]
     Xh, Xd = gen(5, T.X, (tokens, in_f), 1.0, "bf16"); Wh, Wd = gen(5, T.W, (in_f, out_f), 0.05, "bf16")
@@ -479,12 +582,12 @@ def test_linear_split_k_with_bias_gelu_and_ragged_view(hap):
     Y = empty((tokens, out_f), "bf16", 0); P = empty((tokens, out_f), "bf16", 0)
     for j in range(3):
         hap.hap_sharded_linear_fwd(desc, j, Xd, Wd, bd, Y, P, ws)
-    check("split-k Y", host(Y), Yo, "bf16"); check("split-k preact", host(P), preo, "bf16")
+    check("Y", host(Y), Yo, "bf16"); check("preact", host(P), preo, "bf16")
 
 
-def test_cfg1_fp32_split_k_with_workspace(hap):
-    """Config 1 again with workspace: 16 output tiles cannot occupy the chip, so the fp32 kernel splits its 16 K tiles
-    over more workgroups (fp32 partial tiles + reduction); same 1e-5 bar, forward with bias + GeLU and both gradients."""
+def test_cfg1_fp32_with_workspace(hap):
+    """Config 1 again with workspace, which neither the kernel of few rows nor the one launch of the backward needs; same 1e-5 bar, forward
+    with bias + GeLU and all gradients."""
     offs = [0, 38, 64]
     Xh, Xd = gen(0, T.X, (64, 1024), 1.0, "f32"); Wh, Wd = gen(0, T.W, (1024, 1024), 0.02, "f32"); dYh, dYd = gen(0, T.DY, (64, 1024), 1.0, "f32")
     bh, bd = gen(0, T.BIAS, (1024,), 0.5, "f32")
@@ -500,8 +603,8 @@ def test_cfg1_fp32_split_k_with_workspace(hap):
         hap.hap_sharded_linear_bwd(desc, j, Xd, Wd, P, dYd, dX, dW, hap.F32, db, wsb)
         dW_sum += host(dW); db_sum += host(db)
     dXo, dWo, dbo = olin.linear_bwd(Xh, Wh, Po, dYh, act=True)
-    check("cfg1 split-k Y", host(Y), Yo, "f32"); check("cfg1 split-k preact", host(P), Po, "f32")
-    check("cfg1 split-k dX", host(dX), dXo, "f32"); check("cfg1 split-k dW", dW_sum, dWo, "f32"); check("cfg1 split-k db", db_sum, dbo, "f32")
+    check("cfg1 Y", host(Y), Yo, "f32"); check("cfg1 preact", host(P), Po, "f32")
+    check("cfg1 dX", host(dX), dXo, "f32"); check("cfg1 dW", dW_sum, dWo, "f32"); check("cfg1 db", db_sum, dbo, "f32")
 
 
 def test_linear_seeded_random_sweep(hap):
