@@ -278,7 +278,8 @@ def test_linear_paired_wave_groups_with_bias_gelu_and_preactivation(hap, k):
 @pytest.mark.parametrize("k", [8, 24, 32, 40, 96, 104, 200, 328, 520])
 def test_linear_short_contractions_of_many_tiles(hap, k):
     """More than 512 tiles of 128 x 128 over one to seventeen K steps of 32 (fewer than the ring has stages, as many, more), interior and cut
-    at both ends: the forward contracts k or 1040 - k features, bwd-data as many columns, with GeLU, its backward and without."""
+    at both ends: bwd-data over the first third of k columns, the rest and all, the forward over either half of k features and all, with GeLU,
+    its backward and without."""
     before = hap.hap_debug_trio_products()
     run_linear_case(hap, "bf16", 4300, 2104, k, 1, [0, k // 3, k], act=True, bias=True, full=True)        # dX over k // 3, k - k // 3
     run_linear_case(hap, "bf16", 4300, k, 2104, 2, [0, k // 2, k], act=False, bias=False, full=True)      # Y over k // 2
@@ -296,6 +297,24 @@ def test_linear_short_contractions_of_many_tiles(hap, k):
         got = host(dX)
         check(f"dP k{k} lo{lo}", got[:, lo:], want * opw.gelu_grad(Ph[:, lo:]), "bf16")
         assert np.isnan(got[:, :lo]).all()
+
+
+@pytest.mark.parametrize("k", [8, 24, 33, 64, 95, 104, 200, 329, 520, 770])
+def test_linear_weight_gradients_of_many_tiles_over_few_rows(hap, k):
+    """bf16 weight gradients of more than 512 tiles of 128 x 128 over one to 25 K steps of 32, into a compact slice and into a whole tensor's
+    columns off the 16-byte grid: both operands M- / N-contiguous, three workgroups to a compute unit."""
+    in_f, out_f = 2104, 4304
+    Xh, Xd = gen(4, T.X, (k, in_f), 1.0, "bf16"); dYh, dYd = gen(4, T.DY, (k, out_f), 1.0, "bf16")
+    W = empty((in_f, out_f), "bf16", 0)
+    for mode, offsets, j in ((hap.REPLICATED, [0, 1], 0), (olin.FEATURE, [0, 3, out_f], 1)):
+        lo = 3 if j else 0
+        desc = hap.LinearDesc(k, in_f, out_f, mode, offsets, hap.BF16, m=len(offsets) - 1)
+        dW = empty((in_f, out_f), "bf16", 9)
+        before = hap.hap_debug_trio_products()
+        hap.hap_sharded_linear_bwd(desc, j, Xd, W, None, dYd, None, dW, hap.BF16, None, empty((hap.hap_linear_bwd_workspace(desc, j),), "u8"))
+        assert hap.hap_debug_trio_products() - before == 1
+        assert (host(dW)[:, :lo] == 9).all()
+        check("dW", host(dW)[:, lo:], Xh.T @ dYh[:, lo:], "bf16")
 
 
 @pytest.mark.parametrize("tokens,in_f,out_f", [(1, 40, 24), (31, 72, 64), (33, 520, 65), (64, 32, 200), (65, 1000, 63), (197, 1024, 315), (250, 248, 1001), (450, 130, 1030), (1000, 3900, 260)])

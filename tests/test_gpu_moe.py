@@ -206,3 +206,40 @@ def test_moe_few_tiles_per_expert(hap, full):
     reached(3, 3, 1000, 1096, 1000, [0, 3], [1000, 449, 1], act=False, dw_dtype="f32")
     reached(1, 1, 6400, 1096, 1000, [0, 1], [130], act=True)
     reached(1, 1, 6400, 1096, 1000, [0, 1], [4900], act=True, dw_dtype="f32")
+
+
+@pytest.mark.parametrize("full", [True, False])
+def test_moe_many_tiles_over_short_contractions(hap, full):
+    """Grouped products of more than 256 tiles of 128 x 128 over short contractions run three workgroups to a compute unit: the forward with
+    ragged rows (0, 1, a tile and one, all) and the GeLU epilogue, the weight gradient over token counts of none, one, a K step of 32 and one
+    more, fewer steps than the ring has stages, and all."""
+    def reached(want, *args, **kw):
+        before = hap.hap_debug_trio_products()
+        run_moe_case(hap, "bf16", *args, bias=True, full=full, fwd_ws=True, **kw)
+        assert hap.hap_debug_trio_products() - before == want, args
+    reached(1, 10, 640, 512, 1280, [0, 10], [640, 0, 1, 129, 128, 300, 639, 512, 64, 333], act=True)       # forward
+    reached(1, 10, 200, 520, 1288, [0, 10], [200, 0, 1, 32, 33, 64, 95, 96, 97, 199], act=True)            # dW
+
+
+def test_moe_activation_backward_of_many_tiles(hap):
+    """The grouped gelu' epilogue in the kernel with three workgroups to a compute unit: the expert block of ten experts of 640 rows."""
+    from oracle import layers as olay, pointwise as opw
+    from paper_2401_05965_amd.programs import MoeExpertShard
+    torch = torch_mod()
+    E, C, Hd, F = 10, 640, 512, 1544
+    Xh, Xd = gen(6, T.X, (E, C, Hd), 1.0, "bf16"); dOh, dOd = gen(6, T.DY, (E, C, Hd), 1.0, "bf16")
+    W1h, W1d = gen(6, T.W, (E, Hd, F), 0.05, "bf16"); b1h, b1d = gen(6, T.BIAS, (E, F), 0.1, "bf16")
+    W2h, W2d = gen(6, T.W2, (E, F, Hd), 0.05, "bf16"); b2h, b2d = gen(6, T.BETA, (E, Hd), 0.1, "bf16")
+    rows = np.array([640, 0, 1, 129, 128, 300, 639, 512, 64, 333])
+    ref = olay.moe_ffn_block(Xh, W1h, b1h, W2h, b2h, dOh, rows)
+    ref["dP"] = ref["dH"] * opw.gelu_grad(ref["pre"])
+    live = np.arange(C)[None, :] < rows[:, None]
+    sh = MoeExpertShard(E, C, Hd, F, [0, E], 0, Xd, W1d, b1d, W2d, b2d, torch.from_numpy(rows.astype(np.int32)).cuda(), dOd)
+    sh.forward()
+    before = hap.hap_debug_trio_products()
+    sh.backward()
+    assert hap.hap_debug_trio_products() > before and sh.dH_holds == "dP"
+    for name, t in (("H", sh.H), ("out", sh.Out), ("dP", sh.dH), ("dX", sh.dX)):
+        check(name, host(t)[live], ref[name][live], "bf16")
+    for name, t in (("dW1", sh.dW1), ("db1", sh.db1), ("dW2", sh.dW2), ("db2", sh.db2)):
+        check(name, host(t), ref[name], "bf16")
