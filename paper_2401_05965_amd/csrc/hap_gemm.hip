@@ -369,7 +369,10 @@ __global__ __launch_bounds__(256) void gemm_generic_kernel(const GenericArgs g) 
 
 inline long long cdiv(long long a, long long b) { return (a + b - 1) / b; }
 
+constexpr size_t kSmallTileBytes = 128 * 128 * sizeof(float);     // a partial tile
+
 /* What the planner weighs the kernels by (below). */
+long long workgroup_splits(const hap_gemm_problem* p, long long tiles, long long slots, long long steps, int min_steps, size_t tile_bytes);
 bool kpair_applies(const hap_gemm_problem* p, long long tiles, long long nk);
 int kpair_splits(const hap_gemm_problem* p, long long tiles, long long nk, double* us);
 double us_256(const hap_gemm_problem* p, long long n, long long nk);
@@ -393,17 +396,34 @@ struct Plan {
  *   tiles of 32, forward:  197 x 1024 x 1260 13.6 -> 6.7    512 x 512 x 512 9.9 -> 5.6    400 x 1024 x 1024 12.2 -> 7.0 (208 tiles)
  *   tiles of 64:  forward 1024 x 1024 x 1024 12.4 -> 9.0, with GeLU 17.1 -> 10.7    bwd-weight 768 x 768 over 1500 rows 15.3 -> 8.9
  *   beyond 256 tiles of 64:  1500 x 768 x 768 11.5 -> 13.6 (288)    2000 x 640 x 1024 11.1 -> 14.4
- *   long contractions:  256 tiles of 64 over K = 3000 / 3940 / 4096 / 8192: 19.0 -> 14.8 / 20.1 -> 18.3 / 20.3 -> 21.1 / 26.4 -> 32.0; with half of the
- *   compute units or fewer 64 x 1024 over 4096 14.2 -> 11.1, 512 x 512 over 4096 17.1 -> 11.3 and 8192 19.9 -> 26.3 (64 x 512: 16.3 -> 17.0) */
+ * Long contractions end it where the others can split theirs (in steps of 32; 2500 random sizes, pitches and epilogues over 62 to 162 steps, time
+ * here over time there, geometric mean / worst):
+ *   tiles of 32:  up to 64 of them, 152 to 159 steps 0.85 / 1.16    65 to 128, 128 to 135 steps 0.82 / 1.02, 144 to 151 0.98 / 1.24
+ *                 beyond, 112 to 119 steps 0.90 / 1.00, 120 to 124 0.95 / 1.06
+ *   tiles of 64, forward and bwd-data:  88 to 95 steps 0.96 / 1.04, 96 to 103 1.00 / 1.10, 112 to 119 1.08 / 1.15
+ *   tiles of 64, bwd-weight:  up to 32 of them, 136 to 143 steps 0.95 / 1.08, 152 to 159 1.01 / 1.22    33 to 128, 104 to 111 steps 0.86 / 0.96, 112 to 119
+ *                 0.93 / 1.05, 128 to 135 0.98 / 1.14    beyond, 120 to 124 steps 0.95 / 1.01
+ * Without a workspace for their partial tiles they take 1.2 to 2.7 times as long as this kernel wherever it applies. */
 int small_rows(const hap_gemm_problem* p, const Plan& pl) {
   if (p->in_dtype != HAP_BF16 || p->tile == 256 || (!p->a_kcontig && p->b_kcontig)) return 0;
   const long long cus = cu_count(), groups = p->groups > 1 ? p->groups : 1;
-  long long steps = 0;
-  for (int s = 0; s < p->nseg; ++s) steps += p->k[s] > 0 ? (pl.skewK + p->k[s] + 31) / 32 : 0;
+  long long steps = 0, nk = 0;
+  for (int s = 0; s < p->nseg; ++s) {
+    if (p->k[s] <= 0) continue;
+    steps += (pl.skewK + p->k[s] + 31) / 32;
+    nk += (pl.skewK + p->k[s] + 63) / 64;
+  }
   const long long columns = groups * ((p->N + pl.skewN + 63) / 64);
   for (int bm = p->a_kcontig ? 32 : 64; bm <= 64; bm *= 2) {      // (an M-contiguous operand's LDS rows are 128 bytes or more)
     const long long tiles = columns * ((p->M + pl.skewM + bm - 1) / bm);
-    if (tiles <= cus) return steps <= (tiles * 2 > cus ? 124 : 160) ? bm : 0;
+    if (tiles > cus) continue;
+    long long most = tiles * 2 > cus ? 124 : 160;
+    if (workgroup_splits(p, groups * cdiv(p->M + pl.skewM, 128) * cdiv(p->N + pl.skewN, 128), 2 * cus, nk, 4, kSmallTileBytes) > 1) {
+      if (bm == 32) most = tiles * 2 > cus ? 124 : (tiles * 4 > cus ? 136 : 160);
+      else if (p->a_kcontig) most = 95;
+      else most = tiles * 2 > cus ? 124 : (tiles * 8 > cus ? 112 : 144);
+    }
+    return steps <= most ? bm : 0;
   }
   return 0;
 }
@@ -536,8 +556,6 @@ long long workgroup_splits(const hap_gemm_problem* p, long long tiles, long long
   if (g > held) g = held;
   return g < 2 ? 1 : g;
 }
-
-constexpr size_t kSmallTileBytes = 128 * 128 * sizeof(float);     // a partial tile
 
 /* Whether 128-tiles of this product run in gemm_kpair_kernel: at most one tile per compute unit, and two K tiles for each of its two
  * wave groups.  The alternative is the 4-wave kernel, which fills the chip by splitting K over workgroups where it has a workspace.

@@ -344,6 +344,32 @@ def test_linear_smallest_outputs_route(hap):
         assert (host(Y) == 2).all()
 
 
+@pytest.mark.parametrize("product,tokens,in_f,out_f,most,alone", [("fwd", 320, None, 512, 136, 160), ("fwd", 256, None, 512, 160, 160), ("fwd", 512, None, 1024, 124, 124),
+                                                                  ("fwd", 1024, None, 1024, 95, 124), ("dX", 320, 512, None, 136, 160), ("dX", 1024, 1024, None, 95, 124),
+                                                                  ("dW", None, 256, 256, 144, 160), ("dW", None, 512, 512, 112, 160), ("dW", None, 768, 1024, 124, 124)])
+def test_linear_smallest_outputs_end_where_others_split(hap, product, tokens, in_f, out_f, most, alone):
+    """How many K steps of 32 the kernel of the smallest outputs takes where another kernel could split its contraction, by tile height,
+    product and tile count, and without a workspace (`alone`).  Right on both sides of each line."""
+    torch = torch_mod()
+    for steps, scratch, want in ((most, True, 1), (most + 1, True, 0), (alone, False, 1), (alone + 1, False, 0)):
+        k = steps * 32
+        t, i, o = tokens or k, in_f or k, out_f or k
+        X, W, dY = empty((t, i), "bf16", 0), empty((i, o), "bf16", 0), empty((t, o), "bf16", 0)
+        X[:, 0] = 1; W[0] = 2; W[:, 0] = 2; dY[:, 0] = 3      # one feature, one column, all rows
+        desc = hap.LinearDesc(t, i, o, hap.REPLICATED, [0, 1], hap.BF16, m=1)
+        ws = empty((hap.hap_linear_bwd_workspace(desc, 0),), "u8") if scratch else None
+        out = empty({"fwd": (t, o), "dX": (t, i), "dW": (i, o)}[product], "f32" if product == "dW" else "bf16", 1)
+        before = hap.hap_debug_small_products()
+        if product == "fwd": hap.hap_sharded_linear_fwd(desc, 0, X, W, None, out, None, ws)
+        elif product == "dX": hap.hap_sharded_linear_bwd(desc, 0, X, W, None, dY, out, None, hap.BF16, None, ws)
+        else: hap.hap_sharded_linear_bwd(desc, 0, X, W, None, dY, None, out, hap.F32, None, ws)
+        assert hap.hap_debug_small_products() - before == want, (steps, scratch)
+        got = host(out)
+        if product == "fwd": assert (got == 2).all()
+        elif product == "dX": assert (got == 6).all()
+        else: assert got[0, 0] == 3 * k and not got[1:].any() and not got[:, 1:].any()
+
+
 @pytest.mark.parametrize("scratch", [True, False])
 @pytest.mark.parametrize("tokens,in_f,cut", [(130, 1000, 128), (130, 1000, 333), (130, 1000, 517), (1000, 1000, 128), (1000, 1000, 333), (1000, 1000, 517),
                                              (1300, 2040, 1000), (1300, 2040, 1003), (1300, 2040, 1037)])
