@@ -52,7 +52,7 @@ struct SkinnyArgs {
 
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
-/* RB: 16-row blocks of a workgroup (blockIdx.y counts them).  1 where that still leaves every workgroup a compute unit of its own: 38
+/* RB: 16-row blocks of a workgroup (blockIdx.y counts them; skinny_f32_row_blocks() chooses).  1: 38
  * rows of a 1024-wide layer are 64 workgroups of three row blocks or 192 of one, each with a third of the MFMAs and of the A
  * traffic (the weight is then read three times, out of L2); with all rows in one workgroup (4) the weight is read once, for outputs
  * wide enough to fill the chip by themselves.  That layer's forward, backward and factor rebuild: 38.2 us with 4, 31.9 with 1. */
@@ -279,13 +279,32 @@ static void look_up_cu_count() {
   t_cus = cached[device];
 }
 
+inline long long cdiv(long long a, long long b) { return (a + b - 1) / b; }
+
+constexpr size_t kSmallTileBytes = 128 * 128 * sizeof(float);     // a partial tile
+
+/* What the planner weighs the kernels by (below). */
+long long workgroup_splits(const hap_gemm_problem* p, long long tiles, long long slots, long long steps, int min_steps, size_t tile_bytes);
+bool kpair_applies(const hap_gemm_problem* p, long long tiles, long long nk);
+int kpair_splits(const hap_gemm_problem* p, long long tiles, long long nk, double* us);
+double us_256(const hap_gemm_problem* p, long long n, long long nk);
+bool trio_applies(const hap_gemm_problem* p, long long n, long long nk, double* us);
+
 /* 16-row blocks per workgroup with which gemm_skinny_f32_kernel takes the product: 1, 4 (all rows, at most 64), or 0 where it does not.
- * One row block each as long as that is at most a thousand workgroups of a million k values in all, and, for up to 64 rows, the columns
- * alone would leave half of the compute units idle.  Microseconds, what ran before -> one row block:
+ * Microseconds, what ran before -> one row block:
  *   forward, rows x in x out:  64 x 2048 x 2048 22.3 -> 16.3    100 x 1024 x 1024 13.1 -> 8.3    256 x 512 x 512: 11.2 -> 6.2    256 x 1024 x 1024 17.6 -> 14.2
  *   bwd-data:  128 x 1024 x 1024 13.4 -> 9.2    512 x 512 x 512 12.4 -> 10.8 (1024 workgroups)
- *   beyond:    128 x 2048 x 2048 27.0 -> 29.9 (1024 workgroups over K = 2048)    256 x 2048 x 512 16.5 -> 18.8 (2048 workgroups)
- *   up to 64 rows, 256 column blocks and more, all rows -> one row block: 38 x 512 x 4096 7.0 -> 8.5    64 x 1024 x 4096 12.7 -> 16.1 */
+ * More than 64 rows: one row block each, where the tiled kernel could split K as long as the rounds of workgroups over the compute units,
+ * times K, are at most 4096 (5120 in a single round):
+ *   one round, 80 to 256 workgroups, K = 4096 / 5120 / 6144:  forward 17.7 -> 13.8 / 20.0 -> 18.8 / 21.7 -> 22.8, bwd-data 18.5 -> 16.1 / 20.3 -> 19.6 / 22.0 -> 23.2
+ *   two rounds, 258 workgroups, K = 2048 / 2560:  18.2 -> 15.5 / 19.8 -> 20.2, 17.3 -> 16.3 / 19.3 -> 20.6
+ *   three rounds, 516 workgroups, K = 1300 / 1536:  17.3 -> 15.9 / 17.3 -> 19.0    four rounds, K = 1024 / 2048: 17.4 -> 14.2 / 27.0 -> 29.9
+ *   more:  256 x 2048 x 512 16.5 -> 18.8 (2048 workgroups)
+ * and, where it could not (no workspace, or a weight whose rows are not on the 16-byte grid and go to the scalar kernel), up to a thousand
+ * workgroups of a million k values in all (without a workspace 688 workgroups over K = 1300 39.3 -> 17.6).
+ * Up to 64 rows: all rows in one workgroup where the columns alone give half of the compute units one: 38 x 512 x 4096 7.0 as one row
+ * block each 8.5, 64 x 1024 x 4096 12.7 and 16.1; and three row blocks of a forward over a long K, whose weight would be read three times:
+ * 38 x 1024 x 1600 8.4 and 7.7, 38 x 2048 x 1600 14.9 and 15.4, 38 x 8192 x 2048 54.0 and 58.7 (bwd-data 56.0 and 53.4, 50 rows 69.0 and 63.2). */
 static int skinny_f32_row_blocks(const hap_gemm_problem* p) {
   if (p->in_dtype != HAP_F32 || p->c_dtype != HAP_F32 || !p->a_kcontig || p->nseg != 1) return 0;
   if (p->groups > 1 || p->group_len || p->force_generic || p->tile || p->dact) return 0;
@@ -293,9 +312,14 @@ static int skinny_f32_row_blocks(const hap_gemm_problem* p) {
   if (K < 256 || K % 4 || K > 0x7fffffff || (p->N + 63) / 64 >= 128) return 0;      // enough 64-wide tiles: the tiled kernel fills the chip by itself
   if (p->lda % 4 || (uintptr_t)p->a[0] % 16) return 0;
   if (p->b_kcontig && (p->ldb % 4 || (uintptr_t)p->b[0] % 16)) return 0;
-  const int64_t columns = (p->N + 15) / 16, rows = (p->M + 15) / 16, cus = cu_count();
-  if (p->M > 64) return rows <= 4 * cus && columns * rows <= 4 * cus && columns * rows * K <= 4096 * cus ? 1 : 0;
-  return columns * rows <= cus || columns * 2 <= cus ? 1 : 4;
+  const int64_t columns = (p->N + 15) / 16, rows = (p->M + 15) / 16, cus = cu_count(), groups = columns * rows;
+  if (p->M > 64) {
+    if (rows > 4 * cus || groups > 4 * cus || groups * K > 4096 * cus) return 0;
+    if (p->ldb % 4 || workgroup_splits(p, cdiv(p->M, 64) * cdiv(p->N, 64), 4 * cus, cdiv(K, 64), 2, 64 * 64 * sizeof(float)) < 2) return 1;
+    return cdiv(groups, cus) * K <= (groups <= cus ? 5120 : 4096) ? 1 : 0;
+  }
+  if (groups <= cus) return 1;
+  return columns * 2 <= cus && (rows > 3 || p->b_kcontig || K <= 1536) ? 1 : 4;
 }
 
 /* Whether a product goes to gemm_rank_f32_kernel: as many k values as its waves contract in the time that the tiled kernel and, where it
@@ -366,17 +390,6 @@ __global__ __launch_bounds__(256) void gemm_generic_kernel(const GenericArgs g) 
   if (g.accumulate) acc += load_s<TC>(dst);
   store_c<TC>(dst, acc);
 }
-
-inline long long cdiv(long long a, long long b) { return (a + b - 1) / b; }
-
-constexpr size_t kSmallTileBytes = 128 * 128 * sizeof(float);     // a partial tile
-
-/* What the planner weighs the kernels by (below). */
-long long workgroup_splits(const hap_gemm_problem* p, long long tiles, long long slots, long long steps, int min_steps, size_t tile_bytes);
-bool kpair_applies(const hap_gemm_problem* p, long long tiles, long long nk);
-int kpair_splits(const hap_gemm_problem* p, long long tiles, long long nk, double* us);
-double us_256(const hap_gemm_problem* p, long long n, long long nk);
-bool trio_applies(const hap_gemm_problem* p, long long n, long long nk, double* us);
 
 constexpr int kPingPongBK = 32;   // K step of the ping-pong kernel
 

@@ -615,6 +615,23 @@ def test_fp32_split_k_with_workspace(hap, scratch):
         assert tuple(b - a for a, b in zip(n, n[1:])) == (want if scratch else (0, 0, 0)), (tokens, in_f, out_f, n)
 
 
+@pytest.mark.parametrize("tokens,out_f,most", [(128, 256, 5120), (104, 688, 2048), (192, 688, 1364), (256, 1024, 1024)])
+def test_fp32_rows_beyond_64_split_k_where_that_is_faster(hap, tokens, out_f, most):
+    """Up to `most` features the contraction is shared by the waves of a workgroup, beyond it is split over workgroups if the workspace allows;
+    a weight whose rows are off the 16-byte grid has no kernel that could.  fp32 bar on both sides."""
+    torch = torch_mod()
+    for in_f, pad, scratch, want in ((most, 0, True, 0), (most + 4, 0, True, 1), (most + 4, 0, False, 0), (most + 4, 1, True, 0)):
+        Xh, Xd = gen(3, T.X, (tokens, in_f), 1.0, "f32"); Wh, Wd = gen(3, T.W, (in_f, out_f), 0.05, "f32"); bh, bd = gen(3, T.BIAS, (out_f,), 0.5, "f32")
+        Wd = torch.nn.functional.pad(Wd, (0, pad), value=float("nan"))
+        desc = hap.LinearDesc(tokens, in_f, out_f, hap.REPLICATED, [0, 1], hap.F32, act=hap.ACT_GELU_ERF, has_bias=True, ldx=in_f, ldw=out_f + pad, ldy=out_f, m=1)
+        Y, P = empty((tokens, out_f), "f32", float("nan")), empty((tokens, out_f), "f32", float("nan"))
+        before = hap.hap_debug_split_products()
+        hap.hap_sharded_linear_fwd(desc, 0, Xd, Wd, bd, Y, P, empty((64 << 20,), "u8") if scratch else None)
+        assert hap.hap_debug_split_products() - before == want, (in_f, pad, scratch)
+        Yo, Po = olin.linear_fwd(Xh, Wh, bh, True)
+        check("Y", host(Y), Yo, "f32"); check("preact", host(P), Po, "f32")
+
+
 def test_linear_smallest_outputs_with_bias_gelu_and_ragged_view(hap):
     """Deep contraction, few output tiles, bias + GeLU + saved pre-activation, misaligned column range, into one pair of whole tensors."""
     tokens, in_f, out_f = 200, 1024, 520
