@@ -631,23 +631,31 @@ static double small_tiles_time(long long n) {
  * aligned and not) x five products, each forced through every kernel: standard error 3 to 10 %.  Over those of at most 24 K tiles the
  * choice that these make is 1.0 to 1.5 % slower than the fastest kernel of each (geometric mean, by product), by whole rounds, whatever the
  * epilogue and the contraction, 4 to 16 %.  Over 24 to 48 K tiles the two are alike, beyond 48 the rounds are 1 to 1.5 % better for bwd-data:
- * there a tile's epilogue matters little and what the operands' pitches cost a kernel much. */
+ * there a tile's epilogue matters little and what the operands' pitches cost a kernel much.  fp32 outputs: 400 more shapes (300 to 16384 each
+ * way, K 32 to 1536) as weight gradients and as rebuilds of two factors; the choice is 0.8 % slower than the fastest kernel, 1.2 % with the
+ * bf16 outputs' terms (which lose up to 13 % at K = 64: 3479 x 3072 14.8 -> 16.7), 1.8 % by whole rounds. */
 constexpr long long kShortContraction = 24;
-enum { kPlain = 0, kGelu = 1, kDact = 2 };     // what the epilogue does
+enum { kPlain = 0, kGelu = 1, kDact = 2, kF32 = 3 };     // what the epilogue does; kF32: a weight gradient's or factor rebuild's fp32 output
 
-int epilogue_kind(const hap_gemm_problem* p) { return p->act != HAP_ACT_NONE ? kGelu : (p->dact != HAP_ACT_NONE ? kDact : kPlain); }
+int epilogue_kind(const hap_gemm_problem* p) {
+  if (p->act != HAP_ACT_NONE) return kGelu;
+  if (p->dact != HAP_ACT_NONE) return kDact;
+  return p->c_dtype == HAP_F32 ? kF32 : kPlain;
+}
 
 /* n 256-tiles.  A K tile of 64 takes 1.5 with all compute units at it (1.65 when both operands are K-contiguous), down to half with few;
- * prologue, epilogue and stores of a round 9.5, with GeLU and the pre-activation copy or with the activation backward 20.  Fewer tiles
+ * prologue, epilogue and stores of a round 9.5, with GeLU and the pre-activation copy or with the activation backward 20.  fp32 outputs: 1.65
+ * per K tile, 11.5 per round, 3.9 instead of 5.5 per launch.  Fewer tiles
  * than compute units, as the launcher splits K over the idle ones: 1.55 and 18 with the reduction (24 with
  * GeLU in it), 0.025 per partial tile (88 tiles over K = 16384, split in two: 199; 68 over 1402 in three: 35, with GeLU 43; 80 over 5312: 68). */
 double us_256(const hap_gemm_problem* p, long long n, long long nk) {
   const long long cus = cu_count();
   const long long g = workgroup_splits(p, n, cus, nk, 4, 4 * kSmallTileBytes);
-  if (g > 1) return (double)nk / (double)g * 1.55 + (epilogue_kind(p) == kPlain ? 18.0 : 24.0) + 0.025 * (double)(n * g);
-  const double kt = (double)nk * (p->a_kcontig && p->b_kcontig ? 1.65 : 1.5), round = epilogue_kind(p) == kPlain ? 9.5 : 20.0;
+  const int e = epilogue_kind(p);
+  if (g > 1) return (double)nk / (double)g * 1.55 + (e == kPlain || e == kF32 ? 18.0 : 24.0) + 0.025 * (double)(n * g);
+  const double kt = (double)nk * ((p->a_kcontig && p->b_kcontig) || e == kF32 ? 1.65 : 1.5), round = e == kPlain ? 9.5 : (e == kF32 ? 11.5 : 20.0);
   const double rest = (double)(n % cus) / (double)cus;
-  return 5.5 + (double)(n / cus) * (kt + round) + (rest > 0.0 ? kt * (0.5 + 0.5 * rest) + round : 0.0);
+  return (e == kF32 ? 3.9 : 5.5) + (double)(n / cus) * (kt + round) + (rest > 0.0 ? kt * (0.5 + 0.5 * rest) + round : 0.0);
 }
 
 /* Whether 128-tiles that do not run in gemm_kpair_kernel run in gemm_trio_kernel, and the estimated time either way.  n: tiles.  What
@@ -658,7 +666,8 @@ double us_256(const hap_gemm_problem* p, long long n, long long nk) {
  *   bwd-data with the activation backward 17947 x 614 over 200 49.7 -> 30.7
  *   long contractions:  forward 16384 x 2731 over 2048 209 -> 199, bwd-data 16384 x 2048 over 2731 188 -> 231 */
 bool trio_applies(const hap_gemm_problem* p, long long n, long long nk, double* us) {
-  static const double four_fixed[3] = {3.0, 4.0, 4.5}, four_tile[3] = {3.0, 5.7, 5.0}, trio_fixed[3] = {6.0, 7.0, 7.5}, trio_tile[3] = {1.7, 4.1, 3.3};
+  static const double four_fixed[4] = {3.0, 4.0, 4.5, 4.3}, four_tile[4] = {3.0, 5.7, 5.0, 3.25};      // by epilogue_kind()
+  static const double trio_fixed[4] = {6.0, 7.0, 7.5, 0.0}, trio_tile[4] = {1.7, 4.1, 3.3, 0.0};        // (not built for fp32 outputs)
   const long long cus = cu_count();
   const int e = epilogue_kind(p);
   const bool kk = p->a_kcontig && p->b_kcontig;
