@@ -436,32 +436,33 @@ int layernorm_fwd_t(int64_t rows, int n, const void* x, const void* g, const voi
   return check_launch("layernorm_fwd");
 }
 
-/* sums.p[2], sums.p[3]: NULL, or column sums of dres and dx as well (*sums_taken says whether this layout gives them). */
+/* sums.p[2], sums.p[3]: NULL, or column sums of dres and dx as well; a layout that does not give them launches nothing and leaves *done false. */
 template <typename T>
 int layernorm_bwd_t(int64_t rows, int n, const void* x, const void* g, const float* mean, const float* rstd, const void* dy,
-                    const void* dres, void* dx, const LnSums& sums, bool* sums_taken, float* part, hipStream_t s) {
+                    const void* dres, void* dx, const LnSums& sums, bool* done, float* part, hipStream_t s) {
   const int nblocks = (int)((rows + 3) / 4 < kLnBlocks ? (rows + 3) / 4 : kLnBlocks);
   const bool vec_ok = aligned16(x) && aligned16(dy) && aligned16(dx) && aligned16(g) && aligned16(dres);
   const bool want = sums.p[2] != nullptr;
-  bool took = false;
+  *done = false;
   const bool ok = ln_dispatch<T>(n, vec_ok, [&](auto v, auto nch) {
     constexpr int V = decltype(v)::value, NCH = decltype(nch)::value;
+    if (!want) {
+      hipLaunchKernelGGL((layernorm_bwd_kernel<T, V, NCH, false>), dim3(nblocks), dim3(256), 0, s, rows, n, (const T*)x, (const T*)g, mean, rstd, (const T*)dy, (const T*)dres, (T*)dx, part);
+      *done = true;
+      return;
+    }
     // (rows of up to 1024 elements: beyond, the four sums of a lane take its last registers and the loads in flight with them - 2048
     // elements: 64 -> 119 us, more than the two passes that it saves)
     if constexpr (V > 1 && V * NCH <= 16) {
-      if (want) {
-        took = true;
-        hipLaunchKernelGGL((layernorm_bwd_kernel<T, V, NCH, true>), dim3(nblocks), dim3(256), 0, s, rows, n, (const T*)x, (const T*)g, mean, rstd, (const T*)dy, (const T*)dres, (T*)dx, part);
-        return;
-      }
+      hipLaunchKernelGGL((layernorm_bwd_kernel<T, V, NCH, true>), dim3(nblocks), dim3(256), 0, s, rows, n, (const T*)x, (const T*)g, mean, rstd, (const T*)dy, (const T*)dres, (T*)dx, part);
+      *done = true;
     }
-    hipLaunchKernelGGL((layernorm_bwd_kernel<T, V, NCH, false>), dim3(nblocks), dim3(256), 0, s, rows, n, (const T*)x, (const T*)g, mean, rstd, (const T*)dy, (const T*)dres, (T*)dx, part);
   });
   if (!ok) return hap_fail(HAP_EUNSUPPORTED, "layernorm row of %d elements is too long for this layout", n);
+  if (!*done) return HAP_OK;
   int rc = check_launch("layernorm_bwd");
   if (rc) return rc;
-  *sums_taken = took;
-  hipLaunchKernelGGL(layernorm_bwd_final_kernel, dim3((n + 15) / 16, took ? 4 : 2), dim3(256), 0, s, n, nblocks, part, sums);
+  hipLaunchKernelGGL(layernorm_bwd_final_kernel, dim3((n + 15) / 16, want ? 4 : 2), dim3(256), 0, s, n, nblocks, part, sums);
   return check_launch("layernorm_bwd_final");
 }
 
@@ -618,9 +619,9 @@ int hap_layernorm_bwd(int64_t rows, int64_t n, int io_dtype, const void* x, cons
   if (!ws || ws_bytes < need) return hap_fail(HAP_EWORKSPACE, "layernorm_bwd needs %zu workspace bytes", need);
   hipStream_t s = (hipStream_t)stream;
   const LnSums out = {{dgamma, dbeta, NULL, NULL}};
-  bool took;
-  if (io_dtype == HAP_BF16) return layernorm_bwd_t<__bf16>(rows, (int)n, x, gamma, mean, rstd, dy, dresidual, dx, out, &took, (float*)ws, s);
-  if (io_dtype == HAP_F32) return layernorm_bwd_t<float>(rows, (int)n, x, gamma, mean, rstd, dy, dresidual, dx, out, &took, (float*)ws, s);
+  bool done;
+  if (io_dtype == HAP_BF16) return layernorm_bwd_t<__bf16>(rows, (int)n, x, gamma, mean, rstd, dy, dresidual, dx, out, &done, (float*)ws, s);
+  if (io_dtype == HAP_F32) return layernorm_bwd_t<float>(rows, (int)n, x, gamma, mean, rstd, dy, dresidual, dx, out, &done, (float*)ws, s);
   return hap_fail(HAP_EINVAL, "bad dtype %d", io_dtype);
 }
 
@@ -636,19 +637,18 @@ int hap_layernorm_bwd_sums(int64_t rows, int64_t n, int io_dtype, const void* x,
   if (!sum_dresidual || !sum_dx || (!dresidual && rows > 0)) return hap_fail(HAP_EINVAL, "NULL pointer");
   if (rows > 0 && n >= 1 && (!ws || ws_bytes < hap_layernorm_bwd_sums_workspace(rows, n)))
     return hap_fail(HAP_EWORKSPACE, "layernorm_bwd_sums needs %zu workspace bytes", hap_layernorm_bwd_sums_workspace(rows, n));
-  // rows that the one kernel has the registers for; dx over dresidual is fine there, each element is read before it is written
-  const int v = io_dtype == HAP_BF16 ? 8 : 4;
-  const bool one = rows > 0 && (io_dtype == HAP_BF16 || io_dtype == HAP_F32) && n % v == 0 && n <= 16 * 64 && x && gamma && mean && rstd && dy && dx && dgamma && dbeta &&
-                   aligned16(x) && aligned16(gamma) && aligned16(dy) && aligned16(dresidual) && aligned16(dx);
-  if (one) {
+  int rc;
+  if (rows > 0 && n >= 1) {
+    if (!x || !gamma || !mean || !rstd || !dy || !dx || !dgamma || !dbeta) return hap_fail(HAP_EINVAL, "NULL pointer");
+    if (io_dtype != HAP_BF16 && io_dtype != HAP_F32) return hap_fail(HAP_EINVAL, "bad dtype %d", io_dtype);
     const LnSums out = {{dgamma, dbeta, sum_dresidual, sum_dx}};
-    bool took = false;
-    hipStream_t s = (hipStream_t)stream;
-    const int rc = io_dtype == HAP_BF16 ? layernorm_bwd_t<__bf16>(rows, (int)n, x, gamma, mean, rstd, dy, dresidual, dx, out, &took, (float*)ws, s)
-                                        : layernorm_bwd_t<float>(rows, (int)n, x, gamma, mean, rstd, dy, dresidual, dx, out, &took, (float*)ws, s);
-    return rc == HAP_OK && !took ? hap_fail(HAP_EDEVICE, "internal: layernorm backward without its column sums") : rc;
+    bool done;
+    // (dx over dresidual is fine in the one kernel, each element is read before it is written)
+    rc = io_dtype == HAP_BF16 ? layernorm_bwd_t<__bf16>(rows, (int)n, x, gamma, mean, rstd, dy, dresidual, dx, out, &done, (float*)ws, (hipStream_t)stream)
+                              : layernorm_bwd_t<float>(rows, (int)n, x, gamma, mean, rstd, dy, dresidual, dx, out, &done, (float*)ws, (hipStream_t)stream);
+    if (rc || done) return rc;
   }
-  int rc = hap_colsum(rows, n, io_dtype, dresidual, n, sum_dresidual, ws, ws_bytes, stream);      // (before dx, which may take its place)
+  rc = hap_colsum(rows, n, io_dtype, dresidual, n, sum_dresidual, ws, ws_bytes, stream);      // (before dx, which may take its place)
   if (rc) return rc;
   if ((rc = hap_layernorm_bwd(rows, n, io_dtype, x, gamma, mean, rstd, dy, dresidual, dx, dgamma, dbeta, ws, ws_bytes, stream))) return rc;
   return hap_colsum(rows, n, io_dtype, dx, n, sum_dx, ws, ws_bytes, stream);

@@ -308,3 +308,8 @@ def test_layernorm_bwd_with_column_sums(hap, dtype, n, rows, inplace):
         assert (np.abs(host(got) - terms.sum(0)) <= bound).all(), name
     with pytest.raises(hap.HapError):
         hap.hap_layernorm_bwd_sums(7, n, io, xd, gd, mean, rstd, dyd, rd, dx2, dg2, db2, sr, sx, empty((16,), "u8"))
+    # a refused call has written nothing
+    sr.fill_(5)
+    with pytest.raises(hap.HapError):
+        hap.hap_layernorm_bwd_sums(max(rows, 1), n, io, None, gd, mean, rstd, dyd, rd, dx2, dg2, db2, sr, sx, empty((hap.hap_layernorm_bwd_sums_workspace(max(rows, 1), n),), "u8"))
+    assert (host(sr) == 5).all()
