@@ -182,6 +182,16 @@ def _check(status: int, where: str):
         raise HapError(status, where)
 
 
+def _launch(entry_point, where: str, *args):
+    """Calls an entry point that has a signature; an argument of the wrong type is a TypeError, as it is for every other function."""
+    try:
+        status = entry_point(*args)
+    except C.ArgumentError as e:
+        raise TypeError(f"{where}: {e}") from None
+    if status != 0:
+        raise HapError(status, where)
+
+
 def _stages(stages):
     arr = (Stage * len(stages))()
     for i, s in enumerate(stages):
@@ -372,23 +382,22 @@ def hap_linear_bwd_workspace(desc: LinearDesc, shard_index: int) -> int:
 
 def hap_sharded_linear_fwd(desc: LinearDesc, shard_index, X, W, bias, Y, preact=None, ws=None, stream=None):
     wp, wb = _ws(ws)
-    _check(lib.hap_sharded_linear_fwd(C.byref(desc.c), shard_index, _ptr(X), _ptr(W), _ptr(bias), _ptr(Y),
-                                      _ptr(preact), wp, wb, _stream(stream)), "hap_sharded_linear_fwd")
+    _launch(lib.hap_sharded_linear_fwd, "hap_sharded_linear_fwd", C.byref(desc.c), shard_index, _ptr(X), _ptr(W), _ptr(bias), _ptr(Y),
+            _ptr(preact), wp, wb, _stream(stream))
 
 
 def hap_sharded_linear_bwd(desc: LinearDesc, shard_index, X, W, preact, dY, dX, dW, dW_dtype, dbias, ws=None, stream=None):
     wp, wb = _ws(ws)
-    _check(lib.hap_sharded_linear_bwd(C.byref(desc.c), shard_index, _ptr(X), _ptr(W), _ptr(preact), _ptr(dY),
-                                      _ptr(dX), _ptr(dW), dW_dtype, _ptr(dbias), wp, wb, _stream(stream)),
-           "hap_sharded_linear_bwd")
+    _launch(lib.hap_sharded_linear_bwd, "hap_sharded_linear_bwd", C.byref(desc.c), shard_index, _ptr(X), _ptr(W), _ptr(preact), _ptr(dY),
+            _ptr(dX), _ptr(dW), dW_dtype, _ptr(dbias), wp, wb, _stream(stream))
 
 
 def hap_sharded_linear_bwd_dact(desc: LinearDesc, shard_index, X, W, preact, dY, dX, dW, dW_dtype, dbias, x_preact, x_act,
                                 ws=None, stream=None):
     wp, wb = _ws(ws)
-    _check(lib.hap_sharded_linear_bwd_dact(C.byref(desc.c), shard_index, _ptr(X), _ptr(W), _ptr(preact), _ptr(dY),
-                                           _ptr(dX), _ptr(dW), dW_dtype, _ptr(dbias), _ptr(x_preact), x_act,
-                                           wp, wb, _stream(stream)), "hap_sharded_linear_bwd_dact")
+    _launch(lib.hap_sharded_linear_bwd_dact, "hap_sharded_linear_bwd_dact", C.byref(desc.c), shard_index, _ptr(X), _ptr(W), _ptr(preact), _ptr(dY),
+            _ptr(dX), _ptr(dW), dW_dtype, _ptr(dbias), _ptr(x_preact), x_act,
+            wp, wb, _stream(stream))
 
 
 def hap_sfb_grad(Xs, dYs, rows, in_features, out_features, ldx, ldy, in_dtype, dW, lddw, accumulate=False, ws=None, stream=None):
@@ -396,18 +405,18 @@ def hap_sfb_grad(Xs, dYs, rows, in_features, out_features, ldx, ldy, in_dtype, d
     xp = (C.c_void_p * m)(*[_ptr(t) for t in Xs])
     yp = (C.c_void_p * m)(*[_ptr(t) for t in dYs])
     wp, wb = _ws(ws)
-    _check(lib.hap_sfb_grad(m, xp, yp, (C.c_int64 * m)(*map(int, rows)), in_features, out_features,
-                            ldx, ldy, in_dtype, _ptr(dW), lddw, int(accumulate),
-                            wp, wb, _stream(stream)), "hap_sfb_grad")
+    _launch(lib.hap_sfb_grad, "hap_sfb_grad", m, xp, yp, (C.c_int64 * m)(*map(int, rows)), in_features, out_features,
+            ldx, ldy, in_dtype, _ptr(dW), lddw, int(accumulate),
+            wp, wb, _stream(stream))
 
 
 def hap_sfb_grad_static(Xs, dYs, rows, in_features, out_features, ldx, ldy, in_dtype, dW, lddw, accumulate=False, stream=None):
     m = len(rows)
     xp = (C.c_void_p * m)(*[_ptr(t) for t in Xs])
     yp = (C.c_void_p * m)(*[_ptr(t) for t in dYs])
-    _check(lib.hap_sfb_grad_static(m, xp, yp, (C.c_int64 * m)(*map(int, rows)), in_features, out_features,
-                                   ldx, ldy, in_dtype, _ptr(dW), lddw, int(accumulate),
-                                   _stream(stream)), "hap_sfb_grad_static")
+    _launch(lib.hap_sfb_grad_static, "hap_sfb_grad_static", m, xp, yp, (C.c_int64 * m)(*map(int, rows)), in_features, out_features,
+            ldx, ldy, in_dtype, _ptr(dW), lddw, int(accumulate),
+            _stream(stream))
 
 
 def hap_sfb_workspace(m, rows, in_features, out_features) -> int:
@@ -424,21 +433,21 @@ def hap_moe_linear_bwd_workspace(desc: MoeDesc, shard_index: int) -> int:
 
 def hap_moe_linear_fwd(desc: MoeDesc, shard_index, X, W, bias, rows, Y, preact=None, ws=None, stream=None):
     wp, wb = _ws(ws)
-    _check(lib.hap_moe_linear_fwd(C.byref(desc.c), shard_index, _ptr(X), _ptr(W), _ptr(bias), _ptr(rows), _ptr(Y),
-                                  _ptr(preact), wp, wb, _stream(stream)), "hap_moe_linear_fwd")
+    _launch(lib.hap_moe_linear_fwd, "hap_moe_linear_fwd", C.byref(desc.c), shard_index, _ptr(X), _ptr(W), _ptr(bias), _ptr(rows), _ptr(Y),
+            _ptr(preact), wp, wb, _stream(stream))
 
 
 def hap_moe_linear_bwd(desc: MoeDesc, shard_index, X, W, preact, dY, rows, dX, dW, dW_dtype, dbias, ws=None, stream=None):
     wp, wb = _ws(ws)
-    _check(lib.hap_moe_linear_bwd(C.byref(desc.c), shard_index, _ptr(X), _ptr(W), _ptr(preact), _ptr(dY), _ptr(rows),
-                                  _ptr(dX), _ptr(dW), dW_dtype, _ptr(dbias), wp, wb, _stream(stream)), "hap_moe_linear_bwd")
+    _launch(lib.hap_moe_linear_bwd, "hap_moe_linear_bwd", C.byref(desc.c), shard_index, _ptr(X), _ptr(W), _ptr(preact), _ptr(dY), _ptr(rows),
+            _ptr(dX), _ptr(dW), dW_dtype, _ptr(dbias), wp, wb, _stream(stream))
 
 
 def hap_moe_linear_bwd_dact(desc: MoeDesc, shard_index, X, W, preact, dY, rows, dX, dW, dW_dtype, dbias, x_preact, x_act, ws=None, stream=None):
     wp, wb = _ws(ws)
-    _check(lib.hap_moe_linear_bwd_dact(C.byref(desc.c), shard_index, _ptr(X), _ptr(W), _ptr(preact), _ptr(dY), _ptr(rows),
-                                       _ptr(dX), _ptr(dW), dW_dtype, _ptr(dbias), _ptr(x_preact), x_act, wp, wb,
-                                       _stream(stream)), "hap_moe_linear_bwd_dact")
+    _launch(lib.hap_moe_linear_bwd_dact, "hap_moe_linear_bwd_dact", C.byref(desc.c), shard_index, _ptr(X), _ptr(W), _ptr(preact), _ptr(dY), _ptr(rows),
+            _ptr(dX), _ptr(dW), dW_dtype, _ptr(dbias), _ptr(x_preact), x_act, wp, wb,
+            _stream(stream))
 
 
 def hap_allgather_capacity(desc: GatherDesc) -> int:
@@ -446,22 +455,22 @@ def hap_allgather_capacity(desc: GatherDesc) -> int:
 
 
 def hap_allgather_pad(desc: GatherDesc, shard_index, shard, ld_shard, slot, ld_slot, stream=None):
-    _check(lib.hap_allgather_pad(C.byref(desc.c), shard_index, _ptr(shard), ld_shard, _ptr(slot), ld_slot,
-                                 _stream(stream)), "hap_allgather_pad")
+    _launch(lib.hap_allgather_pad, "hap_allgather_pad", C.byref(desc.c), shard_index, _ptr(shard), ld_shard, _ptr(slot), ld_slot,
+            _stream(stream))
 
 
 def hap_allgather_assemble(desc: GatherDesc, pieces, ld_pieces, out, ld_out, stream=None):
     m = desc.m
     pp = (C.c_void_p * m)(*[_ptr(t) for t in pieces])
-    _check(lib.hap_allgather_assemble(C.byref(desc.c), pp, (C.c_int64 * m)(*map(int, ld_pieces)), _ptr(out), ld_out,
-                                      _stream(stream)), "hap_allgather_assemble")
+    _launch(lib.hap_allgather_assemble, "hap_allgather_assemble", C.byref(desc.c), pp, (C.c_int64 * m)(*map(int, ld_pieces)), _ptr(out), ld_out,
+            _stream(stream))
 
 
 def hap_reducescatter_split(desc: GatherDesc, full, ld_full, slots, ld_slots, stream=None):
     m = desc.m
     pp = (C.c_void_p * m)(*[_ptr(t) for t in slots])
-    _check(lib.hap_reducescatter_split(C.byref(desc.c), _ptr(full), ld_full, pp, (C.c_int64 * m)(*map(int, ld_slots)),
-                                       _stream(stream)), "hap_reducescatter_split")
+    _launch(lib.hap_reducescatter_split, "hap_reducescatter_split", C.byref(desc.c), _ptr(full), ld_full, pp, (C.c_int64 * m)(*map(int, ld_slots)),
+            _stream(stream))
 
 
 def hap_attn_bwd_workspace(desc: AttnDesc, shard_index: int) -> int:
@@ -470,19 +479,19 @@ def hap_attn_bwd_workspace(desc: AttnDesc, shard_index: int) -> int:
 
 def hap_sharded_attn_fwd(desc: AttnDesc, shard_index, Q, K, V, O, lse, ws=None, stream=None):
     wp, wb = _ws(ws)
-    _check(lib.hap_sharded_attn_fwd(C.byref(desc.c), shard_index, _ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(lse),
-                                    wp, wb, _stream(stream)), "hap_sharded_attn_fwd")
+    _launch(lib.hap_sharded_attn_fwd, "hap_sharded_attn_fwd", C.byref(desc.c), shard_index, _ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(lse),
+            wp, wb, _stream(stream))
 
 
 def hap_sharded_attn_bwd(desc: AttnDesc, shard_index, Q, K, V, O, lse, dO, dQ, dK, dV, ws=None, stream=None):
     wp, wb = _ws(ws)
-    _check(lib.hap_sharded_attn_bwd(C.byref(desc.c), shard_index, _ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(lse),
-                                    _ptr(dO), _ptr(dQ), _ptr(dK), _ptr(dV), wp, wb, _stream(stream)), "hap_sharded_attn_bwd")
+    _launch(lib.hap_sharded_attn_bwd, "hap_sharded_attn_bwd", C.byref(desc.c), shard_index, _ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(lse),
+            _ptr(dO), _ptr(dQ), _ptr(dK), _ptr(dV), wp, wb, _stream(stream))
 
 
 def hap_layernorm_fwd(rows, n, io_dtype, x, gamma, beta, y, mean, rstd, stream=None):
-    _check(lib.hap_layernorm_fwd(rows, n, io_dtype, _ptr(x), _ptr(gamma), _ptr(beta), _ptr(y),
-                                 _ptr(mean), _ptr(rstd), _stream(stream)), "hap_layernorm_fwd")
+    _launch(lib.hap_layernorm_fwd, "hap_layernorm_fwd", rows, n, io_dtype, _ptr(x), _ptr(gamma), _ptr(beta), _ptr(y),
+            _ptr(mean), _ptr(rstd), _stream(stream))
 
 
 def hap_layernorm_bwd_workspace(rows, n) -> int:
@@ -491,8 +500,8 @@ def hap_layernorm_bwd_workspace(rows, n) -> int:
 
 def hap_layernorm_bwd(rows, n, io_dtype, x, gamma, mean, rstd, dy, dx, dgamma, dbeta, ws, stream=None, dresidual=None):
     wp, wb = _ws(ws)
-    _check(lib.hap_layernorm_bwd(rows, n, io_dtype, _ptr(x), _ptr(gamma), _ptr(mean), _ptr(rstd),
-                                 _ptr(dy), _ptr(dresidual), _ptr(dx), _ptr(dgamma), _ptr(dbeta), wp, wb, _stream(stream)), "hap_layernorm_bwd")
+    _launch(lib.hap_layernorm_bwd, "hap_layernorm_bwd", rows, n, io_dtype, _ptr(x), _ptr(gamma), _ptr(mean), _ptr(rstd),
+            _ptr(dy), _ptr(dresidual), _ptr(dx), _ptr(dgamma), _ptr(dbeta), wp, wb, _stream(stream))
 
 
 def hap_layernorm_bwd_sums_workspace(rows, n) -> int:
@@ -501,18 +510,18 @@ def hap_layernorm_bwd_sums_workspace(rows, n) -> int:
 
 def hap_layernorm_bwd_sums(rows, n, io_dtype, x, gamma, mean, rstd, dy, dresidual, dx, dgamma, dbeta, sum_dresidual, sum_dx, ws, stream=None):
     wp, wb = _ws(ws)
-    _check(lib.hap_layernorm_bwd_sums(rows, n, io_dtype, _ptr(x), _ptr(gamma), _ptr(mean), _ptr(rstd), _ptr(dy), _ptr(dresidual), _ptr(dx),
-                                      _ptr(dgamma), _ptr(dbeta), _ptr(sum_dresidual), _ptr(sum_dx), wp, wb, _stream(stream)), "hap_layernorm_bwd_sums")
+    _launch(lib.hap_layernorm_bwd_sums, "hap_layernorm_bwd_sums", rows, n, io_dtype, _ptr(x), _ptr(gamma), _ptr(mean), _ptr(rstd), _ptr(dy), _ptr(dresidual), _ptr(dx),
+            _ptr(dgamma), _ptr(dbeta), _ptr(sum_dresidual), _ptr(sum_dx), wp, wb, _stream(stream))
 
 
 def hap_gelu_bwd(rows, cols, io_dtype, preact, ldp, dy, lddy, out, ldo, stream=None):
-    _check(lib.hap_gelu_bwd(rows, cols, io_dtype, _ptr(preact), ldp, _ptr(dy),
-                            lddy, _ptr(out), ldo, _stream(stream)), "hap_gelu_bwd")
+    _launch(lib.hap_gelu_bwd, "hap_gelu_bwd", rows, cols, io_dtype, _ptr(preact), ldp, _ptr(dy),
+            lddy, _ptr(out), ldo, _stream(stream))
 
 
 def hap_add(rows, cols, io_dtype, a, lda, b, ldb, bias, out, ldo, stream=None):
-    _check(lib.hap_add(rows, cols, io_dtype, _ptr(a), lda, _ptr(b), ldb,
-                       _ptr(bias), _ptr(out), ldo, _stream(stream)), "hap_add")
+    _launch(lib.hap_add, "hap_add", rows, cols, io_dtype, _ptr(a), lda, _ptr(b), ldb,
+            _ptr(bias), _ptr(out), ldo, _stream(stream))
 
 
 def hap_colsum_workspace(rows, cols) -> int:
@@ -521,8 +530,8 @@ def hap_colsum_workspace(rows, cols) -> int:
 
 def hap_colsum(rows, cols, io_dtype, a, lda, out, ws, stream=None):
     wp, wb = _ws(ws)
-    _check(lib.hap_colsum(rows, cols, io_dtype, _ptr(a), lda, _ptr(out), wp, wb,
-                          _stream(stream)), "hap_colsum")
+    _launch(lib.hap_colsum, "hap_colsum", rows, cols, io_dtype, _ptr(a), lda, _ptr(out), wp, wb,
+            _stream(stream))
 
 
 def hap_debug_set_gemm_view_limit(nbytes: int) -> int:
@@ -561,6 +570,5 @@ def hap_device_info():
 def hap_probe_mfma_bf16(random_operands: bool, iters: int, scratch, stream=None) -> float:
     """Launches the MFMA issue-rate probe; returns the flops of the launch (the caller times it)."""
     fl = C.c_double()
-    _check(lib.hap_probe_mfma_bf16(int(bool(random_operands)), iters, _ptr(scratch), C.byref(fl), _stream(stream)),
-           "hap_probe_mfma_bf16")
+    _launch(lib.hap_probe_mfma_bf16, "hap_probe_mfma_bf16", int(bool(random_operands)), iters, _ptr(scratch), C.byref(fl), _stream(stream))
     return fl.value

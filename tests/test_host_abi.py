@@ -43,6 +43,14 @@ def test_launching_entry_points_carry_the_signature_of_the_header(hap):
         assert getattr(hap.binding.lib, name).argtypes == want, name
 
 
+def test_arguments_of_the_wrong_type_are_type_errors(hap):
+    """Before anything is launched; integers of other libraries are integers."""
+    for rows, lda in ((2.0, 8), (2, None), ("2", 8), (2, 8.5)):
+        with pytest.raises(TypeError, match="hap_add"):
+            hap.hap_add(rows, 8, hap.F32, 4096, lda, 4096, 8, None, 4096, 8, stream=0)
+    hap.hap_add(np.int64(0), np.int32(8), hap.F32, 4096, np.int64(8), 4096, 8, None, 4096, 8, stream=0)      # no rows: nothing to launch
+
+
 def test_lp_matches_oracle_on_random_problems(hap):
     rng = np.random.default_rng(3)
     for trial in range(40):
