@@ -141,7 +141,11 @@ struct RankArgs {
   int k[HAP_GEMM_MAX_SEG];          // > 0
 };
 
-/* CK: k values of a chunk.  FOLD: no chain of additions longer than 128 k values (left out where there are no more). */
+/* CK: k values of a chunk.  FOLD: no chain of additions longer than 128 k values.  Left out in linear_bwd_f32_kernel, whose callers keep to
+ * kUnfoldedK values in all, 128 for each of its four wave groups: the second set of accumulators would take the registers with which two
+ * workgroups share a compute unit. */
+constexpr int kUnfoldedK = 4 * 128;
+
 template <int KG, int CK, bool FOLD>
 __device__ __forceinline__ void rank_f32_tile(const RankArgs& g, int tile, float* red) {
   const int lane = threadIdx.x & 63, wave = uni((int)threadIdx.x >> 6), cl = lane & 31, h = lane >> 5;
@@ -255,7 +259,9 @@ __global__ __launch_bounds__(256 * KG) void gemm_rank_f32_kernel(const RankArgs 
 }
 
 /* bwd-data of few rows and the weight (and bias) gradient of the same layer in one launch: neither fills the chip and neither needs the
- * other.  The first `nrank` workgroups take the weight gradient, nx x (rows / 16) the data gradient. */
+ * other.  The first `nrank` workgroups take the weight gradient, over at most kUnfoldedK rows, nx x (rows / 16) the data gradient.
+ * Bound: latency; 64 registers at most, so that two workgroups of 1024 threads share a compute unit (38 x 1024 x 1024: 8.0 us with 55
+ * registers, 9.7 with 89). */
 __global__ __launch_bounds__(1024, 8) void linear_bwd_f32_kernel(const RankArgs w, const SkinnyArgs x, int nrank, int nx) {
   __shared__ float red[kRankRed];
   if ((int)blockIdx.x < nrank) { rank_f32_tile<4, 8, false>(w, blockIdx.x, red); return; }
@@ -573,21 +579,19 @@ long long workgroup_splits(const hap_gemm_problem* p, long long tiles, long long
 /* Whether 128-tiles of this product run in gemm_kpair_kernel: at most one tile per compute unit, and two K tiles for each of its two
  * wave groups.  The alternative is the 4-wave kernel, which fills the chip by splitting K over workgroups where it has a workspace.
  * The limits lie where the two cross (microseconds, 4-wave -> K-pair, three operand sets in turn, MI355X):
- *   K tiles, 36 output tiles:  3: forward 8.6 -> 8.8, bwd-data 8.4 -> 9.0    4: 9.4 -> 8.8, 9.2 -> 9.1    5: 9.9 -> 9.4, 9.7 -> 9.6
+ *   K tiles, 88 output tiles:  3: forward 8.7 -> 8.8, bwd-data 8.6 -> 8.9    4: 9.2 -> 8.9, 9.1 -> 8.9    5: 9.7 -> 9.4, 9.6 -> 9.4
  *   output tiles, K = 1024:    256: 29.9 -> 15.6    272: 20.8 -> 25.9    320: 20.8 -> 25.4
- *   without a workspace:       16 tiles over K = 512 / 1024 / 4096  11.1 -> 10.1 / 15.4 -> 12.3 / 46 -> 27
- * Two ranges stay with the 4-wave kernel where it can split K:
- *   - bwd-data of at most an eighth of the chip over 17 to 19 K tiles (24 tiles: 13.6 -> 14.3; four short splits there, three here, whose
- *     sum takes longer).  On its sides: 16 and 20 K tiles 13.5 -> 12.6 and 15.4 -> 13.8 (24 tiles), 17 K tiles 15.5 -> 14.3 (36 tiles).
- *   - past 128 K tiles, where the operands stream from HBM, tile counts that leave compute units idle here but not there (160 tiles:
- *     62 %, as three splits 94 %; forward over K = 6144 / 7680 / 10240 44.6 -> 41.8 / 52.3 -> 50.3 / 70.7 -> 78.2; in between the two are
- *     within 5 %, and the line lies where kpair_splits() raises the cost of a step, so that the planner weighs the kernel that will run).
- * (An M-contiguous A with a K-contiguous B is a form no product of the path has; the kernel is not built for it.) */
+ *   without a workspace:       88 tiles over K = 512 / 1024 / 4096  12.2 -> 10.4 / 17.9 -> 13.2 / 50 -> 28
+ * Past 128 K tiles, where the operands stream from HBM, tile counts that leave compute units idle here but not there stay with the 4-wave
+ * kernel where it can split K (160 tiles: 62 %, as three splits 94 %; forward over K = 6144 / 7680 / 10240 44.6 -> 41.8 / 52.3 -> 50.3 / 70.7 -> 78.2;
+ * in between the two are within 5 %, and the line lies where kpair_splits() raises the cost of a step, so that the planner weighs the
+ * kernel that will run).
+ * (The smallest outputs run in gemm_small_kernel, which make_plan() asks first.  An M-contiguous A with a K-contiguous B is a form no product
+ * of the path has; the kernel is not built for it.) */
 bool kpair_applies(const hap_gemm_problem* p, long long tiles, long long nk) {
   const long long cus = cu_count();
   if (p->in_dtype != HAP_BF16 || (!p->a_kcontig && p->b_kcontig) || tiles > cus || nk < 4) return false;
   if (workgroup_splits(p, tiles, 2 * cus, nk, 4, kSmallTileBytes) == 1) return true;
-  if (p->a_kcontig && p->b_kcontig && tiles * 8 <= cus && nk > 16 && nk < 20) return false;
   const long long here = cus / tiles * tiles * 2, there = 2 * cus / tiles * tiles;      // of 2 * cus wave groups
   return nk <= 128 || here * 20 >= there * 17;
 }
@@ -953,7 +957,7 @@ int hap_gemm_run_bwd_f32(const hap_gemm_problem* dx, const hap_gemm_problem* dw,
   hipStream_t st = static_cast<hipStream_t>(stream);
   const RankArgs w = rank_args(dw, dbias);
   *taken = 1;
-  if (dx && dx->M > 0 && dx->N > 0 && dw->k[0] <= 512 && skinny_f32_row_blocks(dx) == 1) {
+  if (dx && dx->M > 0 && dx->N > 0 && dw->k[0] <= kUnfoldedK && skinny_f32_row_blocks(dx) == 1) {
     const long long nrank = cdiv(dw->M, 64) * w.tiles_n, nx = cdiv(dx->N, 16), rows = cdiv(dx->M, 16);
     // (workgroups that the chip holds at once; twice as many over short contractions: 200 rows x 512 x 512 18.7 us apart, 9.1 together,
     // 400 x 512 x 512 21.3 and 13.6; over k = 1024 100 x 1024 x 1024 15.1 and 15.6.  38 x 1024 x 1024: 11.0 and 8.0.)

@@ -179,8 +179,9 @@ template <> struct Elem<float> {
  * different chunk positions modulo 256 bytes, a transposing 64-bit read when every 32 lanes do.
  *   K-contiguous tile: 16 lanes read the same logical chunk of 16 consecutive rows -> XOR the chunk
  *     index with the row's index inside its 256-byte group.
- *   M/N-contiguous tile (rows are 512 bytes or more): 32 lanes read 64 contiguous bytes of each of 4
- *     consecutive rows -> XOR bits 2..3 of the chunk index with row & 3.                              */
+ *   M/N-contiguous tile (rows are 256 bytes or more): 32 lanes read 64 contiguous bytes of each of 4
+ *     consecutive rows -> XOR bits 2..3 of the chunk index with row & 3.  Rows of 128 bytes (the 64-wide tiles of
+ *     gemm_small_kernel) have eight chunks and lie two to a sweep: XOR bits 1..2, with which the four rows fill it as well. */
 template <bool KC, int CPR>
 __device__ __forceinline__ int swz(int row, int c) {
   if constexpr (KC) {
