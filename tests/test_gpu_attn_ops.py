@@ -278,7 +278,7 @@ def test_row_ops_degenerate_sizes(hap):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
-@pytest.mark.parametrize("n", [8, 77, 512, 1000, 1024, 1032, 2056])
+@pytest.mark.parametrize("n", [8, 77, 512, 1000, 1021, 1024, 1032, 2056])
 @pytest.mark.parametrize("rows", [0, 1, 5, 2100])
 @pytest.mark.parametrize("inplace", [False, True])
 def test_layernorm_bwd_with_column_sums(hap, dtype, n, rows, inplace):
@@ -313,3 +313,20 @@ def test_layernorm_bwd_with_column_sums(hap, dtype, n, rows, inplace):
     with pytest.raises(hap.HapError):
         hap.hap_layernorm_bwd_sums(max(rows, 1), n, io, None, gd, mean, rstd, dyd, rd, dx2, dg2, db2, sr, sx, empty((hap.hap_layernorm_bwd_sums_workspace(max(rows, 1), n),), "u8"))
     assert (host(sr) == 5).all()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_add_without_bias_on_aligned_rows(hap, dtype):
+    ah, ad = gen(8, T.X, (37, 264), 1.0, dtype); bh, bd = gen(8, T.DY, (37, 264), 1.0, dtype)
+    out = empty((37, 264), dtype, 9)
+    hap.hap_add(37, 264, {"bf16": 1, "f32": 0}[dtype], ad, 264, bd, 264, None, out, 264)
+    check("add", host(out), ah + bh, dtype)
+
+
+def test_matrix_rate_probe_adds_up_its_products(hap):
+    """Constant operands: eight accumulators of 16 elements, each 16 products of 0.5 x 0.5 an iteration; nothing beside the scratch is written."""
+    n = 256 * 512
+    scratch = empty((n + 64,), "f32", 7)
+    assert hap.hap_probe_mfma_bf16(False, 3, scratch) == 2.0 * 32 * 32 * 16 * 8 * 3 * 8 * 256
+    got = host(scratch)
+    assert (got[:n] == 3 * 8 * 16 * 4).all() and (got[n:] == 7).all()

@@ -800,12 +800,13 @@ def test_linear_bwd_dact_rejects_partial_sums(hap):
 
 
 @pytest.mark.parametrize("tokens", [1, 16, 38, 64])
-@pytest.mark.parametrize("in_f,out_f", [(1024, 1024), (256, 1000), (4100, 17), (2048, 8000)])
+@pytest.mark.parametrize("in_f,out_f", [(1024, 1024), (256, 1000), (4100, 17), (2048, 8000), (4100, 264), (1600, 1600)])
 def test_fp32_layer_with_few_rows(hap, tokens, in_f, out_f):
     """fp32 layers of at most 64 rows (config 1's shards are 38 and 26 rows) run forward and bwd-data in a kernel that splits the
     contraction over the waves of a workgroup and sums the partial tiles through LDS: all row-block counts, ragged column tiles,
     contractions that do not divide by the 16 waves, bias + GeLU + saved pre-activation, and dX through the K-contiguous weight.
-    (8000 columns are 125 tiles of 64: just below where the tiled kernel takes over.)"""
+    (8000 columns are 125 tiles of 64: just below where the tiled kernel takes over.  4100 columns of dX take all rows in one workgroup, and so
+    does the forward of 38 rows over 1600 features, whose dX takes three row blocks.)"""
     Xh, Xd = gen(3, T.X, (tokens, in_f), 1.0, "f32"); Wh, Wd = gen(3, T.W, (in_f, out_f), 0.05, "f32")
     bh, bd = gen(3, T.BIAS, (out_f,), 0.5, "f32"); dYh, dYd = gen(3, T.DY, (tokens, out_f), 1.0, "f32")
     desc = hap.LinearDesc(tokens, in_f, out_f, olin.REPLICATED, [0, 1], hap.F32, act=hap.ACT_GELU_ERF, has_bias=True, m=1)
