@@ -425,6 +425,7 @@ struct Plan {
  * Without a workspace for their partial tiles they take 1.2 to 2.7 times as long as this kernel wherever it applies. */
 int small_rows(const hap_gemm_problem* p, const Plan& pl) {
   if (p->in_dtype != HAP_BF16 || p->tile == 256 || (!p->a_kcontig && p->b_kcontig)) return 0;
+  if (p->c_dtype == HAP_F32 && p->a_kcontig) return 0;       // (a form no product of the path has)
   const long long cus = cu_count(), groups = p->groups > 1 ? p->groups : 1;
   long long steps = 0, nk = 0;
   for (int s = 0; s < p->nseg; ++s) {
