@@ -419,7 +419,8 @@ struct Plan {
  * here over time there, geometric mean / worst):
  *   tiles of 32:  up to 64 of them, 152 to 159 steps 0.85 / 1.16    65 to 128, 128 to 135 steps 0.82 / 1.02, 144 to 151 0.98 / 1.24
  *                 beyond, 112 to 119 steps 0.90 / 1.00, 120 to 124 0.95 / 1.06
- *   tiles of 64, forward and bwd-data:  88 to 95 steps 0.96 / 1.04, 96 to 103 1.00 / 1.10, 112 to 119 1.08 / 1.15
+ *   tiles of 64, forward:  88 to 95 steps 0.92 / 1.01, 100 to 107 0.99 / 1.06    bwd-data:  84 to 87 steps 0.92 / 1.01, 92 to 95 0.99 / 1.05,
+ *                 experts' 88 to 95 1.07 / 1.11, 108 to 111 1.05 / 1.13
  *   tiles of 64, bwd-weight:  up to 32 of them, 136 to 143 steps 0.95 / 1.08, 152 to 159 1.01 / 1.22    33 to 128, 104 to 111 steps 0.86 / 0.96, 112 to 119
  *                 0.93 / 1.05, 128 to 135 0.98 / 1.14    beyond, 120 to 124 steps 0.95 / 1.01
  * Without a workspace for their partial tiles they take 1.2 to 2.7 times as long as this kernel wherever it applies. */
@@ -440,7 +441,7 @@ int small_rows(const hap_gemm_problem* p, const Plan& pl) {
     long long most = tiles * 2 > cus ? 124 : 160;
     if (workgroup_splits(p, groups * cdiv(p->M + pl.skewM, 128) * cdiv(p->N + pl.skewN, 128), 2 * cus, nk, 4, kSmallTileBytes) > 1) {
       if (bm == 32) most = tiles * 2 > cus ? 124 : (tiles * 4 > cus ? 136 : 160);
-      else if (p->a_kcontig) most = 95;
+      else if (p->a_kcontig) most = p->b_kcontig ? 87 : 95;
       else most = tiles * 2 > cus ? 124 : (tiles * 8 > cus ? 112 : 144);
     }
     return steps <= most ? bm : 0;
