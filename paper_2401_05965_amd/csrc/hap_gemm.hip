@@ -288,6 +288,7 @@ static void look_up_cu_count() {
 inline long long cdiv(long long a, long long b) { return (a + b - 1) / b; }
 
 constexpr size_t kSmallTileBytes = 128 * 128 * sizeof(float);     // a partial tile
+constexpr long long kShortContraction = 24;                      // K tiles of 64 up to which the planner compares microseconds (us_256() below)
 
 /* What the planner weighs the kernels by (below). */
 long long workgroup_splits(const hap_gemm_problem* p, long long tiles, long long slots, long long steps, int min_steps, size_t tile_bytes);
@@ -511,15 +512,22 @@ Plan make_plan(const hap_gemm_problem* p) {
   } else {
     bool big = p->tile ? p->tile == 256 : (p->M + pl.skewM > 128 && p->N + pl.skewN > 128);
     if (big && !p->tile && (p->groups > 1 || p->group_len)) {
-      // A grouped launch is not cut into strips: all tiles of all groups, big or small
+      // A grouped launch is not cut into strips: all tiles of all groups, big or small; by microseconds over short contractions,
+      // else by rounds: of big tiles (one per CU, time 1; as split-K spreads a few of them over the chip at about a third of a round for the
+      // partial-tile traffic) and of small ones (two per CU, 0.6 per round, 0.3 when half empty)
       const long long g = p->groups > 1 ? p->groups : 1;
       const long long nb = g * ((p->M + pl.skewM + 255) / 256) * ((p->N + pl.skewN + 255) / 256);
       const long long ns = g * ((p->M + pl.skewM + 127) / 128) * ((p->N + pl.skewN + 127) / 128);
-      const long long nk = (pl.skewK + p->k[0] + 63) / 64;
-      double ts;
-      trio_applies(p, ns, nk, &ts);
-      if (kpair_applies(p, ns, nk)) kpair_splits(p, ns, nk, &ts);
-      const double tb = us_256(p, nb, nk);
+      const long long nk = (pl.skewK + p->k[0] + 63) / 64, cus = cu_count();
+      double tb, ts;
+      if (nk <= kShortContraction) {
+        trio_applies(p, ns, nk, &ts);
+        if (kpair_applies(p, ns, nk)) kpair_splits(p, ns, nk, &ts);
+        tb = us_256(p, nb, nk);
+      } else {
+        tb = nb * 2 <= cus ? 0.35 + 1.0 / (double)(cus / nb) : (double)cdiv(nb, cus);
+        ts = ns <= cus ? 0.3 : 0.6 * (double)cdiv(ns, 2 * cus);
+      }
       big = tb <= ts;
     }
     pl.bm = pl.bn = big ? 256 : 128;
@@ -640,7 +648,6 @@ static double small_tiles_time(long long n) {
  * there a tile's epilogue matters little and what the operands' pitches cost a kernel much.  fp32 outputs: 400 more shapes (300 to 16384 each
  * way, K 32 to 1536) as weight gradients and as rebuilds of two factors; the choice is 0.8 % slower than the fastest kernel, 1.2 % with the
  * bf16 outputs' terms (which lose up to 13 % at K = 64: 3479 x 3072 14.8 -> 16.7), 1.8 % by whole rounds. */
-constexpr long long kShortContraction = 24;
 enum { kPlain = 0, kGelu = 1, kDact = 2, kF32 = 3 };     // what the epilogue does; kF32: a weight gradient's or factor rebuild's fp32 output
 
 int epilogue_kind(const hap_gemm_problem* p) {
