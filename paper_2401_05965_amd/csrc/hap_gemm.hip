@@ -693,7 +693,7 @@ bool trio_applies(const hap_gemm_problem* p, long long n, long long nk, double* 
   const long long four_rest = cdiv(n % (2 * cus), cus), trio_rest = cdiv(n % (3 * cus), cus);
   const double four_load = 2.0 * (double)(n / (2 * cus)) + (four_rest == 1 ? 1.4 : (double)four_rest);
   const double trio_load = 3.0 * (double)(n / (3 * cus)) + (trio_rest == 1 ? 1.3 : (double)trio_rest);
-  const double four = four_fixed[e] + four_load * ((kk ? 0.44 : 0.475) * (double)nk + four_tile[e]);
+  const double four = four_fixed[e] + four_load * (0.475 * (double)nk + four_tile[e]);
   const double trio = trio_fixed[e] + trio_load * ((kk ? 0.56 : 0.485) * (double)nk + trio_tile[e]);
   const bool built = p->c_dtype == HAP_BF16 && p->in_dtype == HAP_BF16 && (p->a_kcontig || !p->b_kcontig);
   const bool take = built && n > cus && nk <= kShortContraction && trio <= four;
