@@ -420,6 +420,8 @@ struct Plan {
  * here over time there, geometric mean / worst):
  *   tiles of 32:  up to 64 of them, 152 to 159 steps 0.85 / 1.16    65 to 128, 128 to 135 steps 0.82 / 1.02, 144 to 151 0.98 / 1.24
  *                 beyond, 112 to 119 steps 0.90 / 1.00, 120 to 124 0.95 / 1.06
+ *                 experts' bwd-data, each with a weight of its own to read once per 32 rows, more than 64 tiles: 96 to 103 steps 0.81 / 1.02, 104 to 111
+ *                 0.91 / 1.08, 112 to 124 0.96 / 1.19
  *   tiles of 64, forward:  88 to 95 steps 0.92 / 1.01, 100 to 107 0.99 / 1.06    bwd-data:  84 to 87 steps 0.92 / 1.01, 92 to 95 0.99 / 1.05,
  *                 experts' 88 to 95 1.07 / 1.11, 108 to 111 1.05 / 1.13
  *   tiles of 64, bwd-weight:  up to 32 of them, 136 to 143 steps 0.95 / 1.08, 152 to 159 1.01 / 1.22    33 to 128, 104 to 111 steps 0.86 / 0.96, 112 to 119
@@ -441,7 +443,7 @@ int small_rows(const hap_gemm_problem* p, const Plan& pl) {
     if (tiles > cus) continue;
     long long most = tiles * 2 > cus ? 124 : 160;
     if (workgroup_splits(p, groups * cdiv(p->M + pl.skewM, 128) * cdiv(p->N + pl.skewN, 128), 2 * cus, nk, 4, kSmallTileBytes) > 1) {
-      if (bm == 32) most = tiles * 2 > cus ? 124 : (tiles * 4 > cus ? 136 : 160);
+      if (bm == 32) most = tiles * 4 <= cus ? 160 : (groups > 1 && p->b_kcontig ? 103 : (tiles * 2 > cus ? 124 : 136));
       else if (p->a_kcontig) most = p->b_kcontig ? 87 : 95;
       else most = tiles * 2 > cus ? 124 : (tiles * 8 > cus ? 112 : 144);
     }
