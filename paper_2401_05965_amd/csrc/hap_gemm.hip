@@ -675,8 +675,9 @@ double us_256(const hap_gemm_problem* p, long long n, long long nk) {
 
 /* Whether 128-tiles that do not run in gemm_kpair_kernel run in gemm_trio_kernel, and the estimated time either way.  n: tiles.  What
  * separates the two is the price of a workgroup: with three of them on a compute unit one's prologue and epilogue lie behind the others'
- * MFMAs; per K tile they are alike, or the two-workgroup kernel is ahead (both operands K-contiguous).  At most one tile per
- * compute unit leaves nothing to overlap.  Microseconds, two -> three workgroups (2 x 64 KB of LDS against 3 x 48):
+ * MFMAs; per K tile they are alike, or the two-workgroup kernel is ahead (both operands K-contiguous).  Up to two tiles per
+ * compute unit are all under way at once in either kernel: over 280 such products three workgroups took 0.99 to 1.17 times as long (geometric
+ * means by form and length, forward with GeLU of experts 1.04).  Microseconds, two -> three workgroups (2 x 64 KB of LDS against 3 x 48):
  *   forward 50432 x 315 over 1024 61 -> 54, with GeLU 79 -> 68; 50432 x 1024 over 315 74 -> 60, 112 -> 91
  *   bwd-data with the activation backward 17947 x 614 over 200 49.7 -> 30.7
  *   long contractions:  forward 16384 x 2731 over 2048 209 -> 199, bwd-data 16384 x 2048 over 2731 188 -> 231 */
@@ -698,7 +699,7 @@ bool trio_applies(const hap_gemm_problem* p, long long n, long long nk, double* 
   const double four = four_fixed[e] + four_load * (0.475 * (double)nk + four_tile[e]);
   const double trio = trio_fixed[e] + trio_load * ((kk ? 0.56 : 0.485) * (double)nk + trio_tile[e]);
   const bool built = p->c_dtype == HAP_BF16 && p->in_dtype == HAP_BF16 && (p->a_kcontig || !p->b_kcontig);
-  const bool take = built && n > cus && nk <= kShortContraction && trio <= four;
+  const bool take = built && n > 2 * cus && nk <= kShortContraction && trio <= four;
   *us = take ? trio : four;
   return take;
 }

@@ -210,14 +210,14 @@ def test_moe_few_tiles_per_expert(hap, full):
 
 @pytest.mark.parametrize("full", [True, False])
 def test_moe_many_tiles_over_short_contractions(hap, full):
-    """Grouped products of more than 256 tiles of 128 x 128 over short contractions run three workgroups to a compute unit: the forward with
+    """Grouped products of more than 512 tiles of 128 x 128 over short contractions run three workgroups to a compute unit: the forward with
     ragged rows (0, 1, a tile and one, all) and the GeLU epilogue, the weight gradient over token counts of none, one, a K step of 32 and one
     more, fewer steps than the ring has stages, and all."""
     def reached(want, *args, **kw):
         before = hap.hap_debug_trio_products()
         run_moe_case(hap, "bf16", *args, bias=True, full=full, fwd_ws=True, **kw)
         assert hap.hap_debug_trio_products() - before == want, args
-    reached(1, 10, 640, 512, 1280, [0, 10], [640, 0, 1, 129, 128, 300, 639, 512, 64, 333], act=True)       # forward
+    reached(2, 10, 640, 512, 1544, [0, 10], [640, 0, 1, 129, 128, 300, 639, 512, 64, 333], act=True)       # forward, dW
     reached(1, 10, 200, 520, 1288, [0, 10], [200, 0, 1, 32, 33, 64, 95, 96, 97, 199], act=True)            # dW
 
 
