@@ -443,7 +443,7 @@ int small_rows(const hap_gemm_problem* p, const Plan& pl) {
     if (tiles > cus) continue;
     long long most = tiles * 2 > cus ? 124 : 160;
     if (workgroup_splits(p, groups * cdiv(p->M + pl.skewM, 128) * cdiv(p->N + pl.skewN, 128), 2 * cus, nk, 4, kSmallTileBytes) > 1) {
-      if (bm == 32) most = tiles * 4 <= cus ? 160 : (groups > 1 && p->b_kcontig ? 103 : (tiles * 2 > cus ? 124 : 136));
+      if (bm == 32) most = tiles * 4 <= cus ? 160 : ((groups > 1 || p->group_len) && p->b_kcontig ? 103 : (tiles * 2 > cus ? 124 : 136));
       else if (p->a_kcontig) most = p->b_kcontig ? 87 : 95;
       else most = tiles * 2 > cus ? 124 : (tiles * 8 > cus ? 112 : 144);
     }
