@@ -47,55 +47,75 @@ struct Move {
  * row's ends or the shard's edge go unit by unit (UNIT: 4, 2 or 1 bytes, whatever all addresses are
  * multiples of).  A row has at most (width + 30) / 16 chunks: width / 16 rounded up where all rows start on one, and where
  * only some do, these leave the last index empty.
- * Bound: HBM.  Consecutive threads move consecutive chunks of the piece, row after row; a thread finds its row with a reciprocal.
- * STREAM: non-temporal stores (streamed() below says when).
- * 8192 x 16384 bf16 between three column shards (8402 wide the widest), buffers not touched since 1.6 GB ago, against a 64-bit division
- * per chunk, edges byte after byte and plain stores: pad 55.4 -> 49.8 us, assemble 107.1 -> 100.6, split into slots 163.8 -> 130.4 (5.2 TB/s).
- * Two or four chunks per thread, all their loads ahead of the first store: assemble 102.2 and 110.0, split 130.5 and 132.0; pieces of a few MB
- * 0.2 to 3 us slower (2000 x 1333: 6.0 -> 7.2 and 9.2). */
-template <bool STREAM, typename UNIT>
+ * Bound: HBM.  A workgroup moves 256 * UNROLL consecutive chunks of the piece, row after row; a thread has UNROLL loads in flight before its
+ * first store and finds its row with a reciprocal.  STREAM: non-temporal stores (see streamed()).
+ * One chunk per thread in small moves (2000 x 1333 bf16: two 1 us slower, four 3 us) and in moves of row shards; streamed moves of column
+ * shards, whose rows are shorter and end in cut chunks, take two, and four where a full tensor is cut into slots.  Microseconds with one / two / four,
+ * buffers not touched since 1.6 GB ago (in brackets one chunk, a 64-bit division each, edges byte after byte and plain stores):
+ *   assemble  8192 x 16384 in three column shards 100 / 102 / 110 (107)    100000 x 1024 113 / 98 / 103 (125)    row shards of 16384 x 8192 84 / 88 / 92 (92)
+ *   split     8192 x 16384 in three column slots 130 / 130 / 132 (164)     100000 x 1024 155 / 126 / 124 (233)    60000 x 1500 155 / 134 / 120 (238)
+ *             row slots of 16384 x 8192 101 / 103 / 107 (114), of 60000 x 1500 86 / 97 / 106 (103) */
+template <int UNROLL, bool STREAM, typename UNIT>
 __device__ __forceinline__ void move_rows(const Move& m) {
   const bool aligned = ((reinterpret_cast<uintptr_t>(m.dst) | (uintptr_t)m.ldd) & 15) == 0;
-  const hap_move::Chunks n = hap_move::chunks_of(m.rows, m.width, aligned);
-  const double inv = 1.0 / (double)n.per_row;
-  for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < n.total; i += (long long)gridDim.x * 256) {
+  const hap_move::Walk w = hap_move::walk_of(m.rows, m.width, aligned);
+  const long long nch = w.per_row, total = w.total, span = (long long)gridDim.x * (256 * UNROLL);
+  const double inv = 1.0 / (double)nch;
+  for (long long base = (long long)blockIdx.x * (256 * UNROLL) + threadIdx.x; base < total; base += span) {
+    u32x4 v[UNROLL];
+    long long row[UNROLL], lo[UNROLL];
+    bool whole[UNROLL];               // a whole chunk, of data or of zeros; else units or nothing
     // row and chunk of the linear index: the quotient from a reciprocal is off by one at most (total < 2^52)
-    long long r = (long long)((double)i * inv), k = i - r * n.per_row;
-    if (k < 0) { --r; k += n.per_row; }
-    if (k >= n.per_row) { ++r; k -= n.per_row; }
-    char* const drow = m.dst + r * m.ldd;
-    const char* const srow = m.src + r * m.lds;                                              // dereferenced inside the shard only
-    const long long at = 16 * k - (long long)(reinterpret_cast<uintptr_t>(drow) & 15);       // first byte of the chunk within the row
-    const long long vwidth = r < m.vrows ? m.vwidth : 0;
-    const bool data = at + 16 <= vwidth;
-    if (at >= 0 && at + 16 <= m.width && (data || at >= vwidth)) {       // a whole chunk, of data or of zeros
-      u32x4 v = {0u, 0u, 0u, 0u};
-      if (data) __builtin_memcpy(&v, srow + at, 16);
-      if constexpr (STREAM) __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(drow + at));
-      else *reinterpret_cast<u32x4*>(drow + at) = v;
-    } else {
-      // all units are fetched before the first is stored: one trip to memory instead of up to sixteen
-      constexpr int N = 16 / (int)sizeof(UNIT);
-      const hap_move::Units c = hap_move::units_of(at, m.width, vwidth, (int)sizeof(UNIT));
-      const UNIT* const sp = reinterpret_cast<const UNIT*>(srow + at);
-      UNIT* const dp = reinterpret_cast<UNIT*>(drow + at);
-      UNIT unit[N];
+    long long r = (long long)((double)base * inv), k = base - r * nch;
+    if (k < 0) { --r; k += nch; }
+    if (k >= nch) { ++r; k -= nch; }
 #pragma unroll
-      for (int x = 0; x < N; ++x) {
-        unit[x] = 0;
-        if (x >= c.first && x < c.data) unit[x] = sp[x];
+    for (int u = 0; u < UNROLL; ++u) {
+      if (u > 0) {
+        r += w.over; k += w.step;
+        if (k >= nch) { ++r; k -= nch; }
       }
+      const long long i = base + u * 256;
+      row[u] = r;
+      lo[u] = 16 * k - (long long)(reinterpret_cast<uintptr_t>(m.dst + r * m.ldd) & 15);       // first byte of the chunk within the row
+      const long long hi = lo[u] + 16;
+      const bool data = r < m.vrows && hi <= m.vwidth, zeros = r >= m.vrows || lo[u] >= m.vwidth;
+      whole[u] = i < total && lo[u] >= 0 && hi <= m.width && (data || zeros);
+      v[u] = u32x4{0u, 0u, 0u, 0u};
+      if (whole[u] && data) __builtin_memcpy(&v[u], m.src + r * m.lds + lo[u], 16);
+    }
 #pragma unroll
-      for (int x = 0; x < N; ++x)
-        if (x >= c.first && x < c.last) dp[x] = unit[x];
+    for (int u = 0; u < UNROLL; ++u) {
+      if (base + u * 256 >= total) continue;
+      const long long r = row[u], at = lo[u];
+      char* const drow = m.dst + r * m.ldd;
+      if (whole[u]) {
+        if constexpr (STREAM) __builtin_nontemporal_store(v[u], reinterpret_cast<u32x4*>(drow + at));
+        else *reinterpret_cast<u32x4*>(drow + at) = v[u];
+      } else {
+        // all units are fetched before the first is stored: one trip to memory instead of up to sixteen
+        constexpr int N = 16 / (int)sizeof(UNIT);
+        const hap_move::Units c = hap_move::units_of(at, m.width, r < m.vrows ? m.vwidth : 0, (int)sizeof(UNIT));
+        const UNIT* const sp = reinterpret_cast<const UNIT*>(m.src + r * m.lds + at);           // dereferenced inside the shard only
+        UNIT* const dp = reinterpret_cast<UNIT*>(drow + at);
+        UNIT unit[N];
+#pragma unroll
+        for (int x = 0; x < N; ++x) {
+          unit[x] = 0;
+          if (x >= c.first && x < c.data) unit[x] = sp[x];
+        }
+#pragma unroll
+        for (int x = 0; x < N; ++x)
+          if (x >= c.first && x < c.last) dp[x] = unit[x];
+      }
     }
   }
 }
 
-template <bool STREAM, typename UNIT>
+template <int UNROLL, bool STREAM, typename UNIT>
 __global__ __launch_bounds__(256) void copy_pieces_kernel(const PieceArgs a) {
   const int j = blockIdx.y;
-  move_rows<STREAM, UNIT>({a.src[j], a.out + a.dst_off[j], a.ld_src[j], a.ld_out, a.rows[j], a.width[j], a.rows[j], a.width[j]});
+  move_rows<UNROLL, STREAM, UNIT>({a.src[j], a.out + a.dst_off[j], a.ld_src[j], a.ld_out, a.rows[j], a.width[j], a.rows[j], a.width[j]});
 }
 
 /* f(value of the widest unit type that every address is a multiple of) */
@@ -115,13 +135,14 @@ void with_unit(uintptr_t phases, F&& f) {
  * Past the last-level cache the two are alike with a reader (assemble 256 MB 213.0 -> 213.9, 500 MB 415.0 -> 416.5), without one the gain stays (110.1 -> 100.6). */
 inline bool streamed(long long bytes) { return bytes >= (72LL << 20); }
 
-inline dim3 move_grid(long long chunks, int pieces) {
-  long long gx = (chunks + 255) / 256;
+inline dim3 move_grid(long long chunks, int unroll, int pieces) {
+  long long gx = (chunks + 256 * unroll - 1) / (256 * unroll);
   if (gx > 256 * 32) gx = 256 * 32;        // grid-stride beyond 32 blocks per CU and piece
   return dim3((unsigned)gx, (unsigned)pieces);
 }
 
-int launch_pieces(const PieceArgs& a, hipStream_t s) {
+/* columns: the pieces are column ranges. */
+int launch_pieces(const PieceArgs& a, bool columns, hipStream_t s) {
   long long most = 0, bytes = 0;
   uintptr_t phases = (uintptr_t)a.out | (uintptr_t)a.ld_out;       // its lowest bits: what every address is a multiple of
   for (int j = 0; j < a.m; ++j) {
@@ -132,11 +153,11 @@ int launch_pieces(const PieceArgs& a, hipStream_t s) {
     bytes += a.rows[j] * a.width[j];
   }
   if (most == 0) return HAP_OK;
-  const dim3 grid = move_grid(most, a.m);
   with_unit(phases, [&](auto unit) {
     using U = decltype(unit);
-    if (streamed(bytes)) hipLaunchKernelGGL((copy_pieces_kernel<true, U>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((copy_pieces_kernel<false, U>), grid, dim3(256), 0, s, a);
+    if (!streamed(bytes)) hipLaunchKernelGGL((copy_pieces_kernel<1, false, U>), move_grid(most, 1, a.m), dim3(256), 0, s, a);
+    else if (columns) hipLaunchKernelGGL((copy_pieces_kernel<2, true, U>), move_grid(most, 2, a.m), dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((copy_pieces_kernel<1, true, U>), move_grid(most, 1, a.m), dim3(256), 0, s, a);
   });
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hap_fail(HAP_EDEVICE, "piece copy launch: %s", hipGetErrorString(e));
@@ -155,10 +176,10 @@ struct SplitArgs {
 };
 
 /* The reverse movement: slot j (blockIdx.y) receives shard j's range of the full tensor and zeros up to the slot's extent. */
-template <bool STREAM, typename UNIT>
+template <int UNROLL, bool STREAM, typename UNIT>
 __global__ __launch_bounds__(256) void split_pieces_kernel(const SplitArgs a) {
   const int j = blockIdx.y;
-  move_rows<STREAM, UNIT>({a.src + a.src_off[j], a.dst[j], a.ld_src, a.ld_dst[j], a.srows, a.swidth, a.vrows[j], a.vwidth[j]});
+  move_rows<UNROLL, STREAM, UNIT>({a.src + a.src_off[j], a.dst[j], a.ld_src, a.ld_dst[j], a.srows, a.swidth, a.vrows[j], a.vwidth[j]});
 }
 
 int check_desc(const hap_gather_desc* d) {
@@ -200,7 +221,7 @@ int hap_allgather_pad(const hap_gather_desc* d, int shard_index, const void* sha
   a.m = 1; a.out = static_cast<char*>(slot); a.ld_out = ld_slot * d->elem_bytes;
   a.src[0] = static_cast<const char*>(shard); a.ld_src[0] = ld_shard * d->elem_bytes;
   a.rows[0] = r; a.width[0] = c * d->elem_bytes;
-  return launch_pieces(a, static_cast<hipStream_t>(stream));
+  return launch_pieces(a, d->dim == 1, static_cast<hipStream_t>(stream));
 }
 
 int hap_allgather_assemble(const hap_gather_desc* d, const void* const* pieces, const int64_t* ld_pieces, void* out, int64_t ld_out, void* stream) {
@@ -222,7 +243,7 @@ int hap_allgather_assemble(const hap_gather_desc* d, const void* const* pieces, 
     a.dst_off[j] = (d->dim == 0 ? lo * ld_out : lo) * d->elem_bytes;
     a.rows[j] = r; a.width[j] = c * d->elem_bytes;
   }
-  return launch_pieces(a, static_cast<hipStream_t>(stream));
+  return launch_pieces(a, d->dim == 1, static_cast<hipStream_t>(stream));
 }
 
 int hap_reducescatter_split(const hap_gather_desc* d, const void* full, int64_t ld_full, void* const* slots, const int64_t* ld_slots, void* stream) {
@@ -250,13 +271,15 @@ int hap_reducescatter_split(const hap_gather_desc* d, const void* full, int64_t 
     a.vwidth[j] = (d->dim == 0 ? d->cols : hi - lo) * d->elem_bytes;
   }
   const long long chunks = srows * ((a.swidth + 30) / 16);
-  const dim3 grid = move_grid(chunks, d->m);
   uintptr_t phases = (uintptr_t)a.src | (uintptr_t)a.ld_src | (uintptr_t)a.swidth;
   for (int j = 0; j < d->m; ++j) phases |= (uintptr_t)a.dst[j] | (uintptr_t)a.ld_dst[j] | (uintptr_t)a.src_off[j] | (uintptr_t)a.vwidth[j];
+  const bool stream_stores = streamed(srows * a.swidth * d->m);
   with_unit(phases, [&](auto unit) {
     using U = decltype(unit);
-    if (streamed(srows * a.swidth * d->m)) hipLaunchKernelGGL((split_pieces_kernel<true, U>), grid, dim3(256), 0, static_cast<hipStream_t>(stream), a);
-    else hipLaunchKernelGGL((split_pieces_kernel<false, U>), grid, dim3(256), 0, static_cast<hipStream_t>(stream), a);
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    if (!stream_stores) hipLaunchKernelGGL((split_pieces_kernel<1, false, U>), move_grid(chunks, 1, d->m), dim3(256), 0, s, a);
+    else if (d->dim == 1) hipLaunchKernelGGL((split_pieces_kernel<4, true, U>), move_grid(chunks, 4, d->m), dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((split_pieces_kernel<1, true, U>), move_grid(chunks, 1, d->m), dim3(256), 0, s, a);
   });
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hap_fail(HAP_EDEVICE, "slot split launch: %s", hipGetErrorString(e));

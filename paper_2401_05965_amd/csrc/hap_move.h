@@ -7,14 +7,20 @@
 
 namespace hap_move {
 
-/* The chunks of `rows` rows of `width` bytes, numbered row after row.  An empty move has none (a device that owns nothing still has its
- * place in the launch).  aligned: all rows start on a 16-byte boundary; else a row may straddle one chunk more. */
-struct Chunks { long long per_row, total; };
+/* The chunks of `rows` rows of `width` bytes, numbered row after row; a thread walks them 256 apart.  An empty move has none (a device that
+ * owns nothing still has its place in the launch). */
+struct Walk {
+  long long per_row, total;
+  int over, step;                    // 256 chunks on: `over` rows and `step` chunks (and one more row where that passes the row's last one)
+};
 
-constexpr Chunks chunks_of(long long rows, long long width, bool aligned) {
-  if (rows <= 0 || width <= 0) return {1, 0};
+/* aligned: all rows start on a 16-byte boundary; else a row may straddle one chunk more. */
+constexpr Walk walk_of(long long rows, long long width, bool aligned) {
+  if (rows <= 0 || width <= 0) return {1, 0, 0, 0};
   const long long per_row = (width + (aligned ? 15 : 30)) / 16;
-  return {per_row, rows * per_row};
+  const int short_row = per_row < 256 ? (int)per_row : 0;
+  const int over = short_row ? 256 / short_row : 0;
+  return {per_row, rows * per_row, over, 256 - over * short_row};
 }
 
 /* Units of `unit` bytes of the chunk whose first byte is byte `at` of a row (negative where it starts before the row): [first, last) lie in

@@ -182,3 +182,30 @@ def test_large_pieces_move_whole_and_ragged_chunks(hap, eb, cols, shift, mb):
     hap.hap_allgather_assemble(desc, [at(slots, shift + j * rows * cap) for j in range(m)], [cap] * m, at(out, shift), ld)
     back = out.cpu()
     assert torch.equal(back[shift:].view(rows, ld)[:, :cols], full) and (back[:shift] == 9).all() and (back[shift:].view(rows, ld)[:, cols:] == 9).all()
+
+
+@pytest.mark.parametrize("eb,cols,shift", [(1, 4099, 1), (2, 1030, 3), (4, 600, 0)])
+def test_large_row_shards_move_whole_and_ragged_chunks(hap, eb, cols, shift):
+    """The same for row shards, 75 MB and more: an empty one, slots that end in rows of zeros."""
+    import torch
+    dt = {1: torch.uint8, 2: torch.int16, 4: torch.int32}[eb]
+    rows = (76 << 20) // (cols * eb) + 1
+    offs = [0, rows // 2, rows // 2, rows - 7, rows]
+    m, cap, ld = 4, max(offs[i + 1] - offs[i] for i in range(4)), cols + 2
+    g = torch.Generator().manual_seed(7)
+    full = torch.randint(-2 ** 62, 2 ** 62, (rows, cols), generator=g).to(dt)
+    src = torch.zeros(rows * ld + shift, dtype=dt); src[shift:].view(rows, ld)[:, :cols] = full
+    src = src.cuda()
+    slots = torch.full((m * cap * cols + shift + 4,), 7, dtype=dt, device="cuda")
+    at = lambda t, k: t.data_ptr() + k * eb
+    desc = hap.GatherDesc(rows, cols, 0, offs, eb)
+    hap.hap_reducescatter_split(desc, at(src, shift), ld, [at(slots, shift + j * cap * cols) for j in range(m)], [cols] * m)
+    got = slots.cpu()
+    assert (got[:shift] == 7).all() and (got[shift + m * cap * cols:] == 7).all()
+    for j in range(m):
+        want = torch.zeros((cap, cols), dtype=dt); want[:offs[j + 1] - offs[j]] = full[offs[j]:offs[j + 1]]
+        assert torch.equal(got[shift + j * cap * cols:shift + (j + 1) * cap * cols].view(cap, cols), want), j
+    out = torch.full((rows * ld + shift,), 9, dtype=dt, device="cuda")
+    hap.hap_allgather_assemble(desc, [at(slots, shift + j * cap * cols) for j in range(m)], [cols] * m, at(out, shift), ld)
+    back = out.cpu()
+    assert torch.equal(back[shift:].view(rows, ld)[:, :cols], full) and (back[:shift] == 9).all() and (back[shift:].view(rows, ld)[:, cols:] == 9).all()

@@ -20,11 +20,18 @@ int main() {
   for (long long rows = 0; rows <= 3; ++rows)
     for (long long width : widths)
       for (int aligned = 0; aligned < 2; ++aligned) {
-        const Chunks n = chunks_of(rows, width, aligned);
-        if (n.per_row < 1) fail("divisor", rows, width, aligned, n.per_row);          // a thread's row is its index over this
-        if (rows == 0 || width == 0) { if (n.total != 0) fail("empty", rows, width, aligned, n.total); continue; }
+        const Walk w = walk_of(rows, width, aligned);
+        if (rows == 0 || width == 0) { if (w.total != 0) fail("empty", rows, width, aligned, w.total); continue; }
         // the last byte of a row lies in the last chunk, on or off the 16-byte grid
-        if (n.total != rows * n.per_row || n.per_row * 16 < width + (aligned ? 0 : 15) || n.per_row * 16 > width + (aligned ? 15 : 30)) fail("chunks", rows, width, aligned, n.per_row);
+        if (w.total != rows * w.per_row || w.per_row * 16 < width + (aligned ? 0 : 15) || w.per_row * 16 > width + (aligned ? 15 : 30)) fail("chunks", rows, width, aligned, w.per_row);
+        for (long long at = 0; at < w.total && at < 2000; at += 37) {
+          long long r = at / w.per_row, k = at % w.per_row;
+          for (int u = 1; u <= 3; ++u) {
+            r += w.over; k += w.step;
+            if (k >= w.per_row) { ++r; k -= w.per_row; }
+            if (r != (at + 256 * u) / w.per_row || k != (at + 256 * u) % w.per_row) fail("walk", rows, width, aligned, at);
+          }
+        }
       }
   // byte by byte: which units of a chunk lie in the row, which of those in the shard
   for (int unit = 1; unit <= 4; unit *= 2)
