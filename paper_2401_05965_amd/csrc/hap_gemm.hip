@@ -514,15 +514,21 @@ Plan make_plan(const hap_gemm_problem* p) {
   } else {
     bool big = p->tile ? p->tile == 256 : (p->M + pl.skewM > 128 && p->N + pl.skewN > 128);
     if (big && !p->tile && (p->groups > 1 || p->group_len)) {
-      // A grouped launch is not cut into strips: all tiles of all groups, big or small; by microseconds over short contractions,
-      // else by rounds: of big tiles (one per CU, time 1; as split-K spreads a few of them over the chip at about a third of a round for the
-      // partial-tile traffic) and of small ones (two per CU, 0.6 per round, 0.3 when half empty)
+      // A grouped launch is not cut into strips: all tiles of all groups, big or small; by microseconds or by rounds: of big tiles (one per
+      // CU, time 1; as split-K spreads a few of them over the chip at about a third of a round for the partial-tile traffic) and of small
+      // ones (two per CU, 0.6 per round, 0.3 when half empty).
+      // Microseconds are the better up to kShortContraction, and for weight gradients past 96 K tiles and, with bf16 outputs, wherever big
+      // tiles fill more than half of the chip.  Small -> big tiles, experts x rows x columns over K, where only microseconds say big:
+      //   10 x 768 x 3072 over 1024 to 2048 rows 125 -> 107    12 x 1024 x 1976 over up to 5878 275 -> 212    5 x 256 x 3680 over 9545 186 -> 118
+      // and where they say so wrongly:
+      //   7 x 256 x 2960 over 3094 50.5 -> 54.3    5 x 2048 x 696 over 5767 81.6 -> 86.1    bwd-data 6 x 2039 x 1024 over 1640 50.8 -> 63.6
       const long long g = p->groups > 1 ? p->groups : 1;
       const long long nb = g * ((p->M + pl.skewM + 255) / 256) * ((p->N + pl.skewN + 255) / 256);
       const long long ns = g * ((p->M + pl.skewM + 127) / 128) * ((p->N + pl.skewN + 127) / 128);
       const long long nk = (pl.skewK + p->k[0] + 63) / 64, cus = cu_count();
+      const bool long_us = !p->a_kcontig && (nk > 96 || (nb * 2 > cus && p->c_dtype == HAP_BF16));
       double tb, ts;
-      if (nk <= kShortContraction) {
+      if (nk <= kShortContraction || long_us) {
         trio_applies(p, ns, nk, &ts);
         if (kpair_applies(p, ns, nk)) kpair_splits(p, ns, nk, &ts);
         tb = us_256(p, nb, nk);
