@@ -132,6 +132,8 @@ void with_unit(uintptr_t phases, F&& f) {
  *   assemble:  30 MB 27.3 -> 30.4 (19.5 -> 18.1)    53 MB 42.1 -> 46.5 (28.3 -> 26.5)    78 MB 70.1 -> 66.5 (40.1 -> 38.0)    128 MB 120.2 -> 106.0 (56.9 -> 52.2)
  *   split:     47 MB 36.4 -> 40.2 (25.4 -> 22.4)    70 MB 54.2 -> 56.1 (34.7 -> 30.7)    82 MB 66.7 -> 63.2 (37.1 -> 33.4)    197 MB 169.3 -> 153.6 (84.1 -> 74.5)
  *   pad:       36 MB 25.1 -> 29.2 (16.1 -> 14.9)    66 MB 47.7 -> 52.1 (30.0 -> 27.8)    80 MB 64.0 -> 61.6 (34.9 -> 32.2)    131 MB 112.7 -> 106.6 (52.8 -> 49.8)
+ * Pad, assemble and split of one tensor in turn, 26 of 40 to 160 MB, the line at 72 / 128 MB: 3 x 102 MB of columns 104.5 / 120.2, 4 x 90 MB of columns
+ * 90.6 / 113.5, 5 x 72 MB of rows 73.4 / 81.8; none is slower with 72, whether a pass repeats on its buffers or goes around three sets of them.
  * Past the last-level cache the two are alike with a reader (assemble 256 MB 213.0 -> 213.9, 500 MB 415.0 -> 416.5), without one the gain stays (110.1 -> 100.6). */
 inline bool streamed(long long bytes) { return bytes >= (72LL << 20); }
 

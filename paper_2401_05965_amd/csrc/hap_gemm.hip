@@ -655,7 +655,10 @@ static double small_tiles_time(long long n) {
  * epilogue and the contraction, 4 to 16 %.  Over 24 to 48 K tiles the two are alike, beyond 48 the rounds are 1 to 1.5 % better for bwd-data:
  * there a tile's epilogue matters little and what the operands' pitches cost a kernel much.  fp32 outputs: 400 more shapes (300 to 16384 each
  * way, K 32 to 1536) as weight gradients and as rebuilds of two factors; the choice is 0.8 % slower than the fastest kernel, 1.2 % with the
- * bf16 outputs' terms (which lose up to 13 % at K = 64: 3479 x 3072 14.8 -> 16.7), 1.8 % by whole rounds. */
+ * bf16 outputs' terms (which lose up to 13 % at K = 64: 3479 x 3072 14.8 -> 16.7), 1.8 % by whole rounds.
+ * Over 1200 fresh products of up to 24 K tiles, those of the small-output and the K-pair kernel among them: forward / with GeLU / bwd-data / with
+ * gelu' / weight gradient / in fp32 1.2 / 1.4 / 1.4 / 1.9 / 1.3 / 1.0 % off the fastest kernel, by whole rounds 3.0 / 4.3 / 5.8 / 9.3 / 8.0 / 1.2; of the
+ * 860 that take 15 us or more, rounds are more than 3 % better for 21 (forward 14701 x 680 over 737 30.1 against 34.5), worse for 202. */
 enum { kPlain = 0, kGelu = 1, kDact = 2, kF32 = 3 };     // what the epilogue does; kF32: a weight gradient's or factor rebuild's fp32 output
 
 int epilogue_kind(const hap_gemm_problem* p) {
